@@ -234,6 +234,9 @@ static uint32_t grid_cap(uint64_t work, uint32_t lo, uint32_t hi)
     return uint32_t(b);
 }
 
+// expected boundary cells of a fiber: about one shell of the cylinder widened by 1
+static double shell_cells(const lbm_fiber &f) { return 2.0 * M_PI * (f.radius + 1.0) * (f.length + 2.0); }
+
 // (re)allocate the per-fiber buffers for c->np fibers and upload states
 static lbm_status upload_particles(lbm_ctx *c)
 {
@@ -270,9 +273,7 @@ static lbm_status upload_particles(lbm_ctx *c)
         soff[i] = uint32_t(total);
         scap[i] = uint32_t(cap);
         total += double(scap[i]);
-        // expected boundary cells: about one shell of the cylinder widened by 1
-        const double rs = c->fib[i].radius + 1.0, ls = c->fib[i].length + 2.0;
-        maxsurf = std::max(maxsurf, 2.0 * M_PI * rs * ls);
+        maxsurf = std::max(maxsurf, shell_cells(c->fib[i]));
     }
     if (total >= 4294967295.0) return fail(c, LBM_E_ARG, "boundary list too large");
     c->list_cap = uint32_t(total);
@@ -280,10 +281,11 @@ static lbm_status upload_particles(lbm_ctx *c)
     HIPCHK(c, dalloc(c, &c->list_mask, c->list_cap));
     HIPCHK(c, hipMemcpyAsync(c->seg_off, soff.data(), np * sizeof(uint32_t), hipMemcpyHostToDevice, c->st));
     HIPCHK(c, hipMemcpyAsync(c->seg_cap, scap.data(), np * sizeof(uint32_t), hipMemcpyHostToDevice, c->st));
-    // boundary launch: blocks per fiber segment, about one entry per thread
-    // for the largest fiber (each pass over a segment is a chain of
-    // dependent loads, so extra passes add latency, not throughput)
-    c->bpf = std::max(1, std::min(16, int(std::ceil(maxsurf / 256.0))));
+    // boundary launch: waves per fiber segment, one entry per lane for the
+    // largest fiber (each pass over a segment is a chain of dependent loads,
+    // so extra passes add latency, not throughput; waves beyond the list's
+    // end return at once).  A segment holds about 1.2 shells.
+    c->bpf = std::max(1, std::min(64, int(std::ceil(1.35 * maxsurf / 64.0))));
     c->remap_grid = uint32_t(np * c->nslab);
     c->bnd_grid = uint32_t(np * c->bpf);
     std::vector<PState> hs(np);
@@ -1044,6 +1046,17 @@ struct BufRef {
     void *p;
     size_t bytes;
 };
+// Workgroup slots of the stabilization buffer in a checkpoint.  Only the head
+// carries state (a step writes its slots before it reads them); the count is
+// part of the file format: the sweep's workgroups and one slot per 256
+// expected boundary cells of the largest fiber, at most 16, for every fiber.
+static uint32_t stab_slots_saved(const lbm_ctx *c)
+{
+    double m = 0.0;
+    for (const lbm_fiber &f : c->fib) m = std::max(m, shell_cells(f));
+    const int per = std::max(1, std::min(16, int(std::ceil(m / 256.0))));
+    return std::max(STAB_SCAN_GRID, c->sweep_grid + uint32_t(c->np) * uint32_t(per));
+}
 static std::vector<BufRef> state_buffers(lbm_ctx *c)
 {
     std::vector<BufRef> v;
@@ -1054,8 +1067,7 @@ static std::vector<BufRef> state_buffers(lbm_ctx *c)
     v.push_back({c->pid, nc * sizeof(int32_t)});
     v.push_back({c->ctr, sizeof(DevCounters)});
     if (c->p.stabilize) {
-        const uint32_t nslot = std::max(STAB_SCAN_GRID, c->sweep_grid + c->bnd_grid);
-        v.push_back({c->stab, (size_t(STAB_HEAD) + 4 * size_t(nslot)) * sizeof(double)});
+        v.push_back({c->stab, (size_t(STAB_HEAD) + 4 * size_t(stab_slots_saved(c))) * sizeof(double)});
         v.push_back({c->cov, (size_t(c->cov_cap) + 1) * sizeof(uint32_t)});
     }
     const size_t np = size_t(c->np);

@@ -59,7 +59,6 @@ struct BatchDev {
     PState *ps;                // [ncase][2]: state at even / odd time levels
     Box *box_cur;              // [ncase]
     long long *abc;            // [ncase][NABC] population-free integer sums (SA, SB, SC) for the next step
-    long long *foreign;        // [NACC] sink for links to another fiber (none in a one-fiber case)
     double *ft;                // [ncase][6]
     double *hist;              // [ncase][hist_cap][19]
     int64_t hist_cap;
@@ -81,21 +80,6 @@ struct BShared {
     uint32_t aoff[BMAXP + 1];
     uint32_t nlist;
 };
-
-// A value that every lane loads from the same address: keep it in scalar
-// registers (the compiler cannot prove that memory written by the kernel is
-// uniform when read back).
-template <typename T>
-__device__ __forceinline__ T uniform(const T &v)
-{
-    static_assert(sizeof(T) % 4 == 0, "32-bit words");
-    T r;
-    const int *s = reinterpret_cast<const int *>(&v);
-    int *d = reinterpret_cast<int *>(&r);
-#pragma unroll
-    for (int k = 0; k < int(sizeof(T) / 4); ++k) d[k] = __builtin_amdgcn_readfirstlane(s[k]);
-    return r;
-}
 
 template <typename S>
 using RefillT = typename std::conditional<std::is_same<S, bf16s>::value, uint16_t, S>::type;
@@ -127,6 +111,34 @@ __device__ __forceinline__ void block_sum(const long long (&acc)[NK], BShared<BS
     __syncthreads();
 }
 
+// Links of a case's boundary cells, handled by the lane that updates the
+// cell.  A case has one fiber, so every link goes to it (no owner to look
+// up) and its state sits in scalar registers.
+template <typename S, bool ODD>
+struct OwnLinks {
+    using R = typename St<S>::R;
+    S *f;
+    const Geo &g;
+    const Phys<R> &ph;
+    PState s;
+    DevCounters *ctr;
+    long long acc[6];
+    template <int q>
+    __device__ __forceinline__ void link(bool lk, R v, uint32_t own, uint32_t nb, uint32_t x, uint32_t y, uint32_t z)
+    {
+        if (!lk) return;
+        const double c[3] = {double(CX[q]), double(CY[q]), double(CZ[q])};
+        const uint32_t yc[3] = {x == 0 && CX[q] < 0 ? g.nx - 1 : (x + 1 == g.nx && CX[q] > 0 ? 0 : x + CX[q]),
+                                y == 0 && CY[q] < 0 ? g.ny - 1 : (y + 1 == g.ny && CY[q] > 0 ? 0 : y + CY[q]),
+                                z + CZ[q]};   // walls at the z ends
+        double r[3];
+        const R out = link_bounce<R>(v, 6.0 * wq(q) * double(ph.rho0), c, yc, s.X, s.V, s.W, g, r);
+        if (!isfinite(double(v))) atomicOr(&ctr->err_unstable, 1u);
+        link_terms(acc, double(v), wq(q), c, r, double(ph.rho0));
+        St<S>::st(f, ODD ? uint64_t(opp(q)) * g.qstride + own : uint64_t(q) * g.qstride + nb, out, ph.scale);
+    }
+};
+
 // ------------------------------------------------------------------ sweep of one case
 template <typename S, bool ODD, int BS>
 __device__ __forceinline__ void case_sweep(const BatchDev &bd, S *__restrict__ f, const uint8_t *__restrict__ flags,
@@ -136,20 +148,16 @@ __device__ __forceinline__ void case_sweep(const BatchDev &bd, S *__restrict__ f
     const Phys<R> &ph = case_phys<R>(cd);
     S *fc = f + cd.f_off;
     const uint8_t *flc = flags + cd.cell_off;
+    NoLinks none;
     for (uint32_t cell = threadIdx.x; cell < cd.g.ncell; cell += BS)
-        if (!flc[cell]) update_cell<S, ODD, false>(fc, cd.g, ph, cell, 0u, -1, nullptr, BndData{});
-    BndData b{};
-    b.pid = bd.pid + cd.cell_off;
-    b.ps = bd.ps + size_t(c) * 2 + size_t(s & 1);
-    b.mea = bd.foreign;
-    b.ctr = bd.ctr;
+        if (!flc[cell]) update_cell<S, ODD, false, false, false>(fc, cd.g, ph, cell, 0u, none);
     const uint32_t cnt = uniform(bd.list_n[c]);
     const uint32_t n = cnt < cd.list_cap ? cnt : cd.list_cap;
     const uint32_t *lc = bd.list_cell + cd.list_off, *lm = bd.list_mask + cd.list_off;
-    long long acc[6] = {0, 0, 0, 0, 0, 0};
+    OwnLinks<S, ODD> links{fc, cd.g, ph, uniform(bd.ps[size_t(c) * 2 + size_t(s & 1)]), bd.ctr, {0, 0, 0, 0, 0, 0}};
     for (uint32_t r = threadIdx.x; r < n; r += BS)
-        update_cell<S, ODD, true, 6>(fc, cd.g, ph, lc[r], lm[r], 0, acc, b);
-    block_sum<BS, 6>(acc, sh, sh.tot);
+        update_cell<S, ODD, true, false, false>(fc, cd.g, ph, lc[r], lm[r], links);
+    block_sum<BS, 6>(links.acc, sh, sh.tot);
 }
 
 // ------------------------------------------------------------------ particle phase of one case
@@ -290,7 +298,7 @@ __device__ __forceinline__ void case_particles(const BatchDev &bd, int c, const 
             flc[cell] = F_SOLID;
             continue;
         }
-        const uint32_t mask = fiber_mask(pidc, g, x, y, z);
+        const uint32_t mask = fiber_mask(pidc, g, x, y, z, 0);
         if (!mask) {
             flc[cell] = 0;
             continue;
@@ -405,7 +413,7 @@ struct lbm_batch {
     uint32_t *list_cell = nullptr, *list_mask = nullptr, *list_n = nullptr;
     PState *ps = nullptr;
     Box *box_cur = nullptr;
-    long long *abc = nullptr, *foreign = nullptr;
+    long long *abc = nullptr;
     double *ft = nullptr, *hist = nullptr, *traj = nullptr;
     int64_t *steps_d = nullptr, *traj_pos = nullptr;
     DevCounters *ctr = nullptr;
@@ -528,7 +536,6 @@ static BatchDev batch_dev(lbm_batch *b)
     d.ps = b->ps;
     d.box_cur = b->box_cur;
     d.abc = b->abc;
-    d.foreign = b->foreign;
     d.ft = b->ft;
     d.hist = b->hist;
     d.hist_cap = b->p.history_capacity;
@@ -591,7 +598,6 @@ static lbm_status reset_state(lbm_batch *b)
     BHIP(b, hipMemsetAsync(b->list_n, 0, b->ncase * sizeof(uint32_t), b->st));
     BHIP(b, hipMemsetAsync(b->box_cur, 0, b->ncase * sizeof(Box), b->st));
     BHIP(b, hipMemsetAsync(b->abc, 0, size_t(b->ncase) * NABC * sizeof(long long), b->st));
-    BHIP(b, hipMemsetAsync(b->foreign, 0, NACC * sizeof(long long), b->st));
     BHIP(b, hipMemsetAsync(b->ft, 0, size_t(b->ncase) * 6 * sizeof(double), b->st));
     BHIP(b, hipMemsetAsync(b->steps_d, 0, b->ncase * sizeof(int64_t), b->st));
     BHIP(b, hipMemsetAsync(b->traj_pos, 0, b->ncase * sizeof(int64_t), b->st));
@@ -675,7 +681,6 @@ lbm_status lbm_batch_destroy(lbm_batch *b)
     bfree(b->ps);
     bfree(b->box_cur);
     bfree(b->abc);
-    bfree(b->foreign);
     bfree(b->ft);
     bfree(b->hist);
     bfree(b->traj);
@@ -793,7 +798,7 @@ lbm_status lbm_batch_create(const lbm_batch_params *p, const lbm_batch_case *cas
         balloc(b, &b->pid, b->ncells) != hipSuccess || balloc(b, &b->list_cell, b->nlist) != hipSuccess ||
         balloc(b, &b->list_mask, b->nlist) != hipSuccess || balloc(b, &b->list_n, ncases) != hipSuccess ||
         balloc(b, &b->ps, size_t(ncases) * 2) != hipSuccess || balloc(b, &b->box_cur, ncases) != hipSuccess ||
-        balloc(b, &b->abc, size_t(ncases) * NABC) != hipSuccess || balloc(b, &b->foreign, NACC) != hipSuccess ||
+        balloc(b, &b->abc, size_t(ncases) * NABC) != hipSuccess ||
         balloc(b, &b->ft, size_t(ncases) * 6) != hipSuccess ||
         balloc(b, &b->hist, size_t(ncases) * size_t(p->history_capacity) * 19) != hipSuccess ||
         balloc(b, &b->traj, 13) != hipSuccess || balloc(b, &b->steps_d, ncases) != hipSuccess ||

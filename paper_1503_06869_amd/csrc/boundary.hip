@@ -1,53 +1,47 @@
-// boundary.hip -- the boundary-list work of one time step, in one launch:
-//   blocks [0, np*bpf)        update of the boundary cells (the fused
-//                             stream-collide of the bulk sweep with the
-//                             moving-obstacle bounce-back, Eq. LBMMovWall)
-//                             and the population-dependent momentum-exchange
-//                             sums F0, M0 of their fiber links (Eq.
-//                             LBMhydrodynForce and the torque after it);
-//   blocks [np*bpf, 2*np*bpf) the population-free part of the exchange (A,
-//                             B, C; linear in the surface velocity) of the
-//                             same links as exact integer sums at the
-//                             current poses (see abc_restore).
-// Both halves walk the same list segments (block (fiber p, part j)) and add
-// into disjoint slots of the sums, so they run side by side.
+// boundary.hip -- the boundary-list work of one time step, in one launch: the
+// update of the cells next to fibers (the fused stream-collide of the bulk
+// sweep), the moving-obstacle bounce-back of their fiber links (Eq.
+// LBMMovWall), and the links' momentum exchange (Eq. LBMhydrodynForce and
+// the torque after it): the velocity-free sums F0, M0 and the integer sums
+// of the part linear in the surface velocity (A, B, C; see abc_restore).
+//
+// One wave per workgroup takes 64 entries of a fiber's list segment, in two
+// halves.  First each lane updates its cell; the post-collision values of
+// fiber links go to a queue in LDS.  Then the lanes share the queue, one
+// link per lane: a boundary cell has about five fiber links among its 18
+// directions, so a wave works through 5-6 full rounds of links instead of 18
+// rounds in which a third of the lanes take part, and each round's code
+// exists once.  The kernel is bound by the latency of this FP64 and 64-bit
+// integer chain, not by memory (57,000 cells move 9 MB).  A list entry whose
+// fiber cells all belong to the segment's own fiber (LIST_HOME, set where the
+// list is built; all entries unless two fibers are within a cell of each
+// other) takes that fiber's state from scalar registers and needs no
+// owner look-ups.
 #include "lbm_sweep_dev.h"
 
 namespace lbm {
 
-template <typename S, bool ODD, bool STAB, bool XYW>
-__device__ __forceinline__ void bnd_block(S *__restrict__ f, const Geo &g, const Phys<typename St<S>::R> &ph,
-                                          const BndData &b, int blk, const double *stab, double *part)
-{
-    // block (fiber p, part j) of the fiber's list segment
-    const int p = blk / b.bpf, j = blk % b.bpf;
-    const uint32_t cnt = b.seg_cnt[p], cap = b.seg_cap[p];
-    const uint32_t n = cnt < cap ? cnt : cap, off = b.seg_off[p];
-    long long acc[6] = {0, 0, 0, 0, 0, 0};
-    StabAcc<typename St<S>::R> sa;
-    if constexpr (STAB) stab_begin(sa, stab);
-    for (uint32_t r = j * 256u + threadIdx.x; r < n; r += b.bpf * 256u) {
-        const uint32_t e = off + r;
-        update_cell<S, ODD, true, 6, STAB, XYW>(f, g, ph, b.cell[e], b.mask[e], p, acc, b, &sa);
+// links of one wave's 64 cells: capacity for every direction of every cell
+constexpr uint32_t QCAP = 64u * (Q - 1);
+
+template <typename R>
+struct LinkQueue {
+    uint32_t *code;   // bits 0-5 the cell's lane, 6-10 q, 11-16 c + 1 (2 bits a component), 17 tag
+    R *val;           // post-collision value
+    uint32_t n;       // wave-uniform among the lanes that take part
+    uint32_t tag;     // the lane, bit 17: owners to be looked up
+    template <int q>
+    __device__ __forceinline__ void link(bool lk, R v, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t)
+    {
+        const unsigned long long m = __ballot(lk);
+        if (lk) {
+            const uint32_t at = n + __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u));
+            code[at] = tag | uint32_t(q << 6 | (CX[q] + 1) << 11 | (CY[q] + 1) << 13 | (CZ[q] + 1) << 15);
+            val[at] = v;
+        }
+        n += uint32_t(__popcll(m));
     }
-    if constexpr (STAB) stab_flush(sa, part + 4 * size_t(blk));
-    // integer sums: exact, so the reduction order does not matter
-    __shared__ long long red[4][6];
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-        long long v = acc[k];
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-        if (lane == 0) red[wid][k] = v;
-    }
-    __syncthreads();
-    if (threadIdx.x < 6) {
-        const int k = threadIdx.x;
-        const long long v = red[0][k] + red[1][k] + red[2][k] + red[3][k];
-        if (v) atomicAdd(reinterpret_cast<unsigned long long *>(b.mea + size_t(p) * NACC + k),
-                         (unsigned long long)v);
-    }
-}
+};
 
 }  // namespace lbm
 
@@ -56,84 +50,178 @@ __device__ __forceinline__ void bnd_block(S *__restrict__ f, const Geo &g, const
 
 namespace lbm {
 
-// The integer sums SA, SB, SC of every link of a list segment's part j at
-// the poses ps (links to fiber p into the block's sums, links to another
-// fiber with atomics into that fiber's): block (fiber p, part j).
-__device__ __forceinline__ void abc_block(const BndData &b, const Geo &g, int blk)
+// The product of s with c = -1, 0 or 1.
+__device__ __forceinline__ int32_t times_c(int32_t s, int32_t c) { return c == 0 ? 0 : (c < 0 ? -s : s); }
+
+// integer terms of a link in direction c to the solid cell at offset s from
+// its fiber's reference point (see abc_restore): a[0..5] = SA, then SB, SC
+__device__ __forceinline__ void link_sums(const int32_t c[3], const int32_t s[3], int32_t kap, int32_t (&sa)[6],
+                                          long long (&sb)[9], long long (&sc)[6])
 {
-    const int p = blk / b.bpf, j = blk % b.bpf;
-    const uint32_t cnt = b.seg_cnt[p], cap = b.seg_cap[p];
-    const uint32_t n = cnt < cap ? cnt : cap, off = b.seg_off[p];
-    long long acc[NABC];
+    const int32_t r[3] = {times_c(s[1], c[2]) - times_c(s[2], c[1]), times_c(s[2], c[0]) - times_c(s[0], c[2]),
+                          times_c(s[0], c[1]) - times_c(s[1], c[0])};
+    const int32_t kr[3] = {kap * r[0], kap * r[1], kap * r[2]};
+    const int32_t kc[3] = {kap * c[0], kap * c[1], kap * c[2]};
+    int k = 0, k2 = 0;
 #pragma unroll
-    for (int k = 0; k < NABC; ++k) acc[k] = 0;
-    int32_t hr[3];
-    fiber_ref(b.ps[p].X, hr);
-    for (uint32_t r = j * 256u + threadIdx.x; r < n; r += b.bpf * 256u) {
-        const uint32_t cell = b.cell[off + r], mask = b.mask[off + r];
-        const int32_t z = int32_t(cell / g.nxy), rem = int32_t(cell - uint32_t(z) * g.nxy);
-        const int32_t y = rem / int32_t(g.nx), x = rem - y * int32_t(g.nx);
-        int32_t own[Q];
-        fiber_links(b.pid, g, x, y, z, own);
-        static_for<1, Q>([&](auto qc) {
-            constexpr int q = decltype(qc)::value;
-            if ((mask >> q) & 1u) {
-                const int o = own[q];
-                int32_t rf[3] = {hr[0], hr[1], hr[2]};
-                if (o != p) fiber_ref(b.ps[o].X, rf);
-                const int32_t yx = wrapc(x + CX[q], int32_t(g.nx)), yy = wrapc(y + CY[q], int32_t(g.ny));
-                const int32_t yz = g.zper ? wrapc(z + CZ[q], int32_t(g.nz)) : z + CZ[q];
-                const int32_t sx = mi_i(yx - rf[0], int32_t(g.nx), true);
-                const int32_t sy = mi_i(yy - rf[1], int32_t(g.ny), true);
-                const int32_t sz = mi_i(yz - rf[2], int32_t(g.nz), g.zper != 0);
-                if (o == p) {
-                    link_int_terms<q>(acc, sx, sy, sz);
-                } else {
-                    // link to another fiber (fibers closer than the region margin)
-                    long long tmp[NABC];
+    for (int i = 0; i < 3; ++i)
 #pragma unroll
-                    for (int k = 0; k < NABC; ++k) tmp[k] = 0;
-                    link_int_terms<q>(tmp, sx, sy, sz);
+        for (int j = i; j < 3; ++j) sa[k++] += times_c(kc[i], c[j]);
+    k = 0;
 #pragma unroll
-                    for (int k = 0; k < NABC; ++k)
-                        if (tmp[k])
-                            atomicAdd(reinterpret_cast<unsigned long long *>(b.mea + size_t(o) * NACC + 6 + k),
-                                      (unsigned long long)tmp[k]);
-                }
-            }
-        });
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            sb[k++] += times_c(kr[j], c[i]);
+            if (j >= i) sc[k2++] += (long long)(kr[i]) * r[j];
+        }
+}
+
+// Sum over the wave of 32 values per lane: each step halves the values held
+// and pairs lanes 32, 16, 8, 4, 2 apart, the last adds the remaining pairs;
+// lane l ends with the total of value l >> 1.
+template <int H>
+__device__ __forceinline__ void halve(long long (&v)[32])
+{
+    const bool up = (threadIdx.x & (2 * H)) != 0;
+#pragma unroll
+    for (int k = 0; k < H; ++k) {
+        const long long send = up ? v[k] : v[k + H], keep = up ? v[k + H] : v[k];
+        v[k] = keep + __shfl_xor(send, 2 * H, 64);
     }
-    __shared__ long long red[4][NABC];
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-#pragma unroll
-    for (int k = 0; k < NABC; ++k) {
-        long long v = acc[k];
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-        if (lane == 0) red[wid][k] = v;
-    }
-    __syncthreads();
-    if (threadIdx.x < NABC) {
-        const int k = threadIdx.x;
-        const long long v = red[0][k] + red[1][k] + red[2][k] + red[3][k];
-        if (v) atomicAdd(reinterpret_cast<unsigned long long *>(b.mea + size_t(p) * NACC + 6 + k),
-                         (unsigned long long)v);
-    }
+}
+__device__ __forceinline__ long long wave_totals(long long (&v)[32])
+{
+    halve<16>(v);
+    halve<8>(v);
+    halve<4>(v);
+    halve<2>(v);
+    halve<1>(v);
+    return v[0] + __shfl_xor(v[0], 1, 64);
 }
 
 // Register budget: the bulk sweep keeps 2 waves of 80 VGPRs per SIMD
 // resident for its whole grid-stride run; this kernel runs beside it with
-// up to 2 waves per SIMD, so it must stay within 176 VGPRs (171 for FP32),
-// or bulk workgroups launched after it start late and the sweep stretches.
-// STAB: momentum stabilization (mean velocity stab[0..2]; the boundary-cell
-// workgroup blk writes its sums to part[4 blk .. 4 blk + 3]).  XYW: walls on
-// the x and/or y faces.
+// up to 2 waves per SIMD, so it must stay within 176 VGPRs, or bulk
+// workgroups launched after it start late and the sweep stretches.
+// Grid: np * bpf waves; wave (fiber p, part j) takes entries 64 j, 64 (j +
+// bpf), ... of the fiber's list segment.
+// STAB: momentum stabilization (mean velocity stab[0..2]; wave blk writes
+// its sums to part[4 blk .. 4 blk + 3]).  XYW: walls on the x and/or y
+// faces.
 template <typename S, bool ODD, bool STAB, bool XYW>
-__global__ __launch_bounds__(256) void k_boundary(S *__restrict__ f, Geo g, Phys<typename St<S>::R> ph,
-                                                  BndData b, const double *stab, double *part)
+__global__ __launch_bounds__(64, 2) void k_boundary(S *__restrict__ f, Geo g, Phys<typename St<S>::R> ph, BndData b,
+                                                    const double *stab, double *part)
 {
-    const int nb = b.np * b.bpf;   // block-uniform split
-    if (int(blockIdx.x) < nb) bnd_block<S, ODD, STAB, XYW>(f, g, ph, b, int(blockIdx.x), stab, part);
-    else abc_block(b, g, int(blockIdx.x) - nb);
+    using R = typename St<S>::R;
+    __shared__ uint32_t s_code[QCAP];
+    __shared__ R s_val[QCAP];
+    __shared__ uint32_t s_cell[64];
+    const int p = int(blockIdx.x) / b.bpf, j = int(blockIdx.x) % b.bpf;   // wave-uniform
+    const uint32_t lane = threadIdx.x;
+    const uint32_t cap = b.seg_cap[p], off = b.seg_off[p];
+    // the fiber's state (home links) and the reference point of its sums
+    double X[3], V[3], W[3];
+    for (int k = 0; k < 3; ++k) {
+        X[k] = uniform(b.ps[p].X[k]);
+        V[k] = uniform(b.ps[p].V[k]);
+        W[k] = uniform(b.ps[p].W[k]);
+    }
+    int32_t hr[3];
+    fiber_ref(X, hr);
+    const uint32_t n = min(b.seg_cnt[p], cap);
+    const double r0 = double(ph.rho0);
+    long long fm[6] = {0, 0, 0, 0, 0, 0}, sb[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0}, sc[6] = {0, 0, 0, 0, 0, 0};
+    int32_t sa[6] = {0, 0, 0, 0, 0, 0};
+    StabAcc<R> st;
+    double lj[3] = {0.0, 0.0, 0.0};   // momentum change of the links (stabilization)
+    if constexpr (STAB) stab_begin(st, stab);
+    for (uint32_t e0 = uint32_t(j) * 64u; e0 < n; e0 += uint32_t(b.bpf) * 64u) {
+        LinkQueue<R> queue{s_code, s_val, 0u, lane};
+        if (e0 + lane < n) {
+            const uint32_t cell = b.cell[off + e0 + lane], mask = b.mask[off + e0 + lane];
+            s_cell[lane] = cell;
+            if (!(mask & LIST_HOME)) queue.tag |= 1u << 17;
+            update_cell<S, ODD, true, STAB, XYW>(f, g, ph, cell, mask, queue, &st);
+        }
+        const uint32_t nl = __builtin_amdgcn_readfirstlane(queue.n);   // lane 0 has an entry
+        __syncthreads();
+        for (uint32_t l = lane; l < nl; l += 64u) {
+            const uint32_t code = s_code[l], q = (code >> 6) & 31u;
+            const R v = s_val[l];
+            const int32_t c[3] = {int32_t((code >> 11) & 3u) - 1, int32_t((code >> 13) & 3u) - 1,
+                                  int32_t((code >> 15) & 3u) - 1};
+            const double cd[3] = {double(c[0]), double(c[1]), double(c[2])};
+            const bool axis = (c[0] != 0) + (c[1] != 0) + (c[2] != 0) == 1;
+            const uint32_t cell = s_cell[code & 63u];
+            const uint32_t z = fdiv(cell, g.dnxy), rem = cell - z * g.nxy;
+            const uint32_t y = fdiv(rem, g.dnx), x = rem - y * g.nx;
+            const int32_t nx = int32_t(g.nx), ny = int32_t(g.ny), nz = int32_t(g.nz);
+            const int32_t yx = wrapc(int32_t(x) + c[0], nx), yy = wrapc(int32_t(y) + c[1], ny);
+            const int32_t yz = g.zper ? wrapc(int32_t(z) + c[2], nz) : int32_t(z) + c[2];
+            const uint32_t yc[3] = {uint32_t(yx), uint32_t(yy), uint32_t(yz)};
+            const uint32_t ycell = (yc[2] * g.ny + yc[1]) * g.nx + yc[0];
+            const int o = (code >> 17) & 1u ? b.pid[ycell] : p;
+            const double w = axis ? wq(1) : wq(4), w6r0 = (axis ? 6.0 * wq(1) : 6.0 * wq(4)) * r0;
+            const int32_t kap = axis ? 2 : 1;
+            double r[3];
+            R out;
+            if (!isfinite(double(v))) atomicOr(&b.ctr->err_unstable, 1u);
+            if (o == p) {
+                out = link_bounce<R>(v, w6r0, cd, yc, X, V, W, g, r);
+                link_terms(fm, double(v), w, cd, r, r0);
+                const int32_t s[3] = {mi_i(yx - hr[0], nx, true), mi_i(yy - hr[1], ny, true),
+                                      mi_i(yz - hr[2], nz, g.zper != 0)};
+                link_sums(c, s, kap, sa, sb, sc);
+            } else {
+                // link to another fiber (fibers closer than the region margin)
+                const PState &so = b.ps[o];
+                out = link_bounce<R>(v, w6r0, cd, yc, so.X, so.V, so.W, g, r);
+                long long tf[6] = {0, 0, 0, 0, 0, 0}, tb[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0}, tc[6] = {0, 0, 0, 0, 0, 0};
+                int32_t ta[6] = {0, 0, 0, 0, 0, 0}, rf[3];
+                link_terms(tf, double(v), w, cd, r, r0);
+                fiber_ref(so.X, rf);
+                const int32_t s[3] = {mi_i(yx - rf[0], nx, true), mi_i(yy - rf[1], ny, true),
+                                      mi_i(yz - rf[2], nz, g.zper != 0)};
+                link_sums(c, s, kap, ta, tb, tc);
+                unsigned long long *m = reinterpret_cast<unsigned long long *>(b.mea + size_t(o) * NACC);
+#pragma unroll
+                for (int k = 0; k < 9; ++k) {
+                    if (k < 6) {
+                        atomicAdd(m + k, (unsigned long long)tf[k]);
+                        if (ta[k]) atomicAdd(m + 6 + k, (unsigned long long)(long long)ta[k]);
+                        if (tc[k]) atomicAdd(m + 21 + k, (unsigned long long)tc[k]);
+                    }
+                    if (tb[k]) atomicAdd(m + 12 + k, (unsigned long long)tb[k]);
+                }
+            }
+            if constexpr (STAB) {
+                // the link returns out in direction -c instead of streaming v along c
+                const double m = double(v + out);
+                for (int k = 0; k < 3; ++k) lj[k] -= cd[k] * m;
+            }
+            // even sweep: the mailbox, slot q of the solid cell; odd: own slot opp(q)
+            const uint64_t slot = ODD ? uint64_t(q <= 9u ? q + 9u : q - 9u) * g.qstride + g.nxy + cell
+                                      : uint64_t(q) * g.qstride + g.nxy + ycell;
+            St<S>::st(f, slot, out, ph.scale);
+        }
+        __syncthreads();
+    }
+    // integer sums: exact, so the reduction order does not matter
+    long long v[32] = {fm[0], fm[1], fm[2], fm[3], fm[4], fm[5], sa[0], sa[1], sa[2], sa[3], sa[4], sa[5],
+                       sb[0], sb[1], sb[2], sb[3], sb[4], sb[5], sb[6], sb[7], sb[8],
+                       sc[0], sc[1], sc[2], sc[3], sc[4], sc[5], 0, 0, 0, 0, 0};
+    const long long tot = wave_totals(v);
+    if ((lane & 1u) == 0u && lane < 2u * NACC && tot)
+        atomicAdd(reinterpret_cast<unsigned long long *>(b.mea + size_t(p) * NACC + (lane >> 1)), (unsigned long long)tot);
+    if constexpr (STAB) {
+        double t[4] = {double(st.j[0]) + lj[0], double(st.j[1]) + lj[1], double(st.j[2]) + lj[2], double(st.n)};
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            for (int o = 32; o > 0; o >>= 1) t[k] += __shfl_xor(t[k], o, 64);
+        if (lane == 0)
+            for (int k = 0; k < 4; ++k) part[4 * size_t(blockIdx.x) + k] = t[k];
+    }
 }
 
 template <typename S>
@@ -142,7 +230,7 @@ static hipError_t boundary_t(bool odd, void *f, const Geo &g, const Phys<double>
 {
     using R = typename St<S>::R;
     const Phys<R> p = cast_phys<R>(ph);
-    const dim3 grid(uint32_t(2 * b.np * b.bpf)), bl(256);
+    const dim3 grid(uint32_t(b.np * b.bpf)), bl(64);
     const int mode = (odd ? 1 : 0) | (stab ? 2 : 0) | ((g.xw || g.yw || g.zs) ? 4 : 0);
     switch (mode) {
     case 0: hipLaunchKernelGGL((k_boundary<S, false, false, false>), grid, bl, 0, st, (S *)f, g, p, b, stab, part); break;

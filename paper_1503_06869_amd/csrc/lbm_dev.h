@@ -179,14 +179,18 @@ struct Phys {
     R scale, inv_scale;        // storage scaling of the deviation
 };
 
+// bit of a list entry's mask: all its fiber neighbours belong to the fiber
+// of the list segment (where it is clear, owners are looked up)
+constexpr uint32_t LIST_HOME = 0x80000000u;
+
 struct BndData {               // boundary-cell list and particle access for the sweep
     const uint32_t *cell;
-    const uint32_t *mask;      // bit q (1..18) set: neighbour x + c_q is a fiber cell
+    const uint32_t *mask;      // bit q (1..18) set: neighbour x + c_q is a fiber cell; LIST_HOME
     const uint32_t *seg_off;   // [np] start of each fiber's list segment
     const uint32_t *seg_cnt;   // [np] entries in each segment
     const uint32_t *seg_cap;   // [np] capacity of each segment
     int32_t np;
-    int32_t bpf;               // blocks per fiber segment
+    int32_t bpf;               // waves per fiber segment
     const int32_t *pid;
     const PState *ps;          // state at the time level of the sweep
     long long *mea;            // [np][NACC] fixed-point momentum-exchange sums

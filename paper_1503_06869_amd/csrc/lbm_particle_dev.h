@@ -498,20 +498,25 @@ __device__ __forceinline__ void remap_boxes(const PState &s, const PConst &c, co
     remap_boxes(s, c, old, Box{{0, 0, 0}, {0, 0, 0}}, g, ub, nb);
 }
 
-// neighbour mask of cell (x, y, z): bit q set when x + c_q is a fiber cell
-__device__ __forceinline__ uint32_t fiber_mask(const int32_t *pid, const Geo &g, int32_t x, int32_t y, int32_t z)
+// neighbour mask of cell (x, y, z): bit q set when x + c_q is a fiber cell,
+// and LIST_HOME when every such cell belongs to fiber `home`
+__device__ __forceinline__ uint32_t fiber_mask(const int32_t *pid, const Geo &g, int32_t x, int32_t y, int32_t z,
+                                               int32_t home)
 {
     const int32_t nx = g.nx, ny = g.ny, nz = g.nz;
     uint32_t mask = 0;
+    bool all = true;
 #pragma unroll
     for (int q = 1; q < Q; ++q) {
         int32_t zz = z + CZ[q];
         if (g.zper) zz = wrapc(zz, nz);
         else if (zz < 0 || zz >= nz) continue;
         const int32_t xx = wrapc(x + CX[q], nx), yy = wrapc(y + CY[q], ny);
-        if (pid[(uint32_t(zz) * g.ny + uint32_t(yy)) * g.nx + uint32_t(xx)] >= 0) mask |= 1u << q;
+        const int32_t o = pid[(uint32_t(zz) * g.ny + uint32_t(yy)) * g.nx + uint32_t(xx)];
+        if (o >= 0) mask |= 1u << q;
+        all &= o < 0 || o == home;
     }
-    return mask;
+    return mask && all ? mask | LIST_HOME : mask;
 }
 
 // ------------------------------------------------------------------ population-free link sums
@@ -625,25 +630,6 @@ __device__ __forceinline__ void abc_restore(double *acc, const double X[3], doub
     }
     for (int i = 0; i < 3; ++i)
         for (int j = 0; j < 3; ++j) acc[12 + 3 * i + j] = B[i][j];
-}
-
-// fiber_mask with the owner of each linked cell: own[q] for the set bits
-__device__ __forceinline__ uint32_t fiber_links(const int32_t *pid, const Geo &g, int32_t x, int32_t y, int32_t z,
-                                                int32_t (&own)[Q])
-{
-    const int32_t nx = g.nx, ny = g.ny, nz = g.nz;
-    uint32_t mask = 0;
-#pragma unroll
-    for (int q = 1; q < Q; ++q) {
-        own[q] = -1;
-        int32_t zz = z + CZ[q];
-        if (g.zper) zz = wrapc(zz, nz);
-        else if (zz < 0 || zz >= nz) continue;
-        const int32_t xx = wrapc(x + CX[q], nx), yy = wrapc(y + CY[q], ny);
-        own[q] = pid[(uint32_t(zz) * g.ny + uint32_t(yy)) * g.nx + uint32_t(xx)];
-        if (own[q] >= 0) mask |= 1u << q;
-    }
-    return mask;
 }
 
 template <typename S>

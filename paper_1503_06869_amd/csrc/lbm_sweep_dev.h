@@ -59,6 +59,21 @@ struct St<bf16s> {
     }
 };
 
+// A value that every lane loads from the same address: keep it in scalar
+// registers (the compiler cannot prove that memory written by the kernel is
+// uniform when read back).
+template <typename T>
+__device__ __forceinline__ T uniform(const T &v)
+{
+    static_assert(sizeof(T) % 4 == 0, "32-bit words");
+    T r;
+    const int *s = reinterpret_cast<const int *>(&v);
+    int *d = reinterpret_cast<int *>(&r);
+#pragma unroll
+    for (int k = 0; k < int(sizeof(T) / 4); ++k) d[k] = __builtin_amdgcn_readfirstlane(s[k]);
+    return r;
+}
+
 // Each XCD receives every 8th block; renumber so that each XCD works on a
 // contiguous range of cells (neighbouring blocks share partial cache lines).
 __device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t nb)
@@ -263,21 +278,28 @@ __device__ __forceinline__ long long fx(double v, int k) { return __double2ll_rn
 // This adds the link's F0, M0 terms to acc[0 .. 5]; A, B, C do not depend
 // on the populations and are summed as integers when the list is built
 // (link_int_terms).
-template <int q>
-__device__ __forceinline__ void link_terms(long long *acc, double ft, double rx, double ry, double rz,
-                                           double r0)
+__device__ __forceinline__ void link_terms(long long *acc, double ft, double w, const double c[3],
+                                           const double r[3], double r0)
 {
-    const double m2 = 2.0 * (ft + wq(q) * r0);
-    const double c0 = CX[q], c1 = CY[q], c2 = CZ[q];
-    const double rc0 = ry * c2 - rz * c1, rc1 = rz * c0 - rx * c2, rc2 = rx * c1 - ry * c0;
-    const double t[6] = {m2 * c0, m2 * c1, m2 * c2, m2 * rc0, m2 * rc1, m2 * rc2};
+    const double m2 = 2.0 * (ft + w * r0);
+    const double rc0 = r[1] * c[2] - r[2] * c[1], rc1 = r[2] * c[0] - r[0] * c[2], rc2 = r[0] * c[1] - r[1] * c[0];
+    const double t[6] = {m2 * c[0], m2 * c[1], m2 * c[2], m2 * rc0, m2 * rc1, m2 * rc2};
 #pragma unroll
     for (int k = 0; k < 6; ++k) acc[k] += fx(t[k], k);
 }
 
-// BND: a boundary cell of the list, whose fiber links add their F0, M0
-// terms to acc[0 .. 5] (links to fiber `home`) or directly to the sums of
-// another fiber.  NK: length of acc (6).
+// sink of the cells without fiber links
+struct NoLinks {
+    template <int q, typename R>
+    __device__ __forceinline__ void link(bool, R, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t)
+    {
+    }
+};
+
+// BND: a boundary cell of the list; each of its fiber links (bits of mask) is
+// handed to sink.link<q>(is_link, post-collision value, ...), called by every
+// lane for every q, which does the bounce-back store and the momentum
+// exchange.
 // STAB: momentum stabilization with the accumulator sa (see StabAcc).
 // XYW: walls on the x and/or y faces (g.xw, g.yw) or free-slip z walls
 // (g.zs).  A link leaving the lattice through a resting no-slip x or y wall
@@ -294,11 +316,10 @@ __device__ __forceinline__ void link_terms(long long *acc, double ft, double rx,
 // refl(q) of x + t, which no other cell touches in that sweep (the slot it
 // gathered from for the reverse link), so both sweeps stay in place.  A
 // link that crosses walls of both kinds bounces back.
-template <typename S, bool ODD, bool BND, int NK = NACC, bool STAB = false, bool XYW = false>
+template <typename S, bool ODD, bool BND, bool STAB, bool XYW, typename Sink>
 __device__ __forceinline__ void update_cell(S *__restrict__ f, const Geo &g,
                                             const Phys<typename St<S>::R> &ph, uint32_t cell,
-                                            uint32_t mask, int home, long long *acc, const BndData &b,
-                                            StabAcc<typename St<S>::R> *sa = nullptr)
+                                            uint32_t mask, Sink &sink, StabAcc<typename St<S>::R> *sa = nullptr)
 {
     using R = typename St<S>::R;
     const uint32_t z = fdiv(cell, g.dnxy);
@@ -362,8 +383,6 @@ __device__ __forceinline__ void update_cell(S *__restrict__ f, const Geo &g,
     collide<R, STAB>(fv, ph, R(1) / ph.rho0, sa);
 
     const R six_r0 = R(6) * ph.rho0;
-    const PState *ps = nullptr;
-    if (BND) ps = b.ps;
     static_for<0, Q>([&](auto qc) {
         constexpr int q = decltype(qc)::value;
         const uint32_t nb = zo[1 + CZ[q]] + yo[1 + CY[q]] + xo[1 + CX[q]];
@@ -378,45 +397,17 @@ __device__ __forceinline__ void update_cell(S *__restrict__ f, const Geo &g,
             to_slip = !to_wall && !to_side && (ox || oy || oz);
             slip_m = (ox ? 1 : 0) | (oy ? 2 : 0) | (oz ? 4 : 0);
         }
-        bool to_part = false;
-        if (BND) to_part = ((mask >> q) & 1u) && !to_slip;
+        if constexpr (BND && q > 0) {
+            const bool lk = ((mask >> q) & 1u) && !to_slip && !to_side;
+            sink.template link<q>(lk, fv[q], own, nb, x, y, z);
+            if (lk) return;
+        }
         R out = fv[q];
         if (CX[q] != 0 && to_wall) {
             const R uw = CZ[q] < 0 ? -ph.wall_u : ph.wall_u;
             out -= six_r0 * R(wq(q)) * R(CX[q]) * uw;
         }
-        if (BND && to_part && !to_side) {   // (to_part excludes reflected links)
-            // moving-obstacle bounce-back (Eq. LBMMovWall) and the link's
-            // momentum exchange, from the post-collision value in registers
-            const int32_t p = b.pid[nb - g.nxy];
-            const uint32_t yx = xo[1 + CX[q]], yy = (y + g.ny + CY[q]) % g.ny;
-            const int32_t yzi = int32_t(z) + CZ[q];
-            const uint32_t yz = g.zper ? uint32_t((yzi + int32_t(g.nz)) % int32_t(g.nz)) : uint32_t(yzi);
-            const PState &sp = ps[p];
-            const double rx = mi(double(yx) - sp.X[0], g.nx, true);
-            const double ry = mi(double(yy) - sp.X[1], g.ny, true);
-            const double rz = mi(double(yz) - sp.X[2], g.nz, g.zper != 0);
-            const double us0 = sp.V[0] + (sp.W[1] * rz - sp.W[2] * ry);
-            const double us1 = sp.V[1] + (sp.W[2] * rx - sp.W[0] * rz);
-            const double us2 = sp.V[2] + (sp.W[0] * ry - sp.W[1] * rx);
-            const double cu = double(CX[q]) * us0 + double(CY[q]) * us1 + double(CZ[q]) * us2;
-            out -= R(6.0 * wq(q) * double(ph.rho0) * cu);
-            if (!isfinite(double(fv[q]))) atomicOr(&b.ctr->err_unstable, 1u);
-            if (p == home) {
-                link_terms<q>(acc, double(fv[q]), rx, ry, rz, double(ph.rho0));
-            } else {
-                // link to another fiber (fibers closer than the region margin)
-                long long tmp[6];
-#pragma unroll
-                for (int k = 0; k < 6; ++k) tmp[k] = 0;
-                link_terms<q>(tmp, double(fv[q]), rx, ry, rz, double(ph.rho0));
-#pragma unroll
-                for (int k = 0; k < 6; ++k)
-                    atomicAdd(reinterpret_cast<unsigned long long *>(b.mea + size_t(p) * NACC + k),
-                              (unsigned long long)tmp[k]);
-            }
-        }
-        const bool bounce = to_wall || to_side || to_part;
+        const bool bounce = to_wall || to_side;
         if constexpr (STAB) {
             // a bounced link returns out in direction -c_q instead of
             // streaming fv[q] along c_q; a reflected one reverses the
@@ -434,9 +425,9 @@ __device__ __forceinline__ void update_cell(S *__restrict__ f, const Geo &g,
             }
         }
         if (!ODD) {
-            // mailbox for z walls and fibers; normal streaming, side walls
-            // and reflections: own slot
-            if (to_wall || (to_part && !to_side)) St<S>::st(f, uint64_t(q) * qs + nb, out, sc);
+            // mailbox for z walls; normal streaming, side walls and
+            // reflections: own slot
+            if (to_wall) St<S>::st(f, uint64_t(q) * qs + nb, out, sc);
             else St<S>::st(f, uint64_t(opp(q)) * qs + own, out, sc);
         } else {
             if (to_slip) {
@@ -451,9 +442,25 @@ __device__ __forceinline__ void update_cell(S *__restrict__ f, const Geo &g,
         }
     });
     (void)six_r0;
-    (void)home;
-    (void)acc;
+    (void)sink;
 }
 
+// The moving-obstacle bounce-back (Eq. LBMMovWall) of one fiber link from
+// cell (x, y, z) in direction c to the solid cell y = x + c of the fiber in
+// state X, V, W: the returned value of the post-collision value v; the lever
+// arm y - X in r.
+template <typename R>
+__device__ __forceinline__ R link_bounce(R v, double w6r0, const double c[3], const uint32_t yc[3], const double *X,
+                                         const double *V, const double *W, const Geo &g, double r[3])
+{
+    r[0] = mi(double(yc[0]) - X[0], g.nx, true);
+    r[1] = mi(double(yc[1]) - X[1], g.ny, true);
+    r[2] = mi(double(yc[2]) - X[2], g.nz, g.zper != 0);
+    const double us0 = V[0] + (W[1] * r[2] - W[2] * r[1]);
+    const double us1 = V[1] + (W[2] * r[0] - W[0] * r[2]);
+    const double us2 = V[2] + (W[0] * r[1] - W[1] * r[0]);
+    const double cu = c[0] * us0 + c[1] * us1 + c[2] * us2;
+    return v - R(w6r0 * cu);
+}
 
 }  // namespace lbm

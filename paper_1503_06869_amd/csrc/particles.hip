@@ -358,7 +358,7 @@ __global__ __launch_bounds__(256) void k_near(uint8_t *__restrict__ flags, const
             const uint32_t cell = (uint32_t(z) * g.ny + uint32_t(y)) * g.nx + uint32_t(x);
             // the cell's owner and its neighbours' in one round of loads
             const int32_t own = pid[cell];
-            const uint32_t mask = fiber_mask(pid, g, x, y, z);
+            const uint32_t mask = fiber_mask(pid, g, x, y, z, p);
             const bool near = (own < 0) & (mask != 0u);
             if (!near) {
                 flags[cell] = own >= 0 ? F_SOLID : uint8_t(0);

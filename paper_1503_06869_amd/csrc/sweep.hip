@@ -35,12 +35,13 @@ __global__ __launch_bounds__(256) void k_sweep_bulk(S *__restrict__ f, const uin
 {
     using R = typename St<S>::R;
     StabAcc<R> sa;
+    NoLinks none;
     if constexpr (STAB) stab_begin(sa, stab);
     const uint32_t nchunk = (g.ncell + 255u) >> 8;
     for (uint32_t ch = xcd_block(blockIdx.x, gridDim.x); ch < nchunk; ch += gridDim.x) {
         const uint32_t cell = (ch << 8) + threadIdx.x;
         if (cell < g.ncell && !flags[cell])   // fiber cells idle; boundary cells: k_boundary
-            update_cell<S, ODD, false, NACC, STAB, XYW>(f, g, ph, cell, 0u, -1, nullptr, BndData{}, &sa);
+            update_cell<S, ODD, false, STAB, XYW>(f, g, ph, cell, 0u, none, &sa);
     }
     if constexpr (STAB) stab_flush(sa, part + 4 * size_t(blockIdx.x));
 }
