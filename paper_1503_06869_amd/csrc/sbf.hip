@@ -64,186 +64,249 @@ __host__ __device__ __forceinline__ size_t tile_base(int i, int j, int nt)
 __host__ __device__ __forceinline__ size_t packed_tiles(int nt) { return size_t(nt) * size_t(nt + 1) / 2; }
 
 // ------------------------------------------------------------------ moments
-// 1/sqrt(x) for x > 0: the hardware estimate refined by two Newton steps
-// y <- y + y (1 - x y^2)/2 (each at least doubles the correct bits).
+// 1/sqrt(x) for x > 0: the hardware estimate y (relative error e/2 below
+// 2^-22) refined by the third-order step y (1 + e/2 + 3 e^2/8), e = 1 - x y^2,
+// whose error is of the order of e^3.
 __device__ __forceinline__ double rsqrt_nr(double x)
 {
-    double y = __builtin_amdgcn_rsq(x);
-    double e = fma(-x * y, y, 1.0);
-    y = fma(0.5 * y, e, y);
-    e = fma(-x * y, y, 1.0);
-    return fma(0.5 * y, e, y);
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
-// entry (R, C), R < C, of the symmetric matrix into the packed upper
-// triangle (a diagonal tile is stored whole: its mirror entry too)
-__device__ __forceinline__ void put_sym(double *W, int nt, int R, int C, double v)
-{
-    const int bi = R / TS, bj = C / TS, ri = R % TS, ci = C % TS;
-    double *t = W + tile_base(bi, bj, nt);
-    t[ri * TS + ci] = v;
-    if (bi == bj) t[ci * TS + ri] = v;
-}
-
-// Sums over the inner points s'_j for the outer point s_i of the pair:
-// acc[k] = sum_j w_j P_k(s_j) (alpha, beta R R^T entries) of G(R_ij).
+// Moments: workgroup b takes the pairs b PB .. b PB + PB - 1 of the list of
+// pairs m < m' (row by row; the pair gives both blocks of W, the diagonal
+// blocks stay at the zero the packed matrix was cleared to).
+//
+// With R = D + s p_m - s' p_m', D = x_m - x_m', the tensor part of
+// G = alpha I + beta R R^T is a polynomial in s and s' with scalar weights
+// beta, and s P_n is a combination of P_{n+1} and P_{n-1}.  So the block of a
+// pair follows from the scalar moments of alpha with P_n P_k, n, k <= N, and
+// of beta with n, k <= N + 2; the six tensor components need no sums of
+// their own.  Thread t serves pair slot t / Q and the outer point s_i, i =
+// t % Q, sums over s'_j into N + 1 and N + 3 accumulators (moment_point: 16
+// FP64 instructions for the Green's function and 2 N + 4 multiply-adds,
+// instead of 7 (N + 1)), the outer sums with P_n(s_i) follow from LDS, and one
+// thread per (pair, n, k) then forms the 3 x 3 block.  The split into
+// powers of s cancels where fibers are closer than their length, by a
+// factor of about (L/R)^2 on a sum exact to 1e-16.
+//
+// Bound: FP64 ALU.  1024 fibers, N = 5, Q = 48: 4.27 ms with a sum per tensor
+// component, 2.06 ms with scalar moments.
+// Tables: wl[k][j] = w_j P_k(s_j), k <= N + 2, and the same by points, wj[j] =
+// (s_j, w_j P_0(s_j), ...): an inner point's row is one scalar load.  Three
+// points are taken at a time (Q is a multiple of three), so that their
+// scalar loads are waited for once.
 template <int NP1>
-__device__ __forceinline__ void moment_point(int i, const double (&xm)[3], const double (&pm)[3],
-                                             const double (&xn)[3], const double (&pn)[3], double h,
-                                             const Consts &c, const double *__restrict__ sq,
-                                             const double *__restrict__ wl, double (&acc)[NP1][7])
+__device__ __forceinline__ void moment_term(const double (&b)[3], const double (&pn)[3], double h, const double *w,
+                                            double (&acc)[2 * NP1 + 2])
 {
+    const double R0 = b[0] - w[0] * pn[0], R1 = b[1] - w[0] * pn[1], R2 = b[2] - w[0] * pn[2];
+    const double r2 = R0 * R0 + R1 * R1 + R2 * R2;
+    const double inv = rsqrt_nr(r2);
+    const double inv2 = inv * inv, inv3 = inv * inv2;
+    const double alpha = fma(h, inv3, inv);
+    const double beta = inv3 * fma(-3.0 * h, inv2, 1.0);
 #pragma unroll
-    for (int k = 0; k < NP1; ++k)
-#pragma unroll
-        for (int e = 0; e < 7; ++e) acc[k][e] = 0.0;
-    const double si = sq[i];
-    const double b0 = xm[0] + si * pm[0] - xn[0], b1 = xm[1] + si * pm[1] - xn[1], b2 = xm[2] + si * pm[2] - xn[2];
-    for (int j = 0; j < c.Q; ++j) {
-        const double sj = sq[j];
-        const double R0 = b0 - sj * pn[0], R1 = b1 - sj * pn[1], R2 = b2 - sj * pn[2];
-        const double r2 = R0 * R0 + R1 * R1 + R2 * R2;
-        const double inv = rsqrt_nr(r2);
-        const double inv2 = inv * inv, inv3 = inv * inv2;
-        const double alpha = inv + h * inv3;
-        const double beta = inv3 - 3.0 * h * inv3 * inv2;
-        const double g[7] = {alpha, beta * R0 * R0, beta * R0 * R1, beta * R0 * R2,
-                             beta * R1 * R1, beta * R1 * R2, beta * R2 * R2};
-#pragma unroll
-        for (int k = 0; k < NP1; ++k) {
-            const double wk = wl[k * c.Q + j];
-#pragma unroll
-            for (int e = 0; e < 7; ++e) acc[k][e] += wk * g[e];
-        }
+    for (int k = 0; k < NP1 + 2; ++k) {
+        if (k < NP1) acc[k] = fma(w[1 + k], alpha, acc[k]);
+        acc[NP1 + k] = fma(w[1 + k], beta, acc[NP1 + k]);
     }
 }
-
-// Moments for Q <= 64: workgroup b takes the pairs b PB .. b PB + PB - 1
-// of the list of pairs m < m' (row by row; the pair gives both blocks of W,
-// the diagonal blocks stay at the zero the packed matrix was cleared to).
-// Thread t serves pair slot t / Q and its outer quadrature point
-// s_i, i = t % Q: it sums over the inner points s'_j, per trial mode k, the
-// scalar part alpha and the six components of beta R R^T of
-// G = alpha I + beta R R^T (moment_point); the outer sums with P_n(s_i)
-// follow one trial mode k at a time through LDS ([Q][7] per pair, then
-// out[NP1][NP1][7] per pair).  wl[k][j] = w_j P_k(s_j).
-__device__ __forceinline__ void pair_of(long long p, int M, int &m, int &mp)
+// sums of the inner points j0, j0 + dj, ... for the outer point s_i
+template <int NP1>
+__device__ __forceinline__ void moment_point(double si, const double (&xm)[3], const double (&pm)[3],
+                                             const double (&xn)[3], const double (&pn)[3], double h, int Q,
+                                             const double *wj, int j0, int dj, double (&acc)[2 * NP1 + 2])
 {
-    // start(m) = m (2M - m - 1)/2 pairs precede row m
-    const double b = 2.0 * M - 1.0;
-    long long r = (long long)((b - sqrt(b * b - 8.0 * double(p))) * 0.5);
-    r = r < 0 ? 0 : (r > M - 2 ? M - 2 : r);
-    while (r > 0 && r * (2LL * M - r - 1) / 2 > p) --r;
-    while (r + 1 <= M - 2 && (r + 1) * (2LL * M - r - 2) / 2 <= p) ++r;
-    m = int(r);
-    mp = int(r + 1 + (p - r * (2LL * M - r - 1) / 2));
+#pragma unroll
+    for (int k = 0; k < 2 * NP1 + 2; ++k) acc[k] = 0.0;
+    const double b[3] = {xm[0] + si * pm[0] - xn[0], xm[1] + si * pm[1] - xn[1], xm[2] + si * pm[2] - xn[2]};
+    for (int j = j0; j < Q; j += dj) moment_term<NP1>(b, pn, h, wj + j * (NP1 + 3), acc);
 }
 
-// symmetric 3x3 index of (a, b) into the six beta components
-__device__ __forceinline__ int sym_index(int a, int b) { return a == b ? (a == 0 ? 1 : (a == 1 ? 4 : 6)) : (a + b == 1 ? 2 : (a + b == 2 ? 3 : 5)); }
+// pair p of the list m < m', start(m) = m (2M - m - 1)/2 pairs precede row m
+// (fewer than 2^30 pairs: sbf_create bounds the order of W)
+__device__ __forceinline__ void pair_of(int p, int M, int &m, int &mp)
+{
+    const double b = 2.0 * M - 1.0;
+    int r = int((float(b) - sqrtf(float(b * b - 8.0 * double(p)))) * 0.5f);   // off by one at most, then exact
+    r = min(max(r, 0), M - 2);
+    while (r > 0 && r * (2 * M - r - 1) / 2 > p) --r;
+    while (r + 1 <= M - 2 && (r + 1) * (2 * M - r - 2) / 2 <= p) ++r;
+    m = r;
+    mp = r + 1 + (p - r * (2 * M - r - 1) / 2);
+}
+
+// index of (a, b) among the six components xx xy xz yy yz zz
+__device__ __forceinline__ int sym_index(int a, int b) { return a == b ? (a == 0 ? 0 : (a == 1 ? 3 : 5)) : (a + b == 1 ? 1 : (a + b == 2 ? 2 : 4)); }
+
+// The 3 x 3 block (n, k) of a pair as its components xx xy xz yy yz zz in o[6],
+// from the moments A of alpha [NP1][NP1] and B of beta [NP1 + 2][NP1 + 2], d =
+// (D, p_m, p_m') and s P_n = up[n] P_{n+1} + dn[n] P_{n-1}.
+template <int NP1>
+__device__ __forceinline__ void pair_block(int n, int k, const double *A, const double *B, const double *d,
+                                           const double *up, const double *dn, double *o)
+{
+    constexpr int NB = NP1 + 2;
+    const int n1 = max(n - 1, 0), k1 = max(k - 1, 0), n2 = max(n - 2, 0), k2 = max(k - 2, 0);
+    const double un = up[n], dnn = dn[n], uk = up[k], dk = dn[k];
+    const double b00 = B[n * NB + k];
+    const double b10 = un * B[(n + 1) * NB + k] + dnn * B[n1 * NB + k];
+    const double b01 = uk * B[n * NB + k + 1] + dk * B[n * NB + k1];
+    const double b20 = un * (up[n + 1] * B[(n + 2) * NB + k] + dn[n + 1] * b00) +
+                       dnn * (up[n1] * b00 + dn[n1] * B[n2 * NB + k]);
+    const double b02 = uk * (up[k + 1] * B[n * NB + k + 2] + dn[k + 1] * b00) +
+                       dk * (up[k1] * b00 + dn[k1] * B[n * NB + k2]);
+    const double b11 = un * (uk * B[(n + 1) * NB + k + 1] + dk * B[(n + 1) * NB + k1]) +
+                       dnn * (uk * B[n1 * NB + k + 1] + dk * B[n1 * NB + k1]);
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int b = a; b < 3; ++b) {
+            double v = b00 * (d[a] * d[b]) + b10 * (d[a] * d[3 + b] + d[3 + a] * d[b]) -
+                       b01 * (d[a] * d[6 + b] + d[6 + a] * d[b]) + b20 * (d[3 + a] * d[3 + b]) -
+                       b11 * (d[3 + a] * d[6 + b] + d[6 + a] * d[3 + b]) + b02 * (d[6 + a] * d[6 + b]);
+            if (a == b) v += A[n * NP1 + k];
+            o[sym_index(a, b)] = v;
+        }
+}
+
+// LDS of k_theta in doubles per pair slot: the point sums [Q][theta_cols] (later
+// the blocks' six components), the moments of alpha and beta, and D, p_m, p_m'
+__host__ __device__ constexpr int theta_cols(int np1) { return (2 * np1 + 2) | 1; }   // odd: spreads the banks
+__host__ __device__ constexpr int theta_points(int np1, int q)
+{
+    return q * theta_cols(np1) > 6 * np1 * np1 ? q * theta_cols(np1) : 6 * np1 * np1;
+}
+__host__ __device__ constexpr int theta_lds(int np1, int q)
+{
+    return theta_points(np1, q) + np1 * np1 + (np1 + 2) * (np1 + 2) + 9;
+}
 
 template <int NP1>
 __global__ __launch_bounds__(256) void k_theta(const double *__restrict__ X, const double *__restrict__ p, Consts c,
-                                               const double *__restrict__ sq, const double *__restrict__ wl,
-                                               double *__restrict__ W, int PB, long long P)
+                                               const double *__restrict__ wj, const double *__restrict__ wl,
+                                               double *__restrict__ W, int PB, int P)
 {
-    // LDS: wl [NP1][Q]; the pairs' (m, m') [PB][2]; per pair [Q][7] then out[NP1][NP1][7]
+    constexpr int NB = NP1 + 2, NC = NP1 + NB, NCP = theta_cols(NP1), st = 3 * NP1;
     extern __shared__ double sh[];
-    const int st = 3 * NP1, per = c.Q * 7 + NP1 * NP1 * 7;
-    double *swl = sh;
-    int *pairs = reinterpret_cast<int *>(sh + NP1 * c.Q);
-    double *pd = sh + NP1 * c.Q + (PB + 1) / 2 * 2;
-    const int t = int(threadIdx.x), slot = t / c.Q, i = t % c.Q;
-    const long long p0 = (long long)blockIdx.x * PB;
-    const bool act = slot < PB && p0 + slot < P;
-    for (int e = t; e < NP1 * c.Q; e += int(blockDim.x)) swl[e] = wl[e];
-    int m = 0, mp = 0;
-    if (act) {
-        pair_of(p0 + slot, c.M, m, mp);
-        if (i == 0) {
-            pairs[2 * slot] = m;
-            pairs[2 * slot + 1] = mp;
-        }
+    __shared__ double up[NB], dn[NB];   // s P_n = up P_{n+1} + dn P_{n-1}
+    // where a pair's block lies in W: first element of the tile holding its
+    // first row and column, steps to the next tile right and down
+    struct Place {
+        size_t at, right, down;
+        int r0, c0, diag;
+    };
+    __shared__ Place place[85];               // PB Q <= 256, Q >= 3
+    __shared__ uint32_t entry[st * st];       // row, column and component of each entry of a block
+    const int per = theta_lds(NP1, c.Q), pts = theta_points(NP1, c.Q);
+    const int t = int(threadIdx.x), nt = int(blockDim.x), slot = t / c.Q, i = t % c.Q;
+    // neighbouring workgroups write neighbouring columns of W: keep them on one XCD
+    const uint32_t nb8 = gridDim.x >> 3, rem = gridDim.x & 7u, xcd = blockIdx.x & 7u;
+    const int p0 = int(xcd * nb8 + (xcd < rem ? xcd : rem) + (blockIdx.x >> 3)) * PB;
+    if (t < NB) {
+        up[t] = c.l * (t + 1) / (2 * t + 1);
+        dn[t] = c.l * t / (2 * t + 1);
     }
-    double acc[NP1][7];
-    if (act) {
+    for (int e = t; e < st * st; e += nt) {
+        const int row = e / st, col = e - row * st, n = row / 3, k = col / 3;
+        entry[e] = uint32_t(row) | uint32_t(col) << 8 | uint32_t((n * NP1 + k) * 6 + sym_index(row - 3 * n, col - 3 * k)) << 16;
+    }
+    if (slot < PB && p0 + slot < P) {
+        int m, mp;
+        pair_of(p0 + slot, c.M, m, mp);
         const double xm[3] = {X[3 * m], X[3 * m + 1], X[3 * m + 2]};
         const double pm[3] = {p[3 * m], p[3 * m + 1], p[3 * m + 2]};
         const double xn[3] = {X[3 * mp], X[3 * mp + 1], X[3 * mp + 2]};
         const double pn[3] = {p[3 * mp], p[3 * mp + 1], p[3 * mp + 2]};
-        moment_point<NP1>(i, xm, pm, xn, pn, 0.5 * c.r * c.r, c, sq, wl, acc);
-    }
-#pragma unroll
-    for (int k = 0; k < NP1; ++k) {
-        if (act)
-#pragma unroll
-            for (int e = 0; e < 7; ++e) pd[size_t(slot) * per + i * 7 + e] = acc[k][e];
-        __syncthreads();
-        for (int e = t; e < PB * NP1 * 7; e += int(blockDim.x)) {
-            const int s2 = e / (NP1 * 7), r = e % (NP1 * 7), n = r / 7, cc = r % 7;
-            if (p0 + s2 >= P) continue;
-            const double *b = pd + size_t(s2) * per;
-            const double *w = swl + n * c.Q;
-            double sum = 0.0;
-            for (int q = 0; q < c.Q; ++q) sum += w[q] * b[q * 7 + cc];
-            pd[size_t(s2) * per + c.Q * 7 + (n * NP1 + k) * 7 + cc] = sum;
+        if (i == 0) {
+            // (m st, mp st), m < mp: on or above the diagonal tile
+            const int bi = m * st / TS, bj = mp * st / TS;
+            Place q;
+            q.at = tile_base(bi, bj, c.nt);
+            q.right = TS * TS;
+            q.down = tile_base(bi + 1, max(bj, bi + 1), c.nt) - tile_base(bi, max(bj, bi + 1), c.nt);
+            q.r0 = m * st % TS;
+            q.c0 = mp * st % TS;
+            q.diag = bj - bi;
+            place[slot] = q;
+            double *d = sh + size_t(slot) * per + per - 9;
+            for (int a = 0; a < 3; ++a) {
+                d[a] = xm[a] - xn[a];
+                d[3 + a] = pm[a];
+                d[6 + a] = pn[a];
+            }
         }
-        __syncthreads();
-    }
-    for (int e = t; e < PB * st * st; e += int(blockDim.x)) {
-        const int s3 = e / (st * st), r = e % (st * st);
-        if (p0 + s3 >= P) continue;
-        const int m3 = pairs[2 * s3], mp3 = pairs[2 * s3 + 1];
-        const int row = r / st, col = r % st;
-        const int n = row / 3, a = row % 3, k = col / 3, b = col % 3;
-        const double *o = pd + size_t(s3) * per + c.Q * 7 + (n * NP1 + k) * 7;
-        const double v = o[sym_index(a, b)] + (a == b ? o[0] : 0.0);
-        // Theta^{n,k}_{m,mp} at (m st + row, mp st + col); its transpose,
-        // Theta^{k,n}_{mp,m}, is the mirror entry of the symmetric matrix
-        put_sym(W, c.nt, m3 * st + row, mp3 * st + col, v);
-    }
-}
-
-// Moments for Q > 64: one 64-thread block per ordered pair (m, mp), blocks
-// with m >= mp return at once; each thread takes outer points i, i + 64, ...
-// and keeps their sums in LDS ([Q][NP1][7], then out[NP1][NP1][7]).
-template <int NP1>
-__global__ __launch_bounds__(64) void k_theta_wide(const double *__restrict__ X, const double *__restrict__ p,
-                                                   Consts c, const double *__restrict__ sq,
-                                                   const double *__restrict__ wl, double *__restrict__ W)
-{
-    const int m = int(blockIdx.x) / c.M, mp = int(blockIdx.x) % c.M;
-    const int st = 3 * NP1;
-    if (m >= mp) return;
-    extern __shared__ double sh[];
-    const double xm[3] = {X[3 * m], X[3 * m + 1], X[3 * m + 2]};
-    const double pm[3] = {p[3 * m], p[3 * m + 1], p[3 * m + 2]};
-    const double xn[3] = {X[3 * mp], X[3 * mp + 1], X[3 * mp + 2]};
-    const double pn[3] = {p[3 * mp], p[3 * mp + 1], p[3 * mp + 2]};
-    const double h = 0.5 * c.r * c.r;
-    double acc[NP1][7];
-    double *out = sh + size_t(c.Q) * NP1 * 7;
-    for (int i = threadIdx.x; i < c.Q; i += 64) {
-        moment_point<NP1>(i, xm, pm, xn, pn, h, c, sq, wl, acc);
+        double acc[NC];
 #pragma unroll
-        for (int k = 0; k < NP1; ++k)
+        for (int k = 0; k < NC; ++k) acc[k] = 0.0;
+        const double si = wj[i * (NB + 1)], h = 0.5 * c.r * c.r;
+        const double b[3] = {xm[0] + si * pm[0] - xn[0], xm[1] + si * pm[1] - xn[1], xm[2] + si * pm[2] - xn[2]};
+        for (int j = 0; j < c.Q; j += 3) {
+            double w[3][NB + 1];
 #pragma unroll
-            for (int e = 0; e < 7; ++e) sh[(size_t(i) * NP1 + k) * 7 + e] = acc[k][e];
+            for (int e = 0; e < 3 * (NB + 1); ++e) w[e / (NB + 1)][e % (NB + 1)] = wj[j * (NB + 1) + e];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) moment_term<NP1>(b, pn, h, w[k], acc);
+        }
+        double *o = sh + size_t(slot) * per + i * NCP;
+#pragma unroll
+        for (int k = 0; k < NC; ++k) o[k] = acc[k];
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < NP1 * NP1 * 7; e += 64) {
-        const int n = e / (NP1 * 7), k = (e / 7) % NP1, cc = e % 7;
-        double s = 0.0;
-        for (int i = 0; i < c.Q; ++i) s += wl[n * c.Q + i] * sh[(size_t(i) * NP1 + k) * 7 + cc];
-        out[e] = s;
+    // outer sums: wave w takes three modes n at a time (weights in scalar
+    // registers), the lanes the columns of all pairs
+    const int wv = __builtin_amdgcn_readfirstlane(t >> 6), nw = (nt + 63) >> 6;
+    for (int n = 3 * wv; n < NB; n += 3 * nw) {
+        const double *w0 = wl + n * c.Q, *w1 = wl + min(n + 1, NB - 1) * c.Q, *w2 = wl + min(n + 2, NB - 1) * c.Q;
+        for (int e = t & 63; e < PB * NC; e += 64) {
+            const int s2 = e / NC, col = e - s2 * NC;
+            const double *b = sh + size_t(s2) * per + col;
+            double a0 = 0.0, a1 = 0.0, a2 = 0.0;
+#pragma unroll 6
+            for (int q = 0; q < c.Q; ++q) {
+                const double v = b[q * NCP];
+                a0 = fma(w0[q], v, a0);
+                a1 = fma(w1[q], v, a1);
+                a2 = fma(w2[q], v, a2);
+            }
+            const double s3[3] = {a0, a1, a2};
+            double *mo = sh + size_t(s2) * per + pts;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                if (col < NP1) {
+                    if (n + k < NP1) mo[(n + k) * NP1 + col] = s3[k];
+                } else if (n + k < NB) {
+                    mo[NP1 * NP1 + (n + k) * NB + col - NP1] = s3[k];
+                }
+            }
+        }
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < st * st; e += 64) {
-        const int row = e / st, col = e % st;
-        const int n = row / 3, a = row % 3, k = col / 3, b = col % 3;
-        const double *o = out + (n * NP1 + k) * 7;
-        const double v = o[sym_index(a, b)] + (a == b ? o[0] : 0.0);
-        put_sym(W, c.nt, m * st + row, mp * st + col, v);
+    // the six components of each (n, k) block
+    for (int e = t; e < PB * NP1 * NP1; e += nt) {
+        const int s2 = e / (NP1 * NP1), nk = e - s2 * (NP1 * NP1), n = nk / NP1, k = nk - n * NP1;
+        double *base = sh + size_t(s2) * per;
+        const double *A = base + pts;
+        pair_block<NP1>(n, k, A, A + NP1 * NP1, base + per - 9, up, dn, base + nk * 6);
+    }
+    __syncthreads();
+    // Theta^{n,k}_{m,mp} at (m st + row, mp st + col); its transpose,
+    // Theta^{k,n}_{mp,m}, is the mirror entry of the symmetric matrix (a
+    // diagonal tile is stored whole: the mirror too)
+    for (int s3 = 0; s3 < PB && p0 + s3 < P; ++s3) {
+        const Place q = place[s3];
+        const double *o = sh + size_t(s3) * per;
+        for (int e = t; e < st * st; e += nt) {
+            const uint32_t en = entry[e];
+            const int r = q.r0 + int(en & 255u), cc = q.c0 + int((en >> 8) & 255u);
+            const double v = o[en >> 16];
+            const int ri = r & (TS - 1), ci = cc & (TS - 1), br = r >= TS, bc = cc >= TS;
+            double *tile = W + q.at + (bc ? q.right : 0) + (br ? q.down : 0);
+            tile[ri * TS + ci] = v;
+            if (q.diag + bc - br == 0) tile[ci * TS + ri] = v;
+        }
     }
 }
 
@@ -258,8 +321,16 @@ __global__ __launch_bounds__(64) void k_theta_wide(const double *__restrict__ X,
 // written exactly once.  x entries beyond D read as zero.
 constexpr int SG = 8;          // tiles per workgroup
 
-__global__ __launch_bounds__(256) void k_symv(const double *__restrict__ W, const double *__restrict__ x,
-                                              double *__restrict__ part, const int4 *__restrict__ ch, int D, int nt)
+// the vectors of a product and their partial sums (two vectors share one pass over W)
+template <int NV>
+struct SymvArgs {
+    const double *x[NV];
+    double *part[NV];
+};
+
+template <int NV>
+__global__ __launch_bounds__(256) void k_symv(const double *__restrict__ W, SymvArgs<NV> a,
+                                              const int4 *__restrict__ ch, int D, int nt)
 {
     const int4 cw = ch[blockIdx.x];
     const int i = cw.x, j0 = cw.y, ng = cw.z, slot = cw.w;
@@ -267,30 +338,32 @@ __global__ __launch_bounds__(256) void k_symv(const double *__restrict__ W, cons
     const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
     const size_t ntT = size_t(nt) * TS;
     const double *tile = W + tile_base(i, j0, nt) + size_t(wv * 16) * TS + lane;
-    double xr[16];
+    double xr[NV][16], rp[NV][16];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const int ri = i * TS + wv * 16 + k;
-        xr[k] = ri < D ? x[ri] : 0.0;
-    }
-    __shared__ double cs[SG][4][TS];
-    double rp[16];
+    for (int s = 0; s < NV; ++s)
 #pragma unroll
-    for (int k = 0; k < 16; ++k) rp[k] = 0.0;
+        for (int k = 0; k < 16; ++k) {
+            const int ri = i * TS + wv * 16 + k;
+            xr[s][k] = ri < D ? a.x[s][ri] : 0.0;
+            rp[s][k] = 0.0;
+        }
+    __shared__ double cs[NV][SG][4][TS];
     double v[16];
 #pragma unroll
     for (int k = 0; k < 16; ++k) v[k] = tile[k * TS];
     for (int g = 0; g < ng; ++g) {
-        const int j = j0 + g;
-        const int cj = j * TS + lane;
-        const double xc = cj < D ? x[cj] : 0.0;
-        double col = 0.0;
+        const int cj = (j0 + g) * TS + lane;
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            col = fma(v[k], xr[k], col);
-            rp[k] = fma(v[k], xc, rp[k]);
+        for (int s = 0; s < NV; ++s) {
+            const double xc = cj < D ? a.x[s][cj] : 0.0;
+            double col = 0.0;
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                col = fma(v[k], xr[s][k], col);
+                rp[s][k] = fma(v[k], xc, rp[s][k]);
+            }
+            cs[s][g][wv][lane] = col;
         }
-        cs[g][wv][lane] = col;
         if (g + 1 < ng) {
             tile += TS * TS;
 #pragma unroll
@@ -302,64 +375,74 @@ __global__ __launch_bounds__(256) void k_symv(const double *__restrict__ W, cons
     // ends with the sum of row 16 v + 8 b5 + 4 b4 + 2 b3 + b2 (b: bits of l)
     const int b5 = (lane >> 5) & 1, b4 = (lane >> 4) & 1, b3 = (lane >> 3) & 1, b2 = (lane >> 2) & 1;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const double send = b5 ? rp[k] : rp[k + 8], keep = b5 ? rp[k + 8] : rp[k];
-        rp[k] = keep + __shfl_xor(send, 32, 64);
-    }
+    for (int s = 0; s < NV; ++s) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const double send = b4 ? rp[k] : rp[k + 4], keep = b4 ? rp[k + 4] : rp[k];
-        rp[k] = keep + __shfl_xor(send, 16, 64);
-    }
+        for (int k = 0; k < 8; ++k) {
+            const double send = b5 ? rp[s][k] : rp[s][k + 8], keep = b5 ? rp[s][k + 8] : rp[s][k];
+            rp[s][k] = keep + __shfl_xor(send, 32, 64);
+        }
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const double send = b3 ? rp[k] : rp[k + 2], keep = b3 ? rp[k + 2] : rp[k];
-        rp[k] = keep + __shfl_xor(send, 8, 64);
-    }
-    {
-        const double send = b2 ? rp[0] : rp[1], keep = b2 ? rp[1] : rp[0];
-        rp[0] = keep + __shfl_xor(send, 4, 64);
-    }
-    double rs = rp[0] + __shfl_xor(rp[0], 2, 64);
-    rs = rs + __shfl_xor(rs, 1, 64);
-    if ((lane & 3) == 0) {
-        const int r = wv * 16 + 8 * b5 + 4 * b4 + 2 * b3 + b2;
-        part[size_t(slot) * ntT + size_t(i) * TS + r] = rs;
+        for (int k = 0; k < 4; ++k) {
+            const double send = b4 ? rp[s][k] : rp[s][k + 4], keep = b4 ? rp[s][k + 4] : rp[s][k];
+            rp[s][k] = keep + __shfl_xor(send, 16, 64);
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const double send = b3 ? rp[s][k] : rp[s][k + 2], keep = b3 ? rp[s][k + 2] : rp[s][k];
+            rp[s][k] = keep + __shfl_xor(send, 8, 64);
+        }
+        const double send = b2 ? rp[s][0] : rp[s][1], keep = b2 ? rp[s][1] : rp[s][0];
+        double rs = keep + __shfl_xor(send, 4, 64);
+        rs += __shfl_xor(rs, 2, 64);
+        rs += __shfl_xor(rs, 1, 64);
+        if ((lane & 3) == 0) {
+            const int r = wv * 16 + 8 * b5 + 4 * b4 + 2 * b3 + b2;
+            a.part[s][size_t(slot) * ntT + size_t(i) * TS + r] = rs;
+        }
     }
     __syncthreads();
     // column sums of the off-diagonal tiles, the four waves' parts in order
-    for (int g = wv; g < ng; g += 4) {
-        const int j = j0 + g;
-        if (j == i) continue;
-        part[size_t(i) * ntT + size_t(j) * TS + lane] = (cs[g][0][lane] + cs[g][1][lane]) + (cs[g][2][lane] + cs[g][3][lane]);
-    }
+#pragma unroll
+    for (int s = 0; s < NV; ++s)
+        for (int g = wv; g < ng; g += 4) {
+            const int j = j0 + g;
+            if (j == i) continue;
+            a.part[s][size_t(i) * ntT + size_t(j) * TS + lane] =
+                (cs[s][g][0][lane] + cs[s][g][1][lane]) + (cs[s][g][2][lane] + cs[s][g][3][lane]);
+        }
 }
 
-// y[R] = sum over the partial sums of row R (block b = R / TS): slots
-// 0 .. ns - 1, ns = b + ceil((nt - b)/SG).  One workgroup per block of 64
-// rows; wave w adds the slots w, w + 4, w + 8, ... (independent loads, four
-// accumulators), the four waves' sums are then added in order.
-__global__ __launch_bounds__(256) void k_symv_sum(const double *__restrict__ part, double *__restrict__ y, int D,
-                                                  int nt)
+// Rows GR g .. GR g + GR - 1 of a product from its partial sums: the slots
+// 0 .. ns - 1 of a row's block b = R / TS, ns = b + ceil((nt - b)/SG), added by
+// four threads per row (slots q, q + 4, ..., four accumulators each), then in
+// order.  Called by 4 GR threads; out[GR] in LDS, zero beyond D; ends with a
+// barrier.
+constexpr int GT = TS;          // (m, n) rows of three per group
+constexpr int GR = 3 * GT;      // rows per group: 64 (m, n) triples, three tiles
+
+__device__ __forceinline__ void row_sums(const double *__restrict__ part, int g, int D, int nt, double (&ws)[4][GR],
+                                         double (&out)[GR])
 {
-    const int b = blockIdx.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int r = b * TS + lane;
-    const int ns = b + (nt - b + SG - 1) / SG;
+    const int lr = int(threadIdx.x) % GR, q = int(threadIdx.x) / GR;
+    const int r = g * GR + lr, b = r / TS;
     const size_t ntT = size_t(nt) * TS;
-    const double *pc = part + r;
     double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-    int t = wv;
-    for (; t + 12 < ns; t += 16) {
-        a0 += pc[size_t(t) * ntT];
-        a1 += pc[size_t(t + 4) * ntT];
-        a2 += pc[size_t(t + 8) * ntT];
-        a3 += pc[size_t(t + 12) * ntT];
+    if (r < D) {
+        const int ns = b + (nt - b + SG - 1) / SG;
+        const double *pc = part + r;
+        int t = q;
+        for (; t + 12 < ns; t += 16) {
+            a0 += pc[size_t(t) * ntT];
+            a1 += pc[size_t(t + 4) * ntT];
+            a2 += pc[size_t(t + 8) * ntT];
+            a3 += pc[size_t(t + 12) * ntT];
+        }
+        for (; t < ns; t += 4) a0 += pc[size_t(t) * ntT];
     }
-    for (; t < ns; t += 4) a0 += pc[size_t(t) * ntT];
-    __shared__ double ws[4][TS];
-    ws[wv][lane] = (a0 + a1) + (a2 + a3);
+    ws[q][lr] = (a0 + a1) + (a2 + a3);
     __syncthreads();
-    if (wv == 0 && r < D) y[r] = (ws[0][lane] + ws[1][lane]) + (ws[2][lane] + ws[3][lane]);
+    if (q == 0) out[lr] = (ws[0][lr] + ws[1][lr]) + (ws[2][lr] + ws[3][lr]);
+    __syncthreads();
 }
 
 // the chunks of k_symv for nt tiles per side: (i, j0, ng, slot) per workgroup
@@ -398,26 +481,20 @@ __device__ __forceinline__ double kbar_eig(int n)
     return -2.0 * s;
 }
 
-// Rows (m, n >= 1) of the system operator from x and z = W x:
+// Rows (m, n) of the system operator from x and z = W x:
 //   n >= 2: (Lambda + L_n K) x_n + c_n z_n
 //   n  = 1: (I - p p^T) x_1 + p p^T [(Lambda + L_1 K) x_1 + c_1 z_1]
-// c_n = (2n + 1)/(2l); rows n = 0 set to zero.  One thread per (m, n).
-__global__ __launch_bounds__(256) void k_apply(const double *__restrict__ x, const double *__restrict__ z,
-                                               double *__restrict__ y, const double *__restrict__ p, Consts c)
+// c_n = (2n + 1)/(2l); rows n = 0 are zero.
+__device__ __forceinline__ void apply_row(int n, const double *xi, const double *zi, const double *pm, const Consts &c,
+                                          double *yo)
 {
-    const int t = int(blockIdx.x * blockDim.x + threadIdx.x);
-    const int NP1 = c.N + 1;
-    if (t >= c.M * NP1) return;
-    const int m = t / NP1, n = t % NP1;
-    double *yo = y + size_t(3) * t;
     if (n == 0) {
         yo[0] = yo[1] = yo[2] = 0.0;
         return;
     }
     double lam[3][3], K[3][3], pp[3][3];
-    blocks(p + 3 * m, c.d, lam, K, pp);
+    blocks(pm, c.d, lam, K, pp);
     const double Ln = kbar_eig(n), cn = (2.0 * n + 1.0) / (2.0 * c.l);
-    const double *xi = x + size_t(3) * t, *zi = z + size_t(3) * t;
     double v[3];
     for (int a = 0; a < 3; ++a) {
         double s = 0.0;
@@ -427,9 +504,9 @@ __global__ __launch_bounds__(256) void k_apply(const double *__restrict__ x, con
     if (n >= 2) {
         for (int a = 0; a < 3; ++a) yo[a] = v[a];
     } else {
-        const double pv = p[3 * m] * v[0] + p[3 * m + 1] * v[1] + p[3 * m + 2] * v[2];
-        const double px = p[3 * m] * xi[0] + p[3 * m + 1] * xi[1] + p[3 * m + 2] * xi[2];
-        for (int a = 0; a < 3; ++a) yo[a] = (xi[a] - p[3 * m + a] * px) + p[3 * m + a] * pv;
+        const double pv = pm[0] * v[0] + pm[1] * v[1] + pm[2] * v[2];
+        const double px = pm[0] * xi[0] + pm[1] * xi[1] + pm[2] * xi[2];
+        for (int a = 0; a < 3; ++a) yo[a] = (xi[a] - pm[a] * px) + pm[a] * pv;
     }
 }
 
@@ -441,15 +518,8 @@ __global__ __launch_bounds__(256) void k_apply(const double *__restrict__ x, con
 // (I - beta/(alpha + beta) p p^T)/alpha.  GMRES runs on the right-
 // preconditioned operator A B^-1; the self part then is the identity and
 // the iteration count reflects the interactions only.
-__global__ __launch_bounds__(256) void k_precond(const double *__restrict__ in, double *__restrict__ out,
-                                                 const double *__restrict__ p, Consts c)
+__device__ __forceinline__ void precond_row(int n, const double *xi, const double *pm, const Consts &c, double *yo)
 {
-    const int t = int(blockIdx.x * blockDim.x + threadIdx.x);
-    const int NP1 = c.N + 1;
-    if (t >= c.M * NP1) return;
-    const int m = t / NP1, n = t % NP1;
-    const double *xi = in + size_t(3) * t;
-    double *yo = out + size_t(3) * t;
     if (n == 0) {
         yo[0] = yo[1] = yo[2] = 0.0;
         return;
@@ -457,33 +527,16 @@ __global__ __launch_bounds__(256) void k_precond(const double *__restrict__ in, 
     const double Ln = kbar_eig(n);
     const double alpha = n == 1 ? 1.0 : c.d + 2.0 + Ln;
     const double beta = n == 1 ? 2.0 * c.d + 2.0 * Ln - 1.0 : c.d - 2.0 + Ln;
-    const double *pm = p + 3 * m;
     const double px = pm[0] * xi[0] + pm[1] * xi[1] + pm[2] * xi[2];
     const double f = beta / (alpha + beta);
     for (int a = 0; a < 3; ++a) yo[a] = (xi[a] - f * px * pm[a]) / alpha;
 }
 
-// the known part of the force as a vector of the (m, k, b) layout:
-// F_m/(2l) in the k = 0 entries, zero elsewhere
-__global__ __launch_bounds__(256) void k_known(double *__restrict__ v, const double *__restrict__ F, Consts c)
-{
-    const int e = int(blockIdx.x * blockDim.x + threadIdx.x);
-    if (e >= c.D) return;
-    const int b = e % 3, k = (e / 3) % (c.N + 1), m = e / (3 * (c.N + 1));
-    v[e] = k == 0 ? F[3 * m + b] / (2.0 * c.l) : 0.0;
-}
-
 // right-hand side from z0 = W [F/(2l); 0]:
 //   n = 1: 3/(2 l^2) M x p - c_1 p p^T z0_1;  n >= 2: -c_n z0_n;  n = 0: 0
-__global__ __launch_bounds__(256) void k_rhs(const double *__restrict__ z0, double *__restrict__ b,
-                                             const double *__restrict__ p, const double *__restrict__ Mt, Consts c)
+__device__ __forceinline__ void rhs_row(int n, const double *zi, const double *pm, const double *mm, const Consts &c,
+                                        double *bo)
 {
-    const int t = int(blockIdx.x * blockDim.x + threadIdx.x);
-    const int NP1 = c.N + 1;
-    if (t >= c.M * NP1) return;
-    const int m = t / NP1, n = t % NP1;
-    double *bo = b + size_t(3) * t;
-    const double *zi = z0 + size_t(3) * t;
     if (n == 0) {
         bo[0] = bo[1] = bo[2] = 0.0;
         return;
@@ -493,27 +546,34 @@ __global__ __launch_bounds__(256) void k_rhs(const double *__restrict__ z0, doub
         for (int a = 0; a < 3; ++a) bo[a] = -cn * zi[a];
         return;
     }
-    const double *pm = p + 3 * m, *mm = Mt + 3 * m;
     const double mxp[3] = {mm[1] * pm[2] - mm[2] * pm[1], mm[2] * pm[0] - mm[0] * pm[2], mm[0] * pm[1] - mm[1] * pm[0]};
     const double pz = pm[0] * zi[0] + pm[1] * zi[1] + pm[2] * zi[2];
     const double tq = 3.0 / (2.0 * c.l * c.l);
     for (int a = 0; a < 3; ++a) bo[a] = tq * mxp[a] - cn * pm[a] * pz;
 }
 
-// velocities from z = W [F/(2l); a] (rows n = 0: int U ds, n = 1: int U P_1 ds):
+// the known part of the force as a vector of the (m, k, b) layout:
+// F_m/(2l) in the k = 0 entries, zero elsewhere
+__device__ __forceinline__ double known_entry(int e, const double *F, const Consts &c)
+{
+    const int b = e % 3, k = (e / 3) % (c.N + 1), m = e / (3 * (c.N + 1));
+    return k == 0 ? F[3 * m + b] / (2.0 * c.l) : 0.0;
+}
+__global__ __launch_bounds__(256) void k_known(double *__restrict__ v, const double *__restrict__ F, Consts c)
+{
+    const int e = int(blockIdx.x * blockDim.x + threadIdx.x);
+    if (e < c.D) v[e] = known_entry(e, F, c);
+}
+
+// velocities of fiber m from z = W [F/(2l); a] (rows n = 0: int U ds, n = 1:
+// int U P_1 ds):
 //   dx/dt = (Lambda F + z_0) / (8 pi mu L)
 //   dp/dt = 3/(2 pi mu L^3) [d M x p + (I - p p^T) l z_1]
-__global__ __launch_bounds__(256) void k_velocity(const double *__restrict__ z, const double *__restrict__ p,
-                                                  const double *__restrict__ F, const double *__restrict__ Mt,
-                                                  double *__restrict__ V, double *__restrict__ Pd, Consts c)
+__device__ __forceinline__ void velocity_of(const double z0[3], const double z1[3], const double *pm, const double *f,
+                                            const double *mm, const Consts &c, double *V, double *Pd)
 {
-    const int m = int(blockIdx.x * blockDim.x + threadIdx.x);
-    if (m >= c.M) return;
-    const int NP1 = c.N + 1;
     double lam[3][3], K[3][3], pp[3][3];
-    blocks(p + 3 * m, c.d, lam, K, pp);
-    const double *z0 = z + size_t(3) * (m * NP1), *z1 = z0 + 3;
-    const double *pm = p + 3 * m, *mm = Mt + 3 * m, *f = F + 3 * m;
+    blocks(pm, c.d, lam, K, pp);
     const double kv = 1.0 / (8.0 * M_PI * c.mu * c.L);
     const double kw = 3.0 / (2.0 * M_PI * c.mu * c.L * c.L * c.L);
     const double mxp[3] = {mm[1] * pm[2] - mm[2] * pm[1], mm[2] * pm[0] - mm[0] * pm[2], mm[0] * pm[1] - mm[1] * pm[0]};
@@ -521,136 +581,266 @@ __global__ __launch_bounds__(256) void k_velocity(const double *__restrict__ z, 
     for (int a = 0; a < 3; ++a) {
         double s = 0.0;
         for (int b = 0; b < 3; ++b) s += lam[a][b] * f[b];
-        V[3 * m + a] = kv * (s + z0[a]);
-        Pd[3 * m + a] = kw * (c.d * mxp[a] + c.l * (z1[a] - pm[a] * pz));
+        V[a] = kv * (s + z0[a]);
+        Pd[a] = kw * (c.d * mxp[a] + c.l * (z1[a] - pm[a] * pz));
     }
+}
+
+// z = zk + zx: the products with the known and the unknown part
+__global__ __launch_bounds__(256) void k_velocity(const double *__restrict__ zk, const double *__restrict__ zx,
+                                                  const double *__restrict__ p, const double *__restrict__ F,
+                                                  const double *__restrict__ Mt, double *__restrict__ V,
+                                                  double *__restrict__ Pd, Consts c)
+{
+    const int m = int(blockIdx.x * blockDim.x + threadIdx.x);
+    if (m >= c.M) return;
+    const size_t o = size_t(3) * m * (c.N + 1);
+    double z[6];
+    for (int a = 0; a < 6; ++a) z[a] = zk[o + a] + zx[o + a];
+    velocity_of(z, z + 3, p + 3 * m, F + 3 * m, Mt + 3 * m, c, V + 3 * m, Pd + 3 * m);
 }
 
 // ------------------------------------------------------------------ GMRES pieces
-// h[j] = <V_j, w> for j < nj in two passes with a fixed summation order:
-// workgroup (j, p) sums chunk p of DP chunks of the vectors into
-// part[j DP + p]; k_dots_sum adds the DP partial sums of each j in order.
-constexpr int DP = 16;
+// An iteration is five launches: the product's partial sums (k_symv), the rows
+// of A B^-1 v_i with the first dot products (k_apply_dots), the two Gram-
+// Schmidt passes (k_orth), and the new basis vector with the rotation of its
+// column (k_next).  Every dot product is summed per group of GR rows into
+// part[j][group], and each workgroup of the next launch adds the groups'
+// sums itself (a few thousand doubles from L2), so no launch is spent on a
+// reduction.  All orders of summation are fixed.
 
-__global__ __launch_bounds__(256) void k_dots(const double *__restrict__ Vb, const double *__restrict__ w,
-                                              double *__restrict__ part, int D)
+__device__ __forceinline__ double wave_sum(double s)
 {
-    const int j = blockIdx.y, pc = blockIdx.x;
-    const int chunk = (D + DP - 1) / DP, e0 = pc * chunk, e1 = min(D, e0 + chunk);
-    const double *v = Vb + size_t(j) * D;
-    double s = 0.0;
-    for (int e = e0 + int(threadIdx.x); e < e1; e += 256) s += v[e] * w[e];
-    __shared__ double red[4];
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) part[j * DP + pc] = (red[0] + red[1]) + (red[2] + red[3]);
+    return s;
 }
 
-__global__ __launch_bounds__(64) void k_dots_sum(const double *__restrict__ part, double *__restrict__ h, int nj)
+// <V_j, w> over the group's rows w[GR] (LDS) for j < nj, one wave per j
+__device__ __forceinline__ void group_dots(const double *__restrict__ Vb, const double (&w)[GR], double *__restrict__ part,
+                                           int nj, int g, int G, int D)
 {
-    const int j = int(threadIdx.x);
-    if (j >= nj) return;
-    double s = 0.0;
-    for (int p = 0; p < DP; ++p) s += part[j * DP + p];
-    h[j] = s;
-}
-
-// w -= sum_{j < nj} h[j] V_j; acc[j] += h[j] (the column of H)
-__global__ __launch_bounds__(256) void k_orth(const double *__restrict__ Vb, double *__restrict__ w,
-                                              const double *__restrict__ h, int nj, int D)
-{
-    const int e = int(blockIdx.x * blockDim.x + threadIdx.x);
-    if (e >= D) return;
-    double s = w[e];
-    for (int j = 0; j < nj; ++j) s -= h[j] * Vb[size_t(j) * D + e];
-    w[e] = s;
-}
-
-// single thread: H column i += correction; norm of w -> H[i+1][i]; Givens
-// rotations on the column; residual |g[i+1]| into res[0]
-__global__ void k_hcol(double *__restrict__ H, const double *__restrict__ h1, const double *__restrict__ h2,
-                       const double *__restrict__ nrm, double *__restrict__ cs, double *__restrict__ sn,
-                       double *__restrict__ g, double *__restrict__ res, int i)
-{
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    double col[MAXR + 1];
-    for (int j = 0; j <= i; ++j) col[j] = h1[j] + h2[j];
-    col[i + 1] = sqrt(nrm[0]);
-    for (int j = 0; j < i; ++j) {
-        const double a = cs[j] * col[j] + sn[j] * col[j + 1];
-        const double b = -sn[j] * col[j] + cs[j] * col[j + 1];
-        col[j] = a;
-        col[j + 1] = b;
+    const int lane = threadIdx.x & 63;
+    for (int j = int(threadIdx.x >> 6); j < nj; j += int(blockDim.x >> 6)) {
+        const double *v = Vb + size_t(j) * D + size_t(g) * GR;
+        double s = 0.0;
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            if (g * GR + lane + 64 * k < D) s += v[lane + 64 * k] * w[lane + 64 * k];
+        s = wave_sum(s);
+        if (lane == 0) part[size_t(j) * G + g] = s;
     }
-    const double a = col[i], b = col[i + 1];
-    const double rr = sqrt(a * a + b * b);
-    const double c = rr > 0.0 ? a / rr : 1.0, s = rr > 0.0 ? b / rr : 0.0;
+}
+
+// h[j] = sum over the G groups of part[j], j < nj, in LDS; ends with a barrier
+__device__ __forceinline__ void group_totals(const double *__restrict__ part, double *h, int nj, int G)
+{
+    const int lane = threadIdx.x & 63;
+    for (int j = int(threadIdx.x >> 6); j < nj; j += int(blockDim.x >> 6)) {
+        double s = 0.0;
+        for (int g = lane; g < G; g += 64) s += part[size_t(j) * G + g];
+        s = wave_sum(s);
+        if (lane == 0) h[j] = s;
+    }
+    __syncthreads();
+}
+
+// rows of z = W x from the partial sums (a plain product)
+__global__ __launch_bounds__(4 * GR) void k_rows(const double *__restrict__ part, double *__restrict__ z, int D, int nt)
+{
+    __shared__ double ws[4][GR], zs[GR];
+    row_sums(part, int(blockIdx.x), D, nt, ws, zs);
+    const int lr = int(threadIdx.x), r = int(blockIdx.x) * GR + lr;
+    if (lr < GR && r < D) z[r] = zs[lr];
+}
+
+// z = W t from the partial sums, w = A t, and the group's <V_j, w>, j < nj
+__global__ __launch_bounds__(4 * GR) void k_apply_dots(const double *__restrict__ part, const double *__restrict__ t,
+                                                       const double *__restrict__ p, const double *__restrict__ Vb,
+                                                       double *__restrict__ z, double *__restrict__ w,
+                                                       double *__restrict__ dp, int nj, int G, Consts c)
+{
+    __shared__ double ws[4][GR], zs[GR], wr[GR];
+    const int g = int(blockIdx.x), lr = int(threadIdx.x);
+    row_sums(part, g, c.D, c.nt, ws, zs);
+    if (lr < GT) {
+        const int e = g * GT + lr, NP1 = c.N + 1;
+        double y[3] = {0.0, 0.0, 0.0};
+        if (e < c.M * NP1) apply_row(e % NP1, t + size_t(3) * e, zs + 3 * lr, p + 3 * (e / NP1), c, y);
+        for (int a = 0; a < 3; ++a) wr[3 * lr + a] = y[a];
+    }
+    __syncthreads();
+    const int r = g * GR + lr;
+    if (lr < GR && r < c.D) {
+        z[r] = zs[lr];
+        w[r] = wr[lr];
+    }
+    group_dots(Vb, wr, dp, nj, g, G, c.D);
+}
+
+// One Gram-Schmidt pass: h[j] = sum of part_in[j], w -= sum_j h[j] V_j, then
+// the group's <V_j, w> (first pass) or <w, w> (second) into part_out.
+__global__ __launch_bounds__(256) void k_orth(const double *__restrict__ Vb, double *__restrict__ w,
+                                              const double *__restrict__ part_in, double *__restrict__ part_out,
+                                              double *__restrict__ h_out, int nj, int G, int D, int second)
+{
+    __shared__ double h[MAXR + 1], wr[GR];
+    const int g = int(blockIdx.x), lr = int(threadIdx.x), r = g * GR + lr;
+    group_totals(part_in, h, nj, G);
+    if (g == 0 && lr < nj) h_out[lr] = h[lr];
+    if (lr < GR) {
+        double s = 0.0;
+        if (r < D) {
+            s = w[r];
+            for (int j = 0; j < nj; ++j) s -= h[j] * Vb[size_t(j) * D + r];
+            w[r] = s;
+        }
+        wr[lr] = s;
+    }
+    __syncthreads();
+    if (!second) {
+        group_dots(Vb, wr, part_out, nj, g, G, D);
+    } else if (lr < 64) {
+        const double s = wave_sum(wr[lr] * wr[lr] + wr[lr + 64] * wr[lr + 64] + wr[lr + 128] * wr[lr + 128]);
+        if (lr == 0) part_out[g] = s;
+    }
+}
+
+// Column i of H from the two passes' sums and the norm of w: Givens rotations
+// of the column, the residual |g[i+1]| returned.  One thread.
+__device__ __forceinline__ double rotate_column(double *H, int ld, const double *h1, const double *h2, double norm,
+                                                double *cs, double *sn, double *g, int i)
+{
+    double cur = h1[0] + h2[0];
+    for (int j = 0; j < i; ++j) {
+        const double nxt = h1[j + 1] + h2[j + 1];
+        H[j * ld + i] = cs[j] * cur + sn[j] * nxt;
+        cur = -sn[j] * cur + cs[j] * nxt;
+    }
+    const double rr = sqrt(cur * cur + norm * norm);
+    const double c = rr > 0.0 ? cur / rr : 1.0, s = rr > 0.0 ? norm / rr : 0.0;
     cs[i] = c;
     sn[i] = s;
-    col[i] = rr;
-    col[i + 1] = 0.0;
+    H[i * ld + i] = rr;
     g[i + 1] = -s * g[i];
     g[i] = c * g[i];
-    for (int j = 0; j <= i; ++j) H[j * MAXR + i] = col[j];
-    res[0] = fabs(g[i + 1]);
+    return fabs(g[i + 1]);
 }
 
-// V_{i+1} = w / sqrt(nrm) (zero when the Krylov space is exhausted)
-__global__ __launch_bounds__(256) void k_normalize(const double *__restrict__ w, double *__restrict__ v,
-                                                   const double *__restrict__ nrm, int D)
+// V_{i+1} = w/|w| (zero when the Krylov space is exhausted) and t = B^-1 V_{i+1};
+// workgroup 0 also rotates column i and leaves the residual in host memory.
+__global__ __launch_bounds__(256) void k_next(const double *__restrict__ w, double *__restrict__ vn,
+                                              double *__restrict__ t, const double *__restrict__ p,
+                                              const double *__restrict__ part, double *__restrict__ H,
+                                              const double *__restrict__ h1, const double *__restrict__ h2,
+                                              double *__restrict__ cs, double *__restrict__ sn, double *__restrict__ g,
+                                              double *__restrict__ res, int i, int G, Consts c)
 {
-    const int e = int(blockIdx.x * blockDim.x + threadIdx.x);
-    if (e >= D) return;
-    const double n = sqrt(nrm[0]);
-    v[e] = n > 0.0 ? w[e] / n : 0.0;
+    __shared__ double nn[1];
+    group_totals(part, nn, 1, G);
+    const double n = sqrt(nn[0]);
+    const int e = int(blockIdx.x * blockDim.x + threadIdx.x), NP1 = c.N + 1;
+    if (e < c.M * NP1) {
+        double v[3], y[3];
+        for (int a = 0; a < 3; ++a) {
+            v[a] = n > 0.0 ? w[size_t(3) * e + a] / n : 0.0;
+            vn[size_t(3) * e + a] = v[a];
+        }
+        precond_row(e % NP1, v, p + 3 * (e / NP1), c, y);
+        for (int a = 0; a < 3; ++a) t[size_t(3) * e + a] = y[a];
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) res[i] = rotate_column(H, MAXR, h1, h2, n, cs, sn, g, i);
 }
 
-// r = b - y; nrm = <r, r> computed separately; g = (|r|, 0, ...)
-__global__ __launch_bounds__(256) void k_residual(const double *__restrict__ b, const double *__restrict__ y,
-                                                  double *__restrict__ r, int D)
+// b from z0 = W [F/(2l); 0], r = b - A x from zx = W x, and the groups' <b, b>
+// and <r, r> into part[0][], part[1][]
+__global__ __launch_bounds__(GT) void k_start(const double *__restrict__ z0, const double *__restrict__ x,
+                                              const double *__restrict__ zx, const double *__restrict__ p,
+                                              const double *__restrict__ Mt, double *__restrict__ r,
+                                              double *__restrict__ part, int G, Consts c)
 {
-    const int e = int(blockIdx.x * blockDim.x + threadIdx.x);
-    if (e < D) r[e] = b[e] - y[e];
-}
-
-__global__ void k_gstart(double *__restrict__ g, const double *__restrict__ nrm, double *__restrict__ res)
-{
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        g[0] = sqrt(nrm[0]);
-        res[0] = g[0];
+    const int g = int(blockIdx.x), e = g * GT + int(threadIdx.x), NP1 = c.N + 1;
+    double bb = 0.0, rr = 0.0;
+    if (e < c.M * NP1) {
+        const int n = e % NP1, m = e / NP1;
+        double b[3], y[3];
+        rhs_row(n, z0 + size_t(3) * e, p + 3 * m, Mt + 3 * m, c, b);
+        apply_row(n, x + size_t(3) * e, zx + size_t(3) * e, p + 3 * m, c, y);
+        for (int a = 0; a < 3; ++a) {
+            const double v = b[a] - y[a];
+            r[size_t(3) * e + a] = v;
+            bb += b[a] * b[a];
+            rr += v * v;
+        }
+    }
+    bb = wave_sum(bb);
+    rr = wave_sum(rr);
+    if (threadIdx.x == 0) {
+        part[g] = bb;
+        part[G + g] = rr;
     }
 }
 
-// back substitution H y = g over k columns
-__global__ void k_backsolve(const double *__restrict__ H, const double *__restrict__ g, double *__restrict__ y,
-                            int k)
+// V_0 = r/|r|, t = B^-1 V_0, g[0] = |r|; |b| and |r| to host memory
+__global__ __launch_bounds__(256) void k_first(const double *__restrict__ r, double *__restrict__ v0,
+                                               double *__restrict__ t, const double *__restrict__ p,
+                                               const double *__restrict__ part, double *__restrict__ g,
+                                               double *__restrict__ norms, int G, Consts c)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+    __shared__ double nn[2];
+    group_totals(part, nn, 2, G);
+    const double n = sqrt(nn[1]);
+    const int e = int(blockIdx.x * blockDim.x + threadIdx.x), NP1 = c.N + 1;
+    if (e < c.M * NP1) {
+        double v[3], y[3];
+        for (int a = 0; a < 3; ++a) {
+            v[a] = n > 0.0 ? r[size_t(3) * e + a] / n : 0.0;
+            v0[size_t(3) * e + a] = v[a];
+        }
+        precond_row(e % NP1, v, p + 3 * (e / NP1), c, y);
+        for (int a = 0; a < 3; ++a) t[size_t(3) * e + a] = y[a];
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        g[0] = n;
+        norms[0] = sqrt(nn[0]);
+        norms[1] = n;
+    }
+}
+
+// back substitution H y = g over k <= 64 columns by one wave: lane j holds g_j
+__global__ __launch_bounds__(64) void k_backsolve(const double *__restrict__ H, const double *__restrict__ g,
+                                                  double *__restrict__ y, int k)
+{
+    const int j = int(threadIdx.x);
+    double s = j < k ? g[j] : 0.0;
     for (int i = k - 1; i >= 0; --i) {
-        double s = g[i];
-        for (int j = i + 1; j < k; ++j) s -= H[i * MAXR + j] * y[j];
-        const double d = H[i * MAXR + i];
-        y[i] = d != 0.0 ? s / d : 0.0;
+        const double d = H[i * MAXR + i], yi = d != 0.0 ? __shfl(s, i, 64) / d : 0.0;
+        if (j == i) y[i] = yi;
+        if (j < i) s -= H[j * MAXR + i] * yi;
     }
 }
 
-// out = sum_{j < k} y_j V_j
-__global__ __launch_bounds__(256) void k_lincomb(double *__restrict__ out, const double *__restrict__ Vb,
-                                                 const double *__restrict__ y, int k, int D)
+// x += B^-1 sum_j y_j V_j and zx += sum_j y_j Z_j, Z_j = W B^-1 V_j kept from the
+// iterations: zx stays W x without another product
+__global__ __launch_bounds__(256) void k_update(double *__restrict__ x, double *__restrict__ zx,
+                                                const double *__restrict__ Vb, const double *__restrict__ Zb,
+                                                const double *__restrict__ y, const double *__restrict__ p, int k,
+                                                Consts c)
 {
-    const int e = int(blockIdx.x * blockDim.x + threadIdx.x);
-    if (e >= D) return;
-    double s = 0.0;
-    for (int j = 0; j < k; ++j) s += y[j] * Vb[size_t(j) * D + e];
-    out[e] = s;
-}
-
-// out = a + b
-__global__ __launch_bounds__(256) void k_add(const double *a, const double *b, double *out, int D)
-{
-    const int e = int(blockIdx.x * blockDim.x + threadIdx.x);
-    if (e < D) out[e] = a[e] + b[e];
+    const int e = int(blockIdx.x * blockDim.x + threadIdx.x), NP1 = c.N + 1;
+    if (e >= c.M * NP1) return;
+    double v[3] = {0.0, 0.0, 0.0}, z[3] = {0.0, 0.0, 0.0}, u[3];
+    for (int j = 0; j < k; ++j) {
+        const double yj = y[j];
+        for (int a = 0; a < 3; ++a) {
+            v[a] += yj * Vb[size_t(j) * c.D + size_t(3) * e + a];
+            z[a] += yj * Zb[size_t(j) * c.D + size_t(3) * e + a];
+        }
+    }
+    precond_row(e % NP1, v, p + 3 * (e / NP1), c, u);
+    for (int a = 0; a < 3; ++a) {
+        x[size_t(3) * e + a] += u[a];
+        zx[size_t(3) * e + a] += z[a];
+    }
 }
 
 // GMRES start of a time step: the linear extrapolation 2 a_n - a_{n-1} of
@@ -664,27 +854,33 @@ __global__ __launch_bounds__(256) void k_extrap(double *__restrict__ x, double *
     xh[e] = a;
 }
 
-// Adams-Bashforth 2 (Euler when first), p renormalised
+// Adams-Bashforth 2 of fiber m (Euler when first), p renormalised
+__device__ __forceinline__ void advance_fiber(double *X, double *p, const double *V, const double *Pd, double *Vp,
+                                              double *Pp, double dt, bool first)
+{
+    double q[3];
+    for (int a = 0; a < 3; ++a) {
+        const double v = V[a], w = Pd[a];
+        const double dv = first ? v : 1.5 * v - 0.5 * Vp[a];
+        const double dw = first ? w : 1.5 * w - 0.5 * Pp[a];
+        X[a] += dt * dv;
+        q[a] = p[a] + dt * dw;
+        Vp[a] = v;
+        Pp[a] = w;
+    }
+    const double n = sqrt(q[0] * q[0] + q[1] * q[1] + q[2] * q[2]);
+    for (int a = 0; a < 3; ++a) p[a] = q[a] / n;
+}
 __global__ __launch_bounds__(256) void k_advance(double *__restrict__ X, double *__restrict__ p,
                                                  const double *__restrict__ V, const double *__restrict__ Pd,
                                                  double *__restrict__ Vp, double *__restrict__ Pp, int M, double dt,
                                                  int first)
 {
     const int m = int(blockIdx.x * blockDim.x + threadIdx.x);
-    if (m >= M) return;
-    double q[3];
-    for (int a = 0; a < 3; ++a) {
-        const double v = V[3 * m + a], w = Pd[3 * m + a];
-        const double dv = first ? v : 1.5 * v - 0.5 * Vp[3 * m + a];
-        const double dw = first ? w : 1.5 * w - 0.5 * Pp[3 * m + a];
-        X[3 * m + a] += dt * dv;
-        q[a] = p[3 * m + a] + dt * dw;
-        Vp[3 * m + a] = v;
-        Pp[3 * m + a] = w;
-    }
-    const double n = sqrt(q[0] * q[0] + q[1] * q[1] + q[2] * q[2]);
-    for (int a = 0; a < 3; ++a) p[3 * m + a] = q[a] / n;
+    if (m < M) advance_fiber(X + 3 * m, p + 3 * m, V + 3 * m, Pd + 3 * m, Vp + 3 * m, Pp + 3 * m, dt, first != 0);
 }
+
+#include "sbf_small.h"
 
 }  // namespace sbfk
 
@@ -699,21 +895,24 @@ struct sbf_ctx {
     int M = 0, Dmax = 0;
     // device
     double *X = nullptr, *pd = nullptr, *F = nullptr, *Mt = nullptr;
-    double *sq = nullptr, *wl = nullptr;   // quadrature nodes; weights times P_k at the nodes
+    double *wl = nullptr, *wj = nullptr;   // weights times P_k at the nodes, by k; nodes and the same by node
     double *W = nullptr;                   // packed upper triangle of the moment matrix
-    double *part = nullptr;                // [nt][nt TS] partial sums of a product with W
+    double *part = nullptr, *part2 = nullptr;   // [nt][nt TS] partial sums of a product with W (of two vectors)
     int4 *chunks = nullptr;                // work list of the product kernel
-    double *dpart = nullptr;               // [MAXR][DP] partial dot products
+    double *dpart = nullptr;               // [3][MAXR + 1][groups] dot products per group of rows
+    int gmax = 0;                          // groups of Dmax rows
     unsigned nchunks = 0;
-    double *x = nullptr, *b = nullptr, *r = nullptr, *w = nullptr, *y = nullptr, *kn = nullptr, *z = nullptr;
-    double *t = nullptr, *u = nullptr;     // preconditioned vectors
+    double *x = nullptr, *r = nullptr, *w = nullptr, *kn = nullptr;
+    double *z0 = nullptr, *zx = nullptr;   // products of W with the known part and with x
+    double *t = nullptr;                   // preconditioned basis vector
+    double *Zb = nullptr;                  // [restart][D] W B^-1 V_j
     double *xh = nullptr;                   // the solution of the previous time step
     int nsol = 0;                           // solutions of time steps since the fibers were set
     double *Vb = nullptr;                   // [restart + 1][D]
     double *H = nullptr, *cs = nullptr, *sn = nullptr, *g = nullptr, *h1 = nullptr, *h2 = nullptr, *ys = nullptr;
-    double *nrm = nullptr, *res = nullptr;  // scalars
-    double *resh = nullptr;                 // pinned host copies of the residual, one per iteration
-    hipEvent_t rev[MAXR] = {};              // recorded after each copy
+    double *resh = nullptr;                 // pinned host memory: the residual of each iteration, then |b|, |r|
+    SmallResult *small = nullptr;           // pinned host memory: what a one-workgroup solve reports
+    hipEvent_t rev[MAXR] = {};              // recorded after each iteration
     double *V = nullptr, *Pd = nullptr, *Vp = nullptr, *Pp = nullptr;
     bool first = true, solved = false;
     // event timing: pairs recorded around the moment kernel and each GEMV
@@ -750,19 +949,12 @@ static hipError_t theta_t(sbf_ctx *c)
 {
     const int Q = c->c.Q;
     if (c->M < 2) return hipSuccess;
-    if (Q > 64) {
-        const size_t lds = (size_t(Q) * NP1 * 7 + size_t(NP1) * NP1 * 7) * sizeof(double);
-        hipLaunchKernelGGL((k_theta_wide<NP1>), dim3(unsigned(c->M) * unsigned(c->M)), dim3(64), lds, c->st, c->X,
-                           c->pd, c->c, c->sq, c->wl, c->W);
-        return hipGetLastError();
-    }
     // pairs per workgroup: the most lanes busy (PB Q over whole waves), then
-    // the most pairs, within 64 KiB of LDS
-    const size_t per_pair = (size_t(Q) * 7 + size_t(NP1) * NP1 * 7) * sizeof(double);
-    const size_t fixed = size_t(NP1) * Q * sizeof(double);   // the weights; (m, m') pairs below
+    // the most pairs, within 64 KiB of LDS (Q > 128: one pair)
+    const size_t per = size_t(theta_lds(NP1, Q)) * sizeof(double), most = 65536 - 7168;   // and the static part
     int pb = 1;
     double best = 0.0;
-    for (int k = 1; k * Q <= 256 && fixed + size_t((k + 1) / 2 * 2) * 8 + size_t(k) * per_pair <= 65536; ++k) {
+    for (int k = 1; k * Q <= 256 && size_t(k) * per <= most; ++k) {
         const double use = double(k * Q) / double(((k * Q + 63) / 64) * 64);
         if (use >= best) {
             best = use;
@@ -770,10 +962,9 @@ static hipError_t theta_t(sbf_ctx *c)
         }
     }
     const unsigned threads = unsigned(((pb * Q + 63) / 64) * 64);
-    const long long P = (long long)c->M * (c->M - 1) / 2;
-    const size_t lds = fixed + size_t((pb + 1) / 2 * 2) * sizeof(double) + size_t(pb) * per_pair;
-    hipLaunchKernelGGL((k_theta<NP1>), dim3(unsigned((P + pb - 1) / pb)), dim3(threads), lds, c->st, c->X, c->pd,
-                       c->c, c->sq, c->wl, c->W, pb, P);
+    const int P = int((long long)c->M * (c->M - 1) / 2);
+    hipLaunchKernelGGL((k_theta<NP1>), dim3(unsigned((P + pb - 1) / pb)), dim3(threads), size_t(pb) * per, c->st, c->X,
+                       c->pd, c->c, c->wj, c->wl, c->W, pb, P);
     return hipGetLastError();
 }
 
@@ -827,119 +1018,82 @@ static hipError_t collect(sbf_ctx *c)
     return hipSuccess;
 }
 
-static hipError_t gemv(sbf_ctx *c, const double *xin, double *yout)
+// partial sums of W xin into c->part
+static hipError_t product(sbf_ctx *c, const double *xin)
 {
-    hipError_t e = mark(c, 1, true);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_symv, dim3(c->nchunks), dim3(256), 0, c->st, c->W, xin, c->part, c->chunks, c->c.D,
-                       c->c.nt);
-    hipLaunchKernelGGL(k_symv_sum, dim3(unsigned(c->c.nt)), dim3(256), 0, c->st, c->part, yout, c->c.D, c->c.nt);
-    e = hipGetLastError();
-    return e != hipSuccess ? e : mark(c, 1, false);
-}
-
-// y = A x (system operator)
-static hipError_t apply(sbf_ctx *c, const double *xin, double *yout)
-{
-    hipError_t e = gemv(c, xin, c->z);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_apply, dim3(nblk(size_t(c->M) * (c->c.N + 1))), dim3(256), 0, c->st, xin, c->z, yout,
-                       c->pd, c->c);
+    SymvArgs<1> a{{xin}, {c->part}};
+    hipLaunchKernelGGL(k_symv<1>, dim3(c->nchunks), dim3(256), 0, c->st, c->W, a, c->chunks, c->c.D, c->c.nt);
     return hipGetLastError();
-}
-
-// out = B^-1 in (block-Jacobi)
-static hipError_t precond(sbf_ctx *c, const double *in, double *out)
-{
-    hipLaunchKernelGGL(k_precond, dim3(nblk(size_t(c->M) * (c->c.N + 1))), dim3(256), 0, c->st, in, out, c->pd,
-                       c->c);
-    return hipGetLastError();
-}
-
-// nrm = <v, v>
-// h[0 .. nj) = <V_j, w> for the nj vectors starting at Vb
-static hipError_t dots(sbf_ctx *c, const double *Vb, const double *w, double *h, int nj)
-{
-    hipLaunchKernelGGL(k_dots, dim3(DP, unsigned(nj)), dim3(256), 0, c->st, Vb, w, c->dpart, c->c.D);
-    hipLaunchKernelGGL(k_dots_sum, dim3(1), dim3(64), 0, c->st, c->dpart, h, nj);
-    return hipGetLastError();
-}
-
-static hipError_t dot_self(sbf_ctx *c, const double *v) { return dots(c, v, v, c->nrm, 1); }
-
-static lbm_status read_scalar(sbf_ctx *c, const double *dptr, double *out)
-{
-    SCHK(c, hipMemcpyAsync(out, dptr, sizeof(double), hipMemcpyDeviceToHost, c->st));
-    SCHK(c, hipStreamSynchronize(c->st));
-    SCHK(c, collect(c));
-    return LBM_OK;
 }
 
 // moments, right-hand side, GMRES (right block-Jacobi preconditioning, from
 // the previous solution), velocities
 static lbm_status do_solve(sbf_ctx *c)
 {
-    const int D = c->c.D;
-    const unsigned gd = nblk(size_t(D));
+    const int D = c->c.D, G = (D + GR - 1) / GR;
+    const dim3 gg{unsigned(G)}, ge{nblk(size_t(c->M) * (c->c.N + 1))}, b256{256}, b4{4 * GR};
+    double *dp[3] = {c->dpart, c->dpart + size_t(MAXR + 1) * c->gmax, c->dpart + 2 * size_t(MAXR + 1) * c->gmax};
+    double *norms = c->resh + MAXR;
     SCHK(c, mark(c, 0, true));
     SCHK(c, launch_theta(c));
     SCHK(c, mark(c, 0, false));
-    hipLaunchKernelGGL(k_known, dim3(gd), dim3(256), 0, c->st, c->kn, c->F, c->c);
+    // one pass over W for the known part and the start vector
+    SCHK(c, mark(c, 1, true));
+    SymvArgs<2> two{{c->kn, c->x}, {c->part, c->part2}};
+    hipLaunchKernelGGL(k_symv<2>, dim3(c->nchunks), b256, 0, c->st, c->W, two, c->chunks, D, c->c.nt);
+    hipLaunchKernelGGL(k_rows, gg, b4, 0, c->st, c->part, c->z0, D, c->c.nt);
+    hipLaunchKernelGGL(k_rows, gg, b4, 0, c->st, c->part2, c->zx, D, c->c.nt);
     SCHK(c, hipGetLastError());
-    SCHK(c, gemv(c, c->kn, c->z));
-    hipLaunchKernelGGL(k_rhs, dim3(nblk(size_t(c->M) * (c->c.N + 1))), dim3(256), 0, c->st, c->z, c->b, c->pd,
-                       c->Mt, c->c);
-    SCHK(c, hipGetLastError());
-    SCHK(c, dot_self(c, c->b));
-    double bn2 = 0.0;
-    lbm_status s = read_scalar(c, c->nrm, &bn2);
-    if (s != LBM_OK) return s;
-    const double bnorm = std::sqrt(bn2);
+    SCHK(c, mark(c, 1, false));
     const int R = c->p.gmres_restart;
     int it = 0;
     double rel = 0.0;
-    bool conv = false;
-    if (bnorm == 0.0) {
-        SCHK(c, hipMemsetAsync(c->x, 0, size_t(D) * sizeof(double), c->st));
-        conv = true;
-    }
+    bool conv = false, restart = false;
     while (!conv && it < c->p.gmres_maxit) {
+        if (restart) {
+            SCHK(c, mark(c, 1, true));
+            SCHK(c, product(c, c->x));
+            hipLaunchKernelGGL(k_rows, gg, b4, 0, c->st, c->part, c->zx, D, c->c.nt);
+            SCHK(c, hipGetLastError());
+            SCHK(c, mark(c, 1, false));
+        }
+        restart = true;
         // r = b - A x, V_0 = r/|r|, g = (|r|, 0, ...)
-        SCHK(c, apply(c, c->x, c->y));
-        hipLaunchKernelGGL(k_residual, dim3(gd), dim3(256), 0, c->st, c->b, c->y, c->r, D);
+        hipLaunchKernelGGL(k_start, gg, dim3(GT), 0, c->st, c->z0, c->x, c->zx, c->pd, c->Mt, c->r, dp[0], G, c->c);
+        hipLaunchKernelGGL(k_first, ge, b256, 0, c->st, c->r, c->Vb, c->t, c->pd, dp[0], c->g, norms, G, c->c);
         SCHK(c, hipGetLastError());
-        SCHK(c, dot_self(c, c->r));
-        hipLaunchKernelGGL(k_gstart, dim3(1), dim3(64), 0, c->st, c->g, c->nrm, c->res);
-        hipLaunchKernelGGL(k_normalize, dim3(gd), dim3(256), 0, c->st, c->r, c->Vb, c->nrm, D);
-        SCHK(c, hipGetLastError());
-        double r0 = 0.0;
-        if ((s = read_scalar(c, c->res, &r0)) != LBM_OK) return s;
-        rel = r0 / bnorm;
+        SCHK(c, hipStreamSynchronize(c->st));
+        SCHK(c, collect(c));
+        const double bnorm = norms[0];
+        if (bnorm == 0.0) {
+            SCHK(c, hipMemsetAsync(c->x, 0, size_t(D) * sizeof(double), c->st));
+            SCHK(c, hipMemsetAsync(c->zx, 0, size_t(D) * sizeof(double), c->st));
+            rel = 0.0;
+            conv = true;
+            break;
+        }
+        rel = norms[1] / bnorm;
         if (rel <= c->p.gmres_tol) {
             conv = true;
             break;
         }
         int k = 0;
         for (int i = 0; i < R && it < c->p.gmres_maxit; ++i) {
-            double *vi = c->Vb + size_t(i) * D, *vn = c->Vb + size_t(i + 1) * D;
-            SCHK(c, precond(c, vi, c->t));
-            SCHK(c, apply(c, c->t, c->w));
+            SCHK(c, mark(c, 1, true));
+            SCHK(c, product(c, c->t));
+            hipLaunchKernelGGL(k_apply_dots, gg, b4, 0, c->st, c->part, c->t, c->pd, c->Vb, c->Zb + size_t(i) * D, c->w,
+                               dp[0], i + 1, G, c->c);
+            SCHK(c, hipGetLastError());
+            SCHK(c, mark(c, 1, false));
             // classical Gram-Schmidt, twice
-            SCHK(c, dots(c, c->Vb, c->w, c->h1, i + 1));
-            hipLaunchKernelGGL(k_orth, dim3(gd), dim3(256), 0, c->st, c->Vb, c->w, c->h1, i + 1, D);
-            SCHK(c, dots(c, c->Vb, c->w, c->h2, i + 1));
-            hipLaunchKernelGGL(k_orth, dim3(gd), dim3(256), 0, c->st, c->Vb, c->w, c->h2, i + 1, D);
+            hipLaunchKernelGGL(k_orth, gg, b256, 0, c->st, c->Vb, c->w, dp[0], dp[1], c->h1, i + 1, G, D, 0);
+            hipLaunchKernelGGL(k_orth, gg, b256, 0, c->st, c->Vb, c->w, dp[1], dp[2], c->h2, i + 1, G, D, 1);
+            hipLaunchKernelGGL(k_next, ge, b256, 0, c->st, c->w, c->Vb + size_t(i + 1) * D, c->t, c->pd, dp[2], c->H,
+                               c->h1, c->h2, c->cs, c->sn, c->g, c->resh, i, G, c->c);
             SCHK(c, hipGetLastError());
-            SCHK(c, dot_self(c, c->w));
-            hipLaunchKernelGGL(k_hcol, dim3(1), dim3(64), 0, c->st, c->H, c->h1, c->h2, c->nrm, c->cs, c->sn, c->g,
-                               c->res, i);
-            hipLaunchKernelGGL(k_normalize, dim3(gd), dim3(256), 0, c->st, c->w, vn, c->nrm, D);
-            SCHK(c, hipGetLastError());
-            // the residual of this iteration to pinned host memory; the host
-            // tests the previous iteration's while this one runs, so the
-            // stream never drains for the test (at most one iteration more
-            // than needed, which only lowers the residual)
-            SCHK(c, hipMemcpyAsync(c->resh + i, c->res, sizeof(double), hipMemcpyDeviceToHost, c->st));
+            // the host tests the previous iteration's residual while this
+            // one runs, so the stream never drains for the test (at most one
+            // iteration more than needed, which only lowers the residual)
             SCHK(c, hipEventRecord(c->rev[i], c->st));
             ++it;
             k = i + 1;
@@ -957,26 +1111,86 @@ static lbm_status do_solve(sbf_ctx *c)
             rel = c->resh[k - 1] / bnorm;
             conv = rel <= c->p.gmres_tol;
         }
-        // x += B^-1 sum_j y_j V_j
         hipLaunchKernelGGL(k_backsolve, dim3(1), dim3(64), 0, c->st, c->H, c->g, c->ys, k);
-        hipLaunchKernelGGL(k_lincomb, dim3(gd), dim3(256), 0, c->st, c->t, c->Vb, c->ys, k, D);
-        SCHK(c, hipGetLastError());
-        SCHK(c, precond(c, c->t, c->u));
-        hipLaunchKernelGGL(k_add, dim3(gd), dim3(256), 0, c->st, c->x, c->u, c->x, D);
+        hipLaunchKernelGGL(k_update, ge, b256, 0, c->st, c->x, c->zx, c->Vb, c->Zb, c->ys, c->pd, k, c->c);
         SCHK(c, hipGetLastError());
     }
-    // velocities from W [F/(2l); a]: x (zero k = 0 entries) plus the known part
-    hipLaunchKernelGGL(k_known, dim3(gd), dim3(256), 0, c->st, c->kn, c->F, c->c);
-    hipLaunchKernelGGL(k_add, dim3(gd), dim3(256), 0, c->st, c->x, c->kn, c->y, D);
-    SCHK(c, hipGetLastError());
-    SCHK(c, gemv(c, c->y, c->z));
-    hipLaunchKernelGGL(k_velocity, dim3(nblk(size_t(c->M))), dim3(256), 0, c->st, c->z, c->pd, c->F, c->Mt, c->V,
+    hipLaunchKernelGGL(k_velocity, dim3(nblk(size_t(c->M))), b256, 0, c->st, c->z0, c->zx, c->pd, c->F, c->Mt, c->V,
                        c->Pd, c->c);
     SCHK(c, hipGetLastError());
     c->iters = it;
     c->relres = rel;
     c->solved = true;
     return conv ? LBM_OK : sfail(c, LBM_E_UNSTABLE, "GMRES did not reach the tolerance");
+}
+
+// Whether the one-workgroup form takes this system: matrix, basis and
+// vectors fit the LDS of one CU (with the event timing off, which brackets
+// single kernels).  M = 2, N = 5: 0.55 ms per step with a launch for each kernel,
+// 0.050 ms in one.
+static bool small_form(const sbf_ctx *c)
+{
+    return !c->timing && small_lds(c->M, c->c.N + 1, c->c.Q, c->p.gmres_restart) <= SMALL_LDS;
+}
+
+template <int NP1>
+static hipError_t small_t(sbf_ctx *c, const SmallArgs &a)
+{
+    const size_t lds = small_lds(c->M, NP1, c->c.Q, c->p.gmres_restart);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_small<NP1>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_small<NP1>), dim3(1), dim3(SMALL_T), lds, c->st, a);
+    return hipGetLastError();
+}
+
+// n time steps (n = 0: one solve without moving the fibers) in one launch
+static lbm_status do_small(sbf_ctx *c, int n, double dt)
+{
+    SmallArgs a{};
+    a.c = c->c;
+    a.X = c->X;
+    a.p = c->pd;
+    a.F = c->F;
+    a.Mt = c->Mt;
+    a.x = c->x;
+    a.xh = c->xh;
+    a.V = c->V;
+    a.Pd = c->Pd;
+    a.Vp = c->Vp;
+    a.Pp = c->Pp;
+    a.wj = c->wj;
+    a.out = c->small;
+    a.tol = c->p.gmres_tol;
+    a.dt = dt;
+    a.restart = c->p.gmres_restart;
+    a.maxit = c->p.gmres_maxit;
+    a.nsteps = n;
+    a.nsol = c->nsol;
+    a.first = c->first ? 1 : 0;
+    hipError_t e = hipSuccess;
+    switch (c->c.N + 1) {
+    case 2: e = small_t<2>(c, a); break;
+    case 3: e = small_t<3>(c, a); break;
+    case 4: e = small_t<4>(c, a); break;
+    case 5: e = small_t<5>(c, a); break;
+    case 6: e = small_t<6>(c, a); break;
+    case 7: e = small_t<7>(c, a); break;
+    case 8: e = small_t<8>(c, a); break;
+    default: e = small_t<9>(c, a); break;
+    }
+    SCHK(c, e);
+    SCHK(c, hipStreamSynchronize(c->st));
+    const SmallResult r = *c->small;
+    c->iters = r.iters;
+    c->relres = r.relres;
+    c->solved = true;
+    if (r.steps > 0) {
+        c->first = false;
+        c->steps += r.steps;
+        c->nsol += r.steps;
+    }
+    return r.converged ? LBM_OK : sfail(c, LBM_E_UNSTABLE, "GMRES did not reach the tolerance");
 }
 
 // ====================================================================== ABI
@@ -991,9 +1205,9 @@ static void release(sbf_ctx *c)
 {
     for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
     c->ev.clear();
-    double **bufs[] = {&c->X, &c->pd, &c->F, &c->Mt, &c->sq, &c->wl, &c->W, &c->part, &c->dpart, &c->x, &c->xh, &c->b, &c->r,
-                       &c->w, &c->y, &c->kn, &c->z, &c->t, &c->u, &c->Vb, &c->H, &c->cs, &c->sn, &c->g, &c->h1, &c->h2,
-                       &c->ys, &c->nrm, &c->res, &c->V, &c->Pd, &c->Vp, &c->Pp};
+    double **bufs[] = {&c->X, &c->pd, &c->F, &c->Mt, &c->wl, &c->wj, &c->W, &c->part, &c->part2, &c->dpart, &c->x,
+                       &c->xh, &c->r, &c->w, &c->kn, &c->z0, &c->zx, &c->t, &c->Vb, &c->Zb, &c->H, &c->cs, &c->sn,
+                       &c->g, &c->h1, &c->h2, &c->ys, &c->V, &c->Pd, &c->Vp, &c->Pp};
     for (double **b : bufs)
         if (*b) {
             (void)hipFree(*b);
@@ -1006,6 +1220,10 @@ static void release(sbf_ctx *c)
     if (c->resh) {
         (void)hipHostFree(c->resh);
         c->resh = nullptr;
+    }
+    if (c->small) {
+        (void)hipHostFree(c->small);
+        c->small = nullptr;
     }
     for (hipEvent_t &e : c->rev)
         if (e) {
@@ -1079,20 +1297,22 @@ lbm_status sbf_create(const sbf_params *p, sbf_ctx **out)
     A(&c->Pd, 3 * size_t(Mx));
     A(&c->Vp, 3 * size_t(Mx));
     A(&c->Pp, 3 * size_t(Mx));
-    A(&c->sq, size_t(Q));
-    A(&c->wl, size_t(Q) * (N + 1));
+    A(&c->wl, size_t(Q) * (N + 3));
+    A(&c->wj, size_t(Q) * (N + 4));
     A(&c->W, packed_tiles(ntm) * TS * TS);
     A(&c->part, size_t(ntm) * size_t(ntm) * TS);
-    A(&c->dpart, size_t(MAXR) * DP);
+    A(&c->part2, size_t(ntm) * size_t(ntm) * TS);
+    c->gmax = (c->Dmax + GR - 1) / GR;
+    A(&c->dpart, 3 * size_t(MAXR + 1) * size_t(c->gmax));
     if (e == hipSuccess) e = hipMalloc((void **)&c->chunks, std::max<size_t>(symv_chunk_count(ntm), 1) * sizeof(int4));
-    if (e == hipSuccess) e = hipHostMalloc((void **)&c->resh, MAXR * sizeof(double), hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostMalloc((void **)&c->resh, (MAXR + 2) * sizeof(double), hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostMalloc((void **)&c->small, sizeof(SmallResult), hipHostMallocDefault);
     for (int i = 0; i < MAXR && e == hipSuccess; ++i) e = hipEventCreateWithFlags(&c->rev[i], hipEventDisableTiming);
-    for (double **v : {&c->x, &c->xh, &c->b, &c->r, &c->w, &c->y, &c->kn, &c->z, &c->t, &c->u}) A(v, Dm);
+    for (double **v : {&c->x, &c->xh, &c->r, &c->w, &c->kn, &c->z0, &c->zx, &c->t}) A(v, Dm);
     A(&c->Vb, Dm * size_t(R + 1));
+    A(&c->Zb, Dm * size_t(R));
     A(&c->H, size_t(MAXR) * MAXR);
     for (double **v : {&c->cs, &c->sn, &c->g, &c->h1, &c->h2, &c->ys}) A(v, size_t(MAXR + 1));
-    A(&c->nrm, 1);
-    A(&c->res, 1);
     if (e != hipSuccess) {
         release(c);
         if (c->own_stream) (void)hipStreamDestroy(c->st);
@@ -1101,7 +1321,7 @@ lbm_status sbf_create(const sbf_params *p, sbf_ctx **out)
     }
     // composite three-point Gauss rule on [-l, l] (nodes +-sqrt(3/5), 0;
     // weights 5/9, 8/9, 5/9 on each sub-interval) and P_0..P_N at its nodes
-    std::vector<double> sq(Q), wq(Q), leg(size_t(Q) * (N + 1));
+    std::vector<double> sq(Q), wq(Q), leg(size_t(Q) * (N + 3));
     const double gn[3] = {-std::sqrt(0.6), 0.0, std::sqrt(0.6)}, gw[3] = {5.0 / 9.0, 8.0 / 9.0, 5.0 / 9.0};
     const double hstep = 2.0 / p->nq;
     for (int i = 0; i < p->nq; ++i)
@@ -1113,7 +1333,7 @@ lbm_status sbf_create(const sbf_params *p, sbf_ctx **out)
             double p0 = 1.0, p1 = t;
             leg[j] = 1.0;
             if (N >= 1) leg[size_t(Q) + j] = t;
-            for (int n = 1; n < N; ++n) {
+            for (int n = 1; n < N + 2; ++n) {
                 const double p2 = ((2 * n + 1) * t * p1 - n * p0) / (n + 1);
                 leg[size_t(n + 1) * Q + j] = p2;
                 p0 = p1;
@@ -1121,9 +1341,14 @@ lbm_status sbf_create(const sbf_params *p, sbf_ctx **out)
             }
         }
     std::vector<double> wl(leg.size());
-    for (int k = 0; k <= N; ++k)
+    for (int k = 0; k <= N + 2; ++k)
         for (int j = 0; j < Q; ++j) wl[size_t(k) * Q + j] = wq[j] * leg[size_t(k) * Q + j];
-    if (hipMemcpyAsync(c->sq, sq.data(), Q * sizeof(double), hipMemcpyHostToDevice, c->st) != hipSuccess ||
+    std::vector<double> wj(size_t(Q) * (N + 4));
+    for (int j = 0; j < Q; ++j) {
+        wj[size_t(j) * (N + 4)] = sq[j];
+        for (int k = 0; k <= N + 2; ++k) wj[size_t(j) * (N + 4) + 1 + k] = wl[size_t(k) * Q + j];
+    }
+    if (hipMemcpyAsync(c->wj, wj.data(), wj.size() * sizeof(double), hipMemcpyHostToDevice, c->st) != hipSuccess ||
         hipMemcpyAsync(c->wl, wl.data(), wl.size() * sizeof(double), hipMemcpyHostToDevice, c->st) != hipSuccess ||
         hipStreamSynchronize(c->st) != hipSuccess) {
         release(c);
@@ -1173,6 +1398,8 @@ lbm_status sbf_set_fibers(sbf_ctx *c, int32_t m, const double *X, const double *
     const std::vector<int4> chunks = symv_chunks(c->c.nt);
     c->nchunks = unsigned(chunks.size());
     SCHK(c, hipMemcpyAsync(c->chunks, chunks.data(), chunks.size() * sizeof(int4), hipMemcpyHostToDevice, c->st));
+    hipLaunchKernelGGL(k_known, dim3(nblk(size_t(c->c.D))), dim3(256), 0, c->st, c->kn, c->F, c->c);
+    SCHK(c, hipGetLastError());
     SCHK(c, hipStreamSynchronize(c->st));
     c->first = true;
     c->solved = false;
@@ -1185,7 +1412,7 @@ lbm_status sbf_solve(sbf_ctx *c)
 {
     if (!c) return LBM_E_ARG;
     if (c->M < 1) return sfail(c, LBM_E_STATE, "sbf_solve: no fibers set");
-    return do_solve(c);
+    return small_form(c) ? do_small(c, 0, 0.0) : do_solve(c);
 }
 
 lbm_status sbf_get_velocities(sbf_ctx *c, double *V, double *pdot)
@@ -1218,7 +1445,14 @@ lbm_status sbf_step(sbf_ctx *c, int64_t n, double dt)
     if (!c) return LBM_E_ARG;
     if (n < 0 || !(dt > 0.0)) return sfail(c, LBM_E_ARG, "sbf_step: n >= 0 and dt > 0 required");
     if (c->M < 1) return sfail(c, LBM_E_STATE, "sbf_step: no fibers set");
-    for (int64_t s = 0; s < n; ++s) {
+    if (small_form(c)) {
+        for (int64_t left = n; left > 0;) {
+            const int k = int(std::min<int64_t>(left, SMALL_STEPS));
+            const lbm_status st = do_small(c, k, dt);
+            if (st != LBM_OK) return st;
+            left -= k;
+        }
+    } else for (int64_t s = 0; s < n; ++s) {
         // GMRES starts from the extrapolation of the last two solutions
         // (from the last one after the first step)
         const unsigned gd = nblk(size_t(c->c.D));
