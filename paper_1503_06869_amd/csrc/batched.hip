@@ -37,16 +37,6 @@ namespace lbm {
 
 constexpr int BMAXP = 512;   // planes of a case (nz <= 512)
 
-struct CaseDev {
-    Geo g;
-    Phys<float> pf;
-    Phys<double> pd;
-    uint64_t f_off;      // first population element of the case
-    uint64_t cell_off;   // first element of its cell arrays (flags, pid)
-    uint32_t list_off, list_cap;
-    PConst pc;
-};
-
 struct BatchDev {
     const CaseDev *cases;
     const int32_t *bin_case;   // case ids of all bins, concatenated
@@ -417,6 +407,7 @@ struct lbm_batch {
     double *ft = nullptr, *hist = nullptr, *traj = nullptr;
     int64_t *steps_d = nullptr, *traj_pos = nullptr;
     DevCounters *ctr = nullptr;
+    float *feat = nullptr;                   // features of all cases on their way to the host
     uint64_t nf = 0, ncells = 0;
     uint64_t nlist = 0;
     int64_t steps = 0;
@@ -687,6 +678,7 @@ lbm_status lbm_batch_destroy(lbm_batch *b)
     bfree(b->steps_d);
     bfree(b->traj_pos);
     bfree(b->ctr);
+    bfree(b->feat);
     if (b->own_stream && b->st) hipStreamDestroy(b->st);
     delete b;
     return LBM_OK;
@@ -1092,22 +1084,12 @@ lbm_status lbm_batch_sample_features(lbm_batch *b, float *out, int32_t dst_is_de
     for (int i = 0; i < b->ncase; ++i)
         if (b->hc[i].wall_u == 0.0) return bfail(b, LBM_E_ARG, "features need U != 0 in every case");
     const size_t n = size_t(b->ncase) * LBM_MLP_IN;
-    float *d = out;
-    if (!dst_is_device) BHIP(b, hipMalloc(&d, n * sizeof(float)));
-    hipError_t e = hipSuccess;
-    for (int i = 0; i < b->ncase && e == hipSuccess; ++i) {
-        const CaseDev &cd = b->hcd[i];
-        const void *fc = static_cast<const char *>(b->f) + cd.f_off * b->esz;
-        const PState *ps = b->ps + size_t(i) * 2 + size_t(b->steps & 1);
-        const PConst *pc = &b->cases[i].pc;
-        const double gamma = 2.0 * b->hc[i].wall_u / b->hc[i].nz;
-        e = launch_sample_features(b->sk, (b->steps & 1) != 0, fc, b->flags + cd.cell_off, b->pid + cd.cell_off,
-                                   ps, pc, 1, cd.g, cd.pd, gamma, d + size_t(i) * LBM_MLP_IN, b->st);
-    }
-    if (e == hipSuccess && !dst_is_device) e = hipMemcpyAsync(out, d, n * sizeof(float), hipMemcpyDeviceToHost, b->st);
-    if (e == hipSuccess) e = hipStreamSynchronize(b->st);
-    if (!dst_is_device) hipFree(d);
-    if (e != hipSuccess) return bfail(b, LBM_E_HIP, hipGetErrorString(e));
+    if (!dst_is_device && !b->feat) BHIP(b, balloc(b, &b->feat, n));
+    float *d = dst_is_device ? out : b->feat;
+    BHIP(b, launch_sample_features_batch(b->sk, (b->steps & 1) != 0, b->f, b->flags, b->pid, b->ps, int(b->steps & 1),
+                                         b->cases, b->ncase, d, b->st));
+    if (!dst_is_device) BHIP(b, hipMemcpyAsync(out, d, n * sizeof(float), hipMemcpyDeviceToHost, b->st));
+    BHIP(b, hipStreamSynchronize(b->st));
     return LBM_OK;
 }
 

@@ -37,16 +37,18 @@ __device__ __forceinline__ void cell_velocity(const S *__restrict__ f, const uin
     const uint32_t cell = (z * g.ny + y) * g.nx + x;
     const uint8_t fl = flags[cell];
     const int32_t own = pid[cell];
+    // neighbour coordinates as offsets (wrapped; ghost planes at z walls)
+    const uint32_t xs[3] = {x == 0 ? g.nx - 1 : x - 1, x, x + 1 == g.nx ? 0 : x + 1};
+    const uint32_t ys[3] = {(y == 0 ? g.ny - 1 : y - 1) * g.nx, y * g.nx, (y + 1 == g.ny ? 0 : y + 1) * g.nx};
+    const uint32_t zs[3] = {(g.zper && z == 0 ? g.nz : z) * g.nxy, (z + 1) * g.nxy,
+                            (g.zper && z + 1 == g.nz ? 1 : z + 2) * g.nxy};
     R fv[Q];
 #pragma unroll
     for (int q = 1; q < Q; ++q) {
         uint32_t src = (z + 1) * g.nxy + y * g.nx + x;
         int qq = q;
         if (swapped) {
-            const uint32_t sx = (x + g.nx - CX[q]) % g.nx, sy = (y + g.ny - CY[q]) % g.ny;
-            const int32_t szi = int32_t(z) - CZ[q];
-            const uint32_t szs = g.zper ? uint32_t((szi + int32_t(g.nz)) % int32_t(g.nz)) + 1 : uint32_t(szi + 1);
-            src = szs * g.nxy + sy * g.nx + sx;
+            src = zs[1 - CZ[q]] + ys[1 - CY[q]] + xs[1 - CX[q]];
             qq = opp(q);
         }
         fv[q] = St<S>::ld(f, uint64_t(qq) * g.qstride + src, R(ph.inv_scale));
@@ -146,7 +148,8 @@ __device__ void features_block(const S *__restrict__ f, const uint8_t *__restric
         for (int e = 0; e < 3; ++e) sh.x[k * 3 + e] = float((Rm[0][e] * v[0] + Rm[1][e] * v[1] + Rm[2][e] * v[2]) * vs);
     } else if (k < NPT + 4) {
         const double sg = s.q[0] < 0.0 ? -1.0 : 1.0;
-        sh.x[3 * NPT + (k - NPT)] = float(sg * s.q[k - NPT]);
+        const int e = k - NPT;   // selected, not indexed: the state stays in registers
+        sh.x[3 * NPT + e] = float(sg * (e == 0 ? s.q[0] : (e == 1 ? s.q[1] : (e == 2 ? s.q[2] : s.q[3]))));
     }
     __syncthreads();
 }
@@ -163,14 +166,45 @@ __global__ __launch_bounds__(FB) void k_features(const S *__restrict__ f, const 
     for (int i = threadIdx.x; i < NI; i += FB) out[size_t(p) * NI + i] = sh.x[i];
 }
 
-// sum over the 64 lanes of a wave; every lane ends with the same value (the
-// butterfly pairs each sum with its operands swapped, and FP addition is
-// commutative), so the result does not depend on the lane read
-__device__ __forceinline__ float wave_sum(float v)
+// One launch for all cases of the batched form, a workgroup per case (each
+// fiber's stencil is latency bound: 15 us for one case, 45 us for 512, against
+// 512 launches of 15 us).
+template <typename S>
+__global__ __launch_bounds__(FB) void k_features_batch(const S *__restrict__ f, const uint8_t *__restrict__ flags,
+                                                       const int32_t *__restrict__ pid, const PState *__restrict__ ps,
+                                                       int slot, const CaseDev *__restrict__ cases, int swapped,
+                                                       float *__restrict__ out)
 {
+    __shared__ FeatStage sh;
+    const int c = blockIdx.x;
+    const CaseDev cd = uniform(cases[c]);
+    const double gamma = 2.0 * cd.pd.wall_u / double(cd.g.nz);
+    features_block<S>(f + cd.f_off, flags + cd.cell_off, pid + cd.cell_off, ps + size_t(c) * 2 + slot, &cases[c].pc,
+                      cd.g, cd.pd, swapped, gamma, 0, sh);
+    for (int i = threadIdx.x; i < NI; i += FB) out[size_t(c) * NI + i] = sh.x[i];
+}
+
+// Sums over the lower 32 lanes of 16 values per lane: four steps halve the
+// values held while pairing lanes 16, 8, 4 and 2 apart, one adds the last pair.
+// Lane l < 32 returns the total of value 8 b4 + 4 b3 + 2 b2 + b1 (b: bits of
+// l).  One such tree takes the latency of a single sum.
+template <int H>
+__device__ __forceinline__ void halve_f(float (&v)[16])
+{
+    const bool up = (threadIdx.x & (2 * H)) != 0;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    for (int k = 0; k < H; ++k) {
+        const float send = up ? v[k] : v[k + H], keep = up ? v[k + H] : v[k];
+        v[k] = keep + __shfl_xor(send, 2 * H, 64);
+    }
+}
+__device__ __forceinline__ float half_wave_sums(float (&v)[16])
+{
+    halve_f<8>(v);
+    halve_f<4>(v);
+    halve_f<2>(v);
+    halve_f<1>(v);
+    return v[0] + __shfl_xor(v[0], 1, 64);
 }
 
 // One step's closure for fiber p: features, then the network on this one
@@ -201,30 +235,41 @@ __global__ __launch_bounds__(FB) void k_closure_step(const S *__restrict__ f, co
     __syncthreads();
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const uint16_t *wb = m.wb;
+    const int unit = ((lane >> 4) & 1) * 8 + ((lane >> 3) & 1) * 4 + ((lane >> 2) & 1) * 2 + ((lane >> 1) & 1);
+    const bool writer = lane < 32 && (lane & 1) == 0;
+    float a[16];
     // layer 1: 247 inputs, lane l takes inputs l, l + 64, l + 128, l + 192
+#pragma unroll
     for (int u = 0; u < 16; ++u) {
-        const int j = w * 16 + u;
-        float a = 0.0f;
+        float v = 0.0f;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int i = lane + 64 * r;
-            if (i < NI) a = fmaf(bf(wb[OW1 + j * NI + i]), s_xn[i], a);
+            if (i < NI) v = fmaf(bf(wb[OW1 + (w * 16 + u) * NI + i]), s_xn[i], v);
         }
-        a = wave_sum(a);
-        if (lane == 0) s_h1[j] = gelu(a + bf(wb[OB1 + j]));
+        a[u] = v + __shfl_xor(v, 32, 64);
     }
+    const float z1 = half_wave_sums(a);
+    if (writer) s_h1[w * 16 + unit] = gelu(z1 + bf(wb[OB1 + w * 16 + unit]));
     __syncthreads();
+    // layers 2 and 3: the product of the lower lane of a first pair is added
+    // unrounded
+#pragma unroll
     for (int u = 0; u < 16; ++u) {
-        const int j = w * 16 + u;
-        const float a = wave_sum(bf(wb[OW2 + j * NH + lane]) * s_h1[lane]);
-        if (lane == 0) s_h2[j] = gelu(a + bf(wb[OB2 + j]));
+        const float wt = bf(wb[OW2 + (w * 16 + u) * NH + lane]), h = s_h1[lane];
+        a[u] = fmaf(wt, h, __shfl_xor(wt * h, 32, 64));
     }
+    const float z2 = half_wave_sums(a);
+    if (writer) s_h2[w * 16 + unit] = gelu(z2 + bf(wb[OB2 + w * 16 + unit]));
     __syncthreads();
     if (w == 0) {
-        for (int o = 0; o < NO; ++o) {
-            const float a = wave_sum(bf(wb[OW3 + o * NH + lane]) * s_h2[lane]);
-            if (lane == 0) s_y[o] = (a + bf(wb[OB3 + o])) * m.out_scale[o];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            const float wt = u < NO ? bf(wb[OW3 + (u < NO ? u : 0) * NH + lane]) : 0.0f, h = s_h2[lane];
+            a[u] = fmaf(wt, h, __shfl_xor(wt * h, 32, 64));
         }
+        const float z3 = half_wave_sums(a);
+        if (writer && unit < NO) s_y[unit] = (z3 + bf(wb[OB3 + unit])) * m.out_scale[unit];
     }
     __syncthreads();
     if (threadIdx.x < NO) {
@@ -235,7 +280,10 @@ __global__ __launch_bounds__(FB) void k_closure_step(const S *__restrict__ f, co
         const double L = pc[p].length;
         const double sF = rho0 * nu * gamma * L * L, sc = part == 0 ? sF : sF * L;
         const float *yp = s_y + 3 * part;
-        const double lab = Rm[row][0] * yp[0] + Rm[row][1] * yp[1] + Rm[row][2] * yp[2];
+        double rr[3];
+#pragma unroll
+        for (int e = 0; e < 3; ++e) rr[e] = row == 0 ? Rm[0][e] : (row == 1 ? Rm[1][e] : Rm[2][e]);
+        const double lab = rr[0] * yp[0] + rr[1] * yp[1] + rr[2] * yp[2];
         corr[size_t(p) * NO + o] = s_out ? 0.0 : lab * sc;
     }
     if (threadIdx.x == 0) atomicAdd(&stats[s_out ? 1 : 0], 1ull);
@@ -252,6 +300,21 @@ hipError_t launch_sample_features(int sk, bool swapped, const void *f, const uin
     case S_F16: hipLaunchKernelGGL(k_features<_Float16>, dim3(np), dim3(FB), 0, st, (const _Float16 *)f, flags, pid, ps, pc, g, ph, sw, gamma, out); break;
     case S_BF16: hipLaunchKernelGGL(k_features<bf16s>, dim3(np), dim3(FB), 0, st, (const bf16s *)f, flags, pid, ps, pc, g, ph, sw, gamma, out); break;
     default: hipLaunchKernelGGL(k_features<double>, dim3(np), dim3(FB), 0, st, (const double *)f, flags, pid, ps, pc, g, ph, sw, gamma, out); break;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_sample_features_batch(int sk, bool swapped, const void *f, const uint8_t *flags, const int32_t *pid,
+                                        const PState *ps, int slot, const CaseDev *cases, int ncase, float *out,
+                                        hipStream_t st)
+{
+    if (ncase <= 0) return hipSuccess;
+    const int sw = swapped ? 1 : 0;
+    switch (sk) {
+    case S_F32: hipLaunchKernelGGL(k_features_batch<float>, dim3(ncase), dim3(FB), 0, st, (const float *)f, flags, pid, ps, slot, cases, sw, out); break;
+    case S_F16: hipLaunchKernelGGL(k_features_batch<_Float16>, dim3(ncase), dim3(FB), 0, st, (const _Float16 *)f, flags, pid, ps, slot, cases, sw, out); break;
+    case S_BF16: hipLaunchKernelGGL(k_features_batch<bf16s>, dim3(ncase), dim3(FB), 0, st, (const bf16s *)f, flags, pid, ps, slot, cases, sw, out); break;
+    default: hipLaunchKernelGGL(k_features_batch<double>, dim3(ncase), dim3(FB), 0, st, (const double *)f, flags, pid, ps, slot, cases, sw, out); break;
     }
     return hipGetLastError();
 }

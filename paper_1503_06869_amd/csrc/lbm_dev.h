@@ -227,6 +227,17 @@ struct PartData {
     double contact_range;      // gap below which it acts
 };
 
+// one case of the batched form
+struct CaseDev {
+    Geo g;
+    Phys<float> pf;
+    Phys<double> pd;
+    uint64_t f_off;      // first population element of the case
+    uint64_t cell_off;   // first element of its cell arrays (flags, pid)
+    uint32_t list_off, list_cap;
+    PConst pc;
+};
+
 // ---------------------------------------------------------------------------
 // Launch wrappers (defined in sweep.hip / particles.hip)
 // ---------------------------------------------------------------------------
@@ -300,5 +311,11 @@ hipError_t launch_closure_step(int sk, bool swapped, const void *f, const uint8_
 hipError_t launch_sample_features(int sk, bool swapped, const void *f, const uint8_t *flags, const int32_t *pid,
                                   const PState *ps, const PConst *pc, int np, const Geo &g,
                                   const Phys<double> &ph, double gamma, float *out, hipStream_t st);
+
+// features [ncase][247] of the batched form's cases, whose states are
+// ps[2 c + slot], one launch
+hipError_t launch_sample_features_batch(int sk, bool swapped, const void *f, const uint8_t *flags, const int32_t *pid,
+                                        const PState *ps, int slot, const CaseDev *cases, int ncase, float *out,
+                                        hipStream_t st);
 
 }  // namespace lbm
