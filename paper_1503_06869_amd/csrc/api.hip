@@ -325,10 +325,9 @@ static lbm_status setup_mapping(lbm_ctx *c, PState *old_states)
     PState *cur = c->ps[c->steps & 1];
     PartData pd = part_data(c, old_states ? old_states : cur, cur);
     HIPCHK(c, launch_setup_boxes(pd, c->g, c->st));
-    HIPCHK(c, launch_remap(c->sk, (c->steps & 1) != 0, c->f, c->pid, pd, c->g, c->p.rho0, c->scale,
-                           c->st));
     const int s = int(c->steps & 1);
-    HIPCHK(c, launch_near(c->flags[s], c->pid, c->list_cell, c->list_mask, pd, c->g, c->st));
+    HIPCHK(c, launch_map(c->sk, s != 0, c->f, c->pid, c->flags[s], c->list_cell, c->list_mask, pd, c->g, c->p.rho0,
+                         c->scale, false, c->st));
     // the other flag buffer and pose buffer start as copies of the current
     // ones: the first step writes its successor flags over the region of
     // this pose, which then covers every flag the buffer holds
@@ -358,11 +357,10 @@ static lbm_status check_device_errors(lbm_ctx *c)
 
 // One time step as a two-branch graph of kernels:
 //   st : bulk sweep -----------------------------------------------------------+
-//   st2: boundary cells (F0, M0) + A, B, C sums -> rigid -> remap -> near/list -+--> next step
+//   st2: boundary cells and their links' sums -> rigid -> map and list ---------+--> next step
 // The bulk sweep touches only slots of bulk cells; the boundary update, the
 // refill of the remap and the momentum exchange touch only slots and data
-// of cells next to fibers, so the branches are independent; the sums A, B, C
-// read only the list, the cell owners and the poses.  The bulk sweep of step
+// of cells next to fibers, so the branches are independent.  The bulk sweep of step
 // n reads flags[n & 1]; the flag and list rebuild writes the flags of step
 // n + 1 into flags[(n + 1) & 1], over the remap region of the previous,
 // current and new poses, which holds every cell whose flag differs between
@@ -431,9 +429,9 @@ static void launch_one_step(lbm_ctx *c, int64_t step_index, bool with_events, hi
         pd.cov_cap = c->cov_cap;
     }
     if (e == hipSuccess) e = launch_rigid(pd, c->g, c->st2);
-    if (e == hipSuccess) e = launch_remap(c->sk, !odd, c->f, c->pid, pd, c->g, c->p.rho0, c->scale, c->st2);
     if (e == hipSuccess)
-        e = launch_near(c->flags[(step_index + 1) & 1], c->pid, c->list_cell, c->list_mask, pd, c->g, c->st2);
+        e = launch_map(c->sk, !odd, c->f, c->pid, c->flags[(step_index + 1) & 1], c->list_cell, c->list_mask, pd, c->g,
+                       c->p.rho0, c->scale, true, c->st2);
     if (e == hipSuccess) e = hipEventRecord(c->ev_join, c->st2);
     if (e == hipSuccess) e = hipStreamWaitEvent(c->st, c->ev_join, 0);
     if (e == hipSuccess && stab)

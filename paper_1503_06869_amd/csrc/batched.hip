@@ -63,6 +63,7 @@ template <int BS>
 struct BShared {
     long long red[BS / 64][NACC];
     long long tot[NACC];
+    double ac[NACC];
     PState cur, nxt;
     Box ub;
     Rect rect[BMAXP];
@@ -161,41 +162,52 @@ __device__ __forceinline__ void case_particles(const BatchDev &bd, int c, const 
     using R = typename St<S>::R;
     const Geo &g = cd.g;
     const int cur = int(s & 1), nxt = setup ? cur : int((s + 1) & 1);
-    if (threadIdx.x == 0) {
-        const PState so = bd.ps[size_t(c) * 2 + cur];
+    if (threadIdx.x < 64) {
+        // one wave: every lane carries the rigid update, lane 0 writes
+        const int lane = int(threadIdx.x);
+        const PState so = uniform(bd.ps[size_t(c) * 2 + cur]);
         PState o = so;
         if (!setup) {
-            double ac[NACC];
-            for (int k = 0; k < 6; ++k) ac[k] = ldexp(double(sh.tot[k]), -fx_shift(k));
-            for (int k = 6; k < NACC; ++k) ac[k] = double(bd.abc[size_t(c) * NABC + k - 6]);
-            abc_restore(ac, so.X, double(case_phys<R>(cd).rho0));
+            if (lane < NACC)
+                sh.ac[lane] = lane < 6 ? ldexp(double(sh.tot[lane]), -fx_shift(lane))
+                                       : double(bd.abc[size_t(c) * NABC + (lane < 6 ? 0 : lane - 6)]);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            abc_restore(sh.ac, so.X, double(case_phys<R>(cd).rho0), lane);
             const double *row = nullptr;
-            if (cd.pc.traj_off >= 0 && bd.traj_pos[c] < cd.pc.traj_n) {
-                row = bd.traj + (cd.pc.traj_off + bd.traj_pos[c]) * 13;
-                bd.traj_pos[c] += 1;
+            if (cd.pc.traj_off >= 0) {
+                const int64_t at = uniform(bd.traj_pos[c]);
+                if (at < cd.pc.traj_n) {
+                    row = bd.traj + (cd.pc.traj_off + at) * 13;
+                    if (lane == 0) bd.traj_pos[c] = at + 1;
+                }
             }
             double F[3], M[3];
-            rigid_update(so, cd.pc, ac, bd.coupling, row, g, o, F, M);
-            bool bad = false;
-            for (int k = 0; k < 3; ++k) bad |= !isfinite(F[k]) || !isfinite(M[k]);
-            if (bad) atomicOr(&bd.ctr->err_unstable, 1u);
-            bd.ps[size_t(c) * 2 + nxt] = o;
-            for (int k = 0; k < 3; ++k) {
-                bd.ft[size_t(c) * 6 + k] = F[k];
-                bd.ft[size_t(c) * 6 + 3 + k] = M[k];
+            rigid_update(so, cd.pc, sh.ac, bd.coupling, row, g, o, F, M);
+            if (lane == 0) {
+                bool bad = false;
+                for (int k = 0; k < 3; ++k) bad |= !isfinite(F[k]) || !isfinite(M[k]);
+                if (bad) atomicOr(&bd.ctr->err_unstable, 1u);
+                bd.ps[size_t(c) * 2 + nxt] = o;
+                for (int k = 0; k < 3; ++k) {
+                    bd.ft[size_t(c) * 6 + k] = F[k];
+                    bd.ft[size_t(c) * 6 + 3 + k] = M[k];
+                }
+                double *h = bd.hist + (size_t(c) * bd.hist_cap + size_t(s % bd.hist_cap)) * 19;
+                for (int k = 0; k < 3; ++k) { h[k] = F[k]; h[3 + k] = M[k]; h[6 + k] = o.X[k]; }
+                for (int k = 0; k < 4; ++k) h[9 + k] = o.q[k];
+                for (int k = 0; k < 3; ++k) { h[13 + k] = o.V[k]; h[16 + k] = o.W[k]; }
             }
-            double *h = bd.hist + (size_t(c) * bd.hist_cap + size_t(s % bd.hist_cap)) * 19;
-            for (int k = 0; k < 3; ++k) { h[k] = F[k]; h[3 + k] = M[k]; h[6 + k] = o.X[k]; }
-            for (int k = 0; k < 4; ++k) h[9 + k] = o.q[k];
-            for (int k = 0; k < 3; ++k) { h[13 + k] = o.V[k]; h[16 + k] = o.W[k]; }
         }
-        Box ub, nb;
-        remap_boxes(o, cd.pc, bd.box_cur[c], g, ub, nb);
-        bd.box_cur[c] = nb;
-        sh.cur = so;
-        sh.nxt = o;
-        sh.ub = ub;
-        sh.nlist = 0u;
+        if (lane == 0) {
+            Box ub, nb;
+            remap_boxes(o, cd.pc, bd.box_cur[c], g, ub, nb);
+            bd.box_cur[c] = nb;
+            sh.cur = so;
+            sh.nxt = o;
+            sh.ub = ub;
+            sh.nlist = 0u;
+        }
     }
     __syncthreads();
     // plane rectangles of the remap region (both poses), then their offsets
@@ -262,37 +274,35 @@ __device__ __forceinline__ void case_particles(const BatchDev &bd, int c, const 
         y = wrapi(r.y0 + int32_t(iy), g.ny);
         z = sh.zpl[lo];
     };
-    // remap: new owner of every cell of the region; refill of uncovered cells
-    for (uint32_t i = threadIdx.x; i < total; i += BS) {
-        int32_t x, y, z;
-        locate(i, x, y, z);
-        const int owner = inside(sh.nxt, cd.pc, double(x), double(y), double(z), g) ? 0 : -1;
-        const uint32_t cell = (uint32_t(z) * g.ny + uint32_t(y)) * g.nx + uint32_t(x);
-        const int old = pidc[cell];
-        if (old >= 0 && owner < 0) refill_cell<RefillT<S>>(fr, g, x, y, z, sh.cur, rho0, scale, next_odd);
-        pidc[cell] = owner;
-    }
-    __syncthreads();
-    // flags, boundary list, and the population-free link sums at the new pose
+    // one pass over the region: new owner, refill of an uncovered cell, flag,
+    // boundary list, and the population-free link sums at the new pose (the
+    // neighbours' owners tested, not read back: see claims)
     uint32_t *lc = bd.list_cell + cd.list_off, *lm = bd.list_mask + cd.list_off;
     long long acc[NABC];
 #pragma unroll
     for (int k = 0; k < NABC; ++k) acc[k] = 0;
+    const PState pn = uniform(sh.nxt);
+    const bool quick = quick_claims(cd.pc, g);
     int32_t xr[3];
-    fiber_ref(sh.nxt.X, xr);
+    fiber_ref(pn.X, xr);
     for (uint32_t i = threadIdx.x; i < total; i += BS) {
         int32_t x, y, z;
         locate(i, x, y, z);
         const uint32_t cell = (uint32_t(z) * g.ny + uint32_t(y)) * g.nx + uint32_t(x);
-        if (pidc[cell] >= 0) {
+        const int old = pidc[cell];
+        const uint32_t m = claims(pn, cd.pc, x, y, z, g, quick);
+        const int owner = (m & 1u) ? 0 : -1;
+        if (old >= 0 && owner < 0) refill_cell<RefillT<S>>(fr, g, x, y, z, sh.cur, rho0, scale, next_odd);
+        if (owner != old) pidc[cell] = owner;
+        if (owner >= 0) {
             flc[cell] = F_SOLID;
             continue;
         }
-        const uint32_t mask = fiber_mask(pidc, g, x, y, z, 0);
-        if (!mask) {
+        if (!m) {
             flc[cell] = 0;
             continue;
         }
+        const uint32_t mask = m | LIST_HOME;
         const uint32_t r = atomicAdd(&sh.nlist, 1u);
         if (r >= cd.list_cap) {
             flc[cell] = 0;

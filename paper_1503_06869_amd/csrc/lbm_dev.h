@@ -284,10 +284,9 @@ hipError_t launch_encode(int sk, bool swapped, void *f, const Geo &g, double rho
                          const double *fin, hipStream_t st);
 hipError_t launch_rigid(const PartData &pd, const Geo &g, hipStream_t st);
 hipError_t launch_setup_boxes(const PartData &pd, const Geo &g, hipStream_t st);
-hipError_t launch_remap(int sk, bool next_odd, void *f, int32_t *pid, const PartData &pd, const Geo &g,
-                        double rho0, double scale, hipStream_t st);
-hipError_t launch_near(uint8_t *flags, const int32_t *pid, uint32_t *list_cell, uint32_t *list_mask,
-                       const PartData &pd, const Geo &g, hipStream_t st);
+hipError_t launch_map(int sk, bool next_odd, void *f, int32_t *pid, uint8_t *flags, uint32_t *list_cell,
+                      uint32_t *list_mask, const PartData &pd, const Geo &g, double rho0, double scale, bool advance,
+                      hipStream_t st);
 hipError_t launch_copy(void *dst, const void *src, size_t nbytes, hipStream_t st);
 // non-finite stored populations (n elements of the population array) set
 // bit 1 of ctr->err_unstable (check.hip)

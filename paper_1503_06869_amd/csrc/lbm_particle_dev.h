@@ -56,6 +56,59 @@ __device__ __forceinline__ bool inside(const PState &s, const PConst &c, double 
     return (a * a <= hl * hl) && (q <= r2);
 }
 
+// The predicate at a cell and at its 18 neighbours: bit q set when x + c_q is
+// inside (bit 0: the cell itself; neighbours beyond z walls: clear).  Bit for
+// bit the results of inside(): the differences, products and squares of the
+// three coordinates along each axis are formed once and added in its order.
+// A cell farther than 1.5 beyond the surface has no neighbour inside; with
+// `quick` (see quick_claims) its neighbours are not looked at.
+__device__ __forceinline__ uint32_t claims(const PState &s, const PConst &c, int32_t x, int32_t y, int32_t z,
+                                           const Geo &g, bool quick)
+{
+    const int32_t n[3] = {int32_t(g.nx), int32_t(g.ny), int32_t(g.nz)}, xc[3] = {x, y, z};
+    double d2[3][3], pt[3][3];   // [axis][coordinate - 1, same, + 1]: squares and products with the axis
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+            const bool per = k < 2 || g.zper;
+            int32_t v = xc[k] + e - 1;
+            if (per) v = v < 0 ? v + n[k] : (v >= n[k] ? v - n[k] : v);
+            const double d = mi_d(double(v) - s.X[k], uint32_t(n[k]), per);
+            d2[k][e] = d * d;
+            pt[k][e] = d * s.t[k];
+        }
+    const double hl = 0.5 * c.length, r2 = c.radius * c.radius, hl2 = hl * hl, hc = hl - c.radius;
+    const bool lo = g.zper || z > 0, hi = g.zper || z + 1 < n[2];
+    auto test = [&](int cx, int cy, int cz) {
+        const double a = pt[0][1 + cx] + pt[1][1 + cy] + pt[2][1 + cz];
+        const double q = (d2[0][1 + cx] + d2[1][1 + cy] + d2[2][1 + cz]) - a * a;
+        if (c.shape == 1) {
+            const double e = fabs(a) - hc;
+            return e <= 0.0 ? q <= r2 : q + e * e <= r2;
+        }
+        return (a * a <= hl2) && (q <= r2);
+    };
+    uint32_t m = test(0, 0, 0) ? 1u : 0u;
+    if (quick) {
+        const double a = pt[0][1] + pt[1][1] + pt[2][1];
+        const double q = (d2[0][1] + d2[1][1] + d2[2][1]) - a * a;
+        const double rr = c.radius + 1.5;
+        if (fabs(a) > hl + 1.5 || q > rr * rr) return m;
+    }
+#pragma unroll
+    for (int q = 1; q < Q; ++q)
+        if ((CZ[q] >= 0 || lo) && (CZ[q] <= 0 || hi) && test(CX[q], CY[q], CZ[q])) m |= 1u << q;
+    return m;
+}
+
+// whether a cell and its neighbours see a fiber through the same periodic image
+__device__ __forceinline__ bool quick_claims(const PConst &c, const Geo &g)
+{
+    const double h = 0.5 * c.length + c.radius + 3.0;
+    return h < 0.5 * double(g.nx) && h < 0.5 * double(g.ny) && (!g.zper || h < 0.5 * double(g.nz));
+}
+
 // box (dilated AABB) of the cells a fiber can own or border
 __device__ __forceinline__ void fiber_box(const PState &s, const PConst &c, const Geo &g, const double Xref[3],
                           int32_t lo[3], int32_t hi[3])
@@ -125,14 +178,12 @@ __device__ __forceinline__ bool boxes_meet(const Box &a, const Box &b, const Geo
 // ------------------------------------------------------------------ per-plane rectangles
 // Within a box, plane z is crossed by the capsule of radius r + margin
 // around the fiber axis segment only in an x/y rectangle.  Every cell that a
-// fiber can own lies within r of the segment (REMAP_MARGIN leaves half a
-// cell for rounding); every cell that can border it (fluid neighbours lie
-// within sqrt(2) of owned cell centres) within r + sqrt(2) (NEAR_MARGIN);
-// RECT_MARGIN covers both with room to spare (the batched kernel, which does
-// both in one pass).  Rectangles are in the unwrapped frame of the box; for
-// boxes narrower than the domain they are clipped to the box.
+// fiber can own lies within r of the segment, every cell that can border it
+// (fluid neighbours lie within sqrt(2) of owned cell centres) within r +
+// sqrt(2) (NEAR_MARGIN; RECT_MARGIN, of the batched kernel, with room to
+// spare).  Rectangles are in the unwrapped frame of the box; for boxes
+// narrower than the domain they are clipped to the box.
 constexpr double RECT_MARGIN = 2.5;
-constexpr double REMAP_MARGIN = 0.5;
 constexpr double NEAR_MARGIN = 1.5;
 
 struct Rect {
@@ -473,10 +524,11 @@ __device__ __forceinline__ void remap_boxes(const PState &s, const PConst &c, co
     const int32_t n[3] = {int32_t(g.nx), int32_t(g.ny), int32_t(g.nz)};
     int32_t mid_new[3];
     for (int k = 0; k < 3; ++k) mid_new[k] = (lo[k] + hi[k]) / 2;
-    const Box *olds[2] = {&old, &older};
+#pragma unroll
     for (int j = 0; j < 2; ++j) {
-        const Box &ob = *olds[j];
+        const Box &ob = j == 0 ? old : older;
         if (ob.len[0] <= 0) continue;
+#pragma unroll
         for (int k = 0; k < 3; ++k) {
             const bool per = k < 2 || g.zper;
             int32_t olo = ob.lo[k];
@@ -496,27 +548,6 @@ __device__ __forceinline__ void remap_boxes(const PState &s, const PConst &c, co
                                             Box &ub, Box &nb)
 {
     remap_boxes(s, c, old, Box{{0, 0, 0}, {0, 0, 0}}, g, ub, nb);
-}
-
-// neighbour mask of cell (x, y, z): bit q set when x + c_q is a fiber cell,
-// and LIST_HOME when every such cell belongs to fiber `home`
-__device__ __forceinline__ uint32_t fiber_mask(const int32_t *pid, const Geo &g, int32_t x, int32_t y, int32_t z,
-                                               int32_t home)
-{
-    const int32_t nx = g.nx, ny = g.ny, nz = g.nz;
-    uint32_t mask = 0;
-    bool all = true;
-#pragma unroll
-    for (int q = 1; q < Q; ++q) {
-        int32_t zz = z + CZ[q];
-        if (g.zper) zz = wrapc(zz, nz);
-        else if (zz < 0 || zz >= nz) continue;
-        const int32_t xx = wrapc(x + CX[q], nx), yy = wrapc(y + CY[q], ny);
-        const int32_t o = pid[(uint32_t(zz) * g.ny + uint32_t(yy)) * g.nx + uint32_t(xx)];
-        if (o >= 0) mask |= 1u << q;
-        all &= o < 0 || o == home;
-    }
-    return mask && all ? mask | LIST_HOME : mask;
 }
 
 // ------------------------------------------------------------------ population-free link sums
@@ -588,48 +619,53 @@ __device__ __forceinline__ int32_t eps3(int i, int j, int k)
 
 // A, B, C (packed as the momentum-exchange accumulators 6 .. 26: A[6]
 // symmetric, B[9], C[6] symmetric) from the integer sums S (exact values in
-// FP64) of a fiber centred at X, in place
-__device__ __forceinline__ void abc_restore(double *acc, const double X[3], double rho0)
+// FP64) of a fiber centred at X, in place.  acc in LDS; called by a whole
+// wave: lane 3 i + j < 9 forms B_ij and C_ij.
+__device__ __forceinline__ void abc_restore(double *acc, const double X[3], double rho0, int lane)
 {
-    const int si[6][2] = {{0, 0}, {0, 1}, {0, 2}, {1, 1}, {1, 2}, {2, 2}};
-    double SA[3][3], SB[3][3], SC[3][3], d[3];
-    for (int k = 0; k < 6; ++k) {
-        SA[si[k][0]][si[k][1]] = SA[si[k][1]][si[k][0]] = acc[6 + k];
-        SC[si[k][0]][si[k][1]] = SC[si[k][1]][si[k][0]] = acc[21 + k];
-    }
-    for (int i = 0; i < 3; ++i)
-        for (int j = 0; j < 3; ++j) SB[i][j] = acc[12 + 3 * i + j];
+    const int i = lane < 9 ? lane / 3 : 0, j = lane < 9 ? lane % 3 : 0;
+    // position of (a, b) in a packed symmetric matrix
+    auto sym = [](int a, int b) {
+        const int lo = a < b ? a : b, hi = a < b ? b : a;
+        return lo == 0 ? hi : lo + hi + 1;
+    };
+    double d[3], Ei[3], Ej[3];
     for (int k = 0; k < 3; ++k) d[k] = X[k] - floor(X[k]);
     // (delta x c) components as linear maps of c: E[j][b] = eps_jab delta_a
-    double E[3][3];
-    for (int j = 0; j < 3; ++j)
-        for (int b = 0; b < 3; ++b) {
-            double e = 0.0;
-            for (int a = 0; a < 3; ++a) e += double(eps3(j, a, b)) * d[a];
-            E[j][b] = e;
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+        double ei = 0.0, ej = 0.0;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            ei += double(eps3(i, a, b)) * d[a];
+            ej += double(eps3(j, a, b)) * d[a];
         }
-    const double k6 = rho0 / 6.0;
-    double B[3][3], C[3][3];
-    for (int i = 0; i < 3; ++i)
-        for (int j = 0; j < 3; ++j) {
-            double m = 0.0, nn = 0.0, nt = 0.0;
-            for (int b = 0; b < 3; ++b) {
-                m += E[j][b] * SA[i][b];    // M_ij
-                nn += E[j][b] * SB[b][i];   // N_ij
-                nt += E[i][b] * SB[b][j];   // N_ji
-            }
-            double pp = 0.0;                // P_ij = E[i][b] E[j][e] SA_be
-            for (int b = 0; b < 3; ++b)
-                for (int e = 0; e < 3; ++e) pp += E[i][b] * E[j][e] * SA[b][e];
-            B[i][j] = k6 * (SB[i][j] - m);
-            C[i][j] = k6 * (((SC[i][j] - nn) - nt) + pp);
-        }
-    for (int k = 0; k < 6; ++k) {
-        acc[6 + k] = k6 * SA[si[k][0]][si[k][1]];
-        acc[21 + k] = C[si[k][0]][si[k][1]];
+        Ei[b] = ei;
+        Ej[b] = ej;
     }
-    for (int i = 0; i < 3; ++i)
-        for (int j = 0; j < 3; ++j) acc[12 + 3 * i + j] = B[i][j];
+    const double k6 = rho0 / 6.0;
+    double m = 0.0, nn = 0.0, nt = 0.0, pp = 0.0;
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+        m += Ej[b] * acc[6 + sym(i, b)];          // M_ij
+        nn += Ej[b] * acc[12 + 3 * b + i];        // N_ij
+        nt += Ei[b] * acc[12 + 3 * b + j];        // N_ji
+    }
+#pragma unroll
+    for (int b = 0; b < 3; ++b)                   // P_ij = E[i][b] E[j][e] SA_be
+#pragma unroll
+        for (int e = 0; e < 3; ++e) pp += Ei[b] * Ej[e] * acc[6 + sym(b, e)];
+    const double B = k6 * (acc[12 + 3 * i + j] - m);
+    const double C = k6 * (((acc[21 + sym(i, j)] - nn) - nt) + pp);
+    const double A = lane < 6 ? k6 * acc[6 + lane] : 0.0;
+    __builtin_amdgcn_wave_barrier();              // every lane has read its sums
+    if (lane < 6) acc[6 + lane] = A;
+    if (lane < 9) {
+        acc[12 + 3 * i + j] = B;
+        if (i <= j) acc[21 + sym(i, j)] = C;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
 template <typename S>

@@ -3,13 +3,12 @@
 //                LBMhydrodynForce and the torque after it, Sec. 4.2),
 //                accumulated by the boundary sweep, back to FP64; the
 //                rigid-body update (Sec. 4.3); the cell boxes of the remap;
-//   k_remap      cell mapping with the new poses (Sec. 4.2: a cell is an
-//                obstacle cell when its centre lies inside a particle) and
+//   k_map        cell mapping with the new poses (Sec. 4.2: a cell is an
+//                obstacle cell when its centre lies inside a particle),
 //                refill of uncovered cells with f_eq(rho0, u_s) of the
-//                previous step's motion;
-//   k_near       flags of fluid cells next to fibers, written into the flag
-//                buffer of the next step, and the boundary-cell list consumed
-//                by the next step's boundary launch.
+//                previous step's motion, flags of fluid cells next to fibers
+//                in the flag buffer of the next step, and the boundary-cell
+//                list consumed by the next step's boundary launch.
 #include "lbm_sweep_dev.h"
 #include "lbm_particle_dev.h"
 
@@ -17,19 +16,17 @@ namespace lbm {
 
 #pragma clang fp contract(off)
 
-// Plane rectangle of fiber o's remap region: the current and new poses
-// (where cell owners can change; margin for owned cells), and with PREV, for
-// the flag rebuild, also the previous pose (the flags of the next step are
+// Plane rectangle of fiber o's region: the cells it can own or border at the
+// new, the current and the previous pose (the flags of the next step are
 // written into the buffer that held those of the previous step, so the
-// rebuild covers every cell flagged then; margin for bordering cells).
-template <bool PREV>
+// rebuild covers every cell flagged then).
 __device__ __forceinline__ Rect remap_rect(const PartData &pd, int o, int32_t z, const Geo &g)
 {
     const Box b = pd.box_remap[o];
     const PConst c = pd.pc[o];
-    const double m = PREV ? NEAR_MARGIN : REMAP_MARGIN;
-    const Rect r = rect_union(plane_rect(pd.ps_cur[o], c, z, b, g, m), plane_rect(pd.ps_next[o], c, z, b, g, m), g);
-    return PREV ? rect_union(r, plane_rect(pd.ps_prev[o], c, z, b, g, m), g) : r;
+    const Rect r = rect_union(plane_rect(pd.ps_cur[o], c, z, b, g, NEAR_MARGIN),
+                              plane_rect(pd.ps_next[o], c, z, b, g, NEAR_MARGIN), g);
+    return rect_union(r, plane_rect(pd.ps_prev[o], c, z, b, g, NEAR_MARGIN), g);
 }
 
 // ------------------------------------------------------------------ boxes of the remap
@@ -47,12 +44,6 @@ __device__ __forceinline__ void fiber_remap_boxes(const PartData &pd, int p, con
     pd.seg_cnt[p] = 0u;
 }
 
-// end of a time step: advance the device step counter
-__device__ void finish_step(const PartData &pd)
-{
-    if (threadIdx.x == 0) pd.ctr->step += 1ull;
-}
-
 // Set-up of the mapping from ps_cur (old poses, or the current ones) to
 // ps_next: the previous pose is taken equal to the old one.
 __global__ __launch_bounds__(256) void k_setup_boxes(PartData pd, Geo g)
@@ -65,62 +56,70 @@ __global__ __launch_bounds__(256) void k_setup_boxes(PartData pd, Geo g)
 }
 
 // ------------------------------------------------------------------ rigid update kernel
-// One block: the momentum-exchange sums of every fiber (accumulated in fixed
-// point by the boundary sweep) back to FP64, the contact loads (when on), the
+// One wave per fiber: its momentum-exchange sums (accumulated in fixed point
+// by the boundary launch) back to FP64, the contact loads (when on), the
 // rigid-body update, outputs, the boxes of the remap and the list reset.
-__global__ __launch_bounds__(256) void k_rigid(PartData pd, Geo g)
+// Bound by the latency of one serial FP64 chain (a 6x6 Cholesky, sine and
+// cosine, three square roots); nine lanes form the B and C matrices, and the
+// state and the records move as whole rows.
+__global__ __launch_bounds__(64) void k_rigid(PartData pd, Geo g)
 {
-    extern __shared__ double tot[];   // [np][NACC]
-    const int np = pd.np;
-    for (int t = threadIdx.x; t < np * NACC; t += blockDim.x) {
-        const int k = t % NACC;
-        tot[t] = ldexp(double(pd.mea[t]), -fx_shift(k));
-        pd.mea[t] = 0;   // cleared for the next step's boundary sweep
+    constexpr int NPS = int(sizeof(PState) / sizeof(double));
+    static_assert(sizeof(PState) % sizeof(double) == 0 && NPS <= 64, "one lane per word of a state");
+    __shared__ double ac[NACC], s_out[NPS + 6], s_cl[64][6];
+    const int p = int(blockIdx.x), np = pd.np, lane = int(threadIdx.x);
+    const int64_t step = int64_t(pd.ctr->step);
+    if (lane < NACC) {
+        ac[lane] = ldexp(double(pd.mea[size_t(p) * NACC + lane]), -fx_shift(lane));
+        pd.mea[size_t(p) * NACC + lane] = 0;   // cleared for the next step's boundary launch
+    }
+    // the pose of the previous step, about to be overwritten
+    double *nxt = reinterpret_cast<double *>(pd.ps_next + p);
+    if (lane < NPS) reinterpret_cast<double *>(pd.ps_prev + p)[lane] = nxt[lane];
+    const PConst c = pd.pc[p];
+    const PState s = pd.ps_cur[p];
+    const double *row = nullptr;
+    if (c.traj_off >= 0) {
+        const int64_t at = pd.traj_pos[p];
+        if (at < c.traj_n) row = pd.traj + (c.traj_off + at) * 13;
+        __syncthreads();
+        if (lane == 0 && row) pd.traj_pos[p] = at + 1;
     }
     // contact loads at the current poses, each pair in the orientation (lower
     // id, higher id) and summed over partners in ascending order
-    double *cl = tot + size_t(np) * NACC;   // [np][6] when contacts are on
+    double cl[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     if (pd.contact_k > 0.0)
-        for (int p = threadIdx.x; p < np; p += blockDim.x) {
-            double acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-            const PState sp = pd.ps_cur[p];
-            const PConst cp = pd.pc[p];
-            for (int q = 0; q < np; ++q) {
-                if (q == p) continue;
-                double l[6];
-                if (p < q) contact_load(sp, cp, pd.ps_cur[q], pd.pc[q], true, pd.contact_k, pd.contact_range, g, l);
-                else contact_load(pd.ps_cur[q], pd.pc[q], sp, cp, false, pd.contact_k, pd.contact_range, g, l);
-                for (int k = 0; k < 6; ++k) acc[k] += l[k];
+        for (int q0 = 0; q0 < np; q0 += 64) {
+            const int q = q0 + lane;
+            double l[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+            if (q < np && q != p) {
+                if (p < q) contact_load(s, c, pd.ps_cur[q], pd.pc[q], true, pd.contact_k, pd.contact_range, g, l);
+                else contact_load(pd.ps_cur[q], pd.pc[q], s, c, false, pd.contact_k, pd.contact_range, g, l);
             }
-            for (int k = 0; k < 6; ++k) cl[p * 6 + k] = acc[k];
+#pragma unroll
+            for (int k = 0; k < 6; ++k) s_cl[lane][k] = l[k];
+            __syncthreads();
+            for (int e = 0; e < 64 && q0 + e < np; ++e)
+#pragma unroll
+                for (int k = 0; k < 6; ++k) cl[k] += s_cl[e][k];
+            __syncthreads();
         }
     __syncthreads();
-    const int64_t step = int64_t(pd.ctr->step);
-    for (int p = threadIdx.x; p < np; p += blockDim.x) {
-        double ac[NACC];
-        for (int k = 0; k < NACC; ++k) ac[k] = tot[p * NACC + k];
-        const PConst c = pd.pc[p];
-        const PState s = pd.ps_cur[p];
-        abc_restore(ac, s.X, pd.rho0_link);
-        const double *row = nullptr;
-        if (c.traj_off >= 0 && pd.traj_pos[p] < c.traj_n) {
-            row = pd.traj + (c.traj_off + pd.traj_pos[p]) * 13;
-            pd.traj_pos[p] += 1;
-        }
-        PState o;
-        double F[3], M[3];
-        rigid_update(s, c, ac, pd.coupling, row, g, o, F, M, pd.corr ? pd.corr + size_t(p) * 6 : nullptr,
-                     pd.contact_k > 0.0 ? cl + size_t(p) * 6 : nullptr);
+    abc_restore(ac, s.X, pd.rho0_link, lane);
+    PState o;
+    double F[3], M[3];
+    rigid_update(s, c, ac, pd.coupling, row, g, o, F, M, pd.corr ? pd.corr + size_t(p) * 6 : nullptr,
+                 pd.contact_k > 0.0 ? cl : nullptr);
+    if (lane == 0) {
         bool bad = false;
         for (int k = 0; k < 3; ++k) bad |= !isfinite(F[k]) || !isfinite(M[k]);
         if (bad) atomicOr(&pd.ctr->err_unstable, 1u);
-        pd.ps_prev[p] = pd.ps_next[p];   // the pose of the previous step, about to be overwritten
-        pd.ps_next[p] = o;
         if (g.xw || g.yw || g.zs) {
             // fibers keep more than one cell from x and y walls (the mapping
             // and momentum exchange take x and y as periodic) and from
             // free-slip z walls (a reflected population lands on a cell of
             // the wall layer, which must be fluid)
+#pragma unroll
             for (int k = 0; k < 3; ++k) {
                 if (!(k == 0 ? g.xw : (k == 1 ? g.yw : g.zs))) continue;
                 const double ext = c.shape == 1 ? (0.5 * c.length - c.radius) * fabs(o.t[k]) + c.radius
@@ -131,17 +130,18 @@ __global__ __launch_bounds__(256) void k_rigid(PartData pd, Geo g)
             }
         }
         fiber_remap_boxes(pd, p, o, g);
+        *reinterpret_cast<PState *>(s_out) = o;
+#pragma unroll
         for (int k = 0; k < 3; ++k) {
-            pd.ft_out[p * 6 + k] = F[k];
-            pd.ft_out[p * 6 + 3 + k] = M[k];
+            s_out[NPS + k] = F[k];
+            s_out[NPS + 3 + k] = M[k];
         }
-        double *h = pd.hist + ((step % pd.hist_cap) * np + p) * 19;
-        for (int k = 0; k < 3; ++k) { h[k] = F[k]; h[3 + k] = M[k]; h[6 + k] = o.X[k]; }
-        for (int k = 0; k < 4; ++k) h[9 + k] = o.q[k];
-        for (int k = 0; k < 3; ++k) { h[13 + k] = o.V[k]; h[16 + k] = o.W[k]; }
     }
-    __syncthreads();   // every thread has read the step counter
-    finish_step(pd);
+    __syncthreads();
+    if (lane < NPS) nxt[lane] = s_out[lane];
+    if (lane < 6) pd.ft_out[size_t(p) * 6 + lane] = s_out[NPS + lane];
+    // record F M X q V W (X q V W lead the state)
+    if (lane < 19) pd.hist[((step % pd.hist_cap) * np + p) * 19 + lane] = lane < 6 ? s_out[NPS + lane] : s_out[lane - 6];
 }
 
 // ------------------------------------------------------------------ remap and boundary list
@@ -215,7 +215,6 @@ __device__ __forceinline__ void stage_nbrs(const PartData &pd, int p, NbrStage &
 
 // Table of the planes iz0, iz0 + ns, ... of box b (as many as fit); returns
 // the number of planes taken (block-uniform call).
-template <bool PREV>
 __device__ int build_table(const PartData &pd, const NbrStage &sh, int p, const Box &b, int iz0, int ns,
                            const Geo &g, RegionTable &t)
 {
@@ -231,8 +230,8 @@ __device__ int build_table(const PartData &pd, const NbrStage &sh, int p, const 
         else valid = z >= 0 && z < int32_t(g.nz);
         Rect r{1, 0, 1, 0};
         if (valid) {
-            if (j == 0) r = remap_rect<PREV>(pd, p, z, g);
-            else if (in_zrange(sh.box[j - 1], z, g)) r = remap_rect<PREV>(pd, sh.id[j - 1], z, g);
+            if (j == 0) r = remap_rect(pd, p, z, g);
+            else if (in_zrange(sh.box[j - 1], z, g)) r = remap_rect(pd, sh.id[j - 1], z, g);
         }
         t.rect[e] = r;
         if (j == 0) t.z[k] = z;
@@ -274,81 +273,38 @@ __device__ __forceinline__ bool owned_here(const RegionTable &t, int k, int32_t 
     return true;
 }
 
-// new owner of each cell of the remap boxes; refill of uncovered cells
-template <typename S>
-__global__ __launch_bounds__(256) void k_remap(S *__restrict__ f, int32_t *__restrict__ pid, PartData pd,
-                                               Geo g, int next_odd, double rho0, double scale)
-{
-    const int ns = pd.nslab;
-    const int p = blockIdx.x / ns, sl = blockIdx.x % ns;
-    __shared__ NbrStage sh;
-    stage_nbrs(pd, p, sh, g);
-    const Box b = pd.box_remap[p];
-    const PState sp = pd.ps_next[p];
-    const PConst cp = pd.pc[p];
-    __shared__ RegionTable t;
-    for (int iz0 = sl; iz0 < b.len[2];) {   // block-uniform: chunks of planes
-        iz0 += ns * build_table<false>(pd, sh, p, b, iz0, ns, g, t);
-        for (int idx = threadIdx.x; idx < t.pref[t.npl]; idx += blockDim.x) {
-            int k;
-            int32_t x, y;
-            table_cell(t, idx, g, k, x, y);
-            if (!owned_here(t, k, x, y, g)) continue;
-            const int32_t z = t.z[k];
-            const double cx = x, cy = y, cz = z;
-            int owner = -1, claims = 0;
-            if (inside(sp, cp, cx, cy, cz, g)) {
-                owner = p;
-                claims = 1;
-            }
-            for (int j = sh.nlow; j < sh.n; ++j) {
-                const int o = sh.id[j];
-                if (!in_box(sh.box[j], x, y, z, g)) continue;
-                if (inside(pd.ps_next[o], pd.pc[o], cx, cy, cz, g)) {
-                    if (owner < 0) owner = o;
-                    ++claims;
-                }
-            }
-            if (claims > 1) atomicAdd(&pd.ctr->overlaps, (unsigned long long)(claims - 1));
-            const uint32_t cell = (uint32_t(z) * g.ny + uint32_t(y)) * g.nx + uint32_t(x);
-            const int old = pid[cell];
-            if (old >= 0 && owner < 0)   // uncovered
-                refill_cell<S>(f, g, x, y, z, pd.ps_cur[old], rho0, scale, next_odd);
-            if (pd.cov && (old < 0) != (owner < 0)) {
-                // fluid cell count and momentum change for the stabilization
-                const uint32_t k = atomicAdd(pd.cov, 1u);
-                if (k < pd.cov_cap) pd.cov[1 + k] = cell | (owner < 0 ? COV_UNCOVERED : 0u);
-                else atomicOr(&pd.ctr->err_capacity, 4u);
-            }
-            pid[cell] = owner;
-        }
-    }
-}
-
-// Flags of the cells in the remap regions and the boundary-cell list.  The
-// list is cut into one segment per fiber; a block stages the boundary cells
-// it finds in all its planes in LDS and reserves a range of its fiber's
-// segment with a single atomic (cells beyond the stage are appended one by
-// one).
+// New owner of each cell of the regions, refill of uncovered cells, flags and
+// the boundary-cell list.  The neighbours' owners are not read back but
+// tested (claims), so mapping and list are one pass with no wait between
+// them; 18 further tests cost 8 FP64 instructions each, on cells within 1.5
+// of a surface only.  The list is cut into one segment per fiber; a block
+// stages the boundary cells it finds in all its planes in LDS and reserves a
+// range of its fiber's segment with a single atomic (cells beyond the stage
+// are appended one by one).  advance: end of a time step (the step counter).
 constexpr int LSTAGE = 1024;
 
-__global__ __launch_bounds__(256) void k_near(uint8_t *__restrict__ flags, const int32_t *__restrict__ pid,
-                                              uint32_t *__restrict__ list_cell,
-                                              uint32_t *__restrict__ list_mask, PartData pd, Geo g)
+template <typename S>
+__global__ __launch_bounds__(256) void k_map(S *__restrict__ f, int32_t *__restrict__ pid,
+                                             uint8_t *__restrict__ flags, uint32_t *__restrict__ list_cell,
+                                             uint32_t *__restrict__ list_mask, PartData pd, Geo g, int next_odd,
+                                             double rho0, double scale, int advance)
 {
     const int ns = pd.nslab;
     const int p = blockIdx.x / ns, sl = blockIdx.x % ns;
     __shared__ NbrStage sh;
     __shared__ uint32_t s_cell[LSTAGE], s_mask[LSTAGE];
     __shared__ uint32_t s_n, s_base;
-    stage_nbrs(pd, p, sh, g);
+    if (advance && blockIdx.x == 0 && threadIdx.x == 0) pd.ctr->step += 1ull;
     if (threadIdx.x == 0) s_n = 0u;
-    __syncthreads();
+    stage_nbrs(pd, p, sh, g);
     const Box b = pd.box_remap[p];
+    const PState sp = pd.ps_next[p];
+    const PConst cp = pd.pc[p];
     const uint32_t off = pd.seg_off[p], cap = pd.seg_cap[p];
+    const bool quick = quick_claims(cp, g);
     __shared__ RegionTable t;
     for (int iz0 = sl; iz0 < b.len[2];) {   // block-uniform: chunks of planes
-        iz0 += ns * build_table<true>(pd, sh, p, b, iz0, ns, g, t);
+        iz0 += ns * build_table(pd, sh, p, b, iz0, ns, g, t);
         for (int idx = threadIdx.x; idx < t.pref[t.npl]; idx += blockDim.x) {
             int k;
             int32_t x, y;
@@ -356,14 +312,38 @@ __global__ __launch_bounds__(256) void k_near(uint8_t *__restrict__ flags, const
             if (!owned_here(t, k, x, y, g)) continue;
             const int32_t z = t.z[k];
             const uint32_t cell = (uint32_t(z) * g.ny + uint32_t(y)) * g.nx + uint32_t(x);
-            // the cell's owner and its neighbours' in one round of loads
-            const int32_t own = pid[cell];
-            const uint32_t mask = fiber_mask(pid, g, x, y, z, p);
-            const bool near = (own < 0) & (mask != 0u);
-            if (!near) {
-                flags[cell] = own >= 0 ? F_SOLID : uint8_t(0);
+            const int old = pid[cell];
+            // bits of the own fiber, and of all: a lower-indexed fiber cannot
+            // own or border this cell (it would handle it)
+            const uint32_t mine = claims(sp, cp, x, y, z, g, quick);
+            uint32_t any = mine;
+            int owner = (mine & 1u) ? p : -1, nclaim = int(mine & 1u);
+            for (int j = sh.nlow; j < sh.n; ++j) {
+                const int o = sh.id[j];
+                if (!in_box(sh.box[j], x, y, z, g)) continue;
+                const uint32_t m = claims(pd.ps_next[o], pd.pc[o], x, y, z, g, quick_claims(pd.pc[o], g));
+                any |= m;
+                if (m & 1u) {
+                    if (owner < 0) owner = o;
+                    ++nclaim;
+                }
+            }
+            if (nclaim > 1) atomicAdd(&pd.ctr->overlaps, (unsigned long long)(nclaim - 1));
+            if (old >= 0 && owner < 0)   // uncovered
+                refill_cell<S>(f, g, x, y, z, pd.ps_cur[old], rho0, scale, next_odd);
+            if (pd.cov && (old < 0) != (owner < 0)) {
+                // fluid cell count and momentum change for the stabilization
+                const uint32_t kc = atomicAdd(pd.cov, 1u);
+                if (kc < pd.cov_cap) pd.cov[1 + kc] = cell | (owner < 0 ? COV_UNCOVERED : 0u);
+                else atomicOr(&pd.ctr->err_capacity, 4u);
+            }
+            if (owner != old) pid[cell] = owner;
+            uint32_t mask = any & ~1u;
+            if (owner >= 0 || !mask) {
+                flags[cell] = owner >= 0 ? F_SOLID : uint8_t(0);
                 continue;
             }
+            if (!(mask & ~mine)) mask |= LIST_HOME;
             const uint32_t kk = atomicAdd(&s_n, 1u);
             if (kk < LSTAGE) {
                 s_cell[kk] = cell;
@@ -405,8 +385,7 @@ __global__ __launch_bounds__(256) void k_near(uint8_t *__restrict__ flags, const
 // ------------------------------------------------------------------ launchers
 hipError_t launch_rigid(const PartData &pd, const Geo &g, hipStream_t st)
 {
-    const size_t per = NACC + (pd.contact_k > 0.0 ? 6 : 0);
-    hipLaunchKernelGGL(k_rigid, dim3(1), dim3(256), size_t(pd.np) * per * sizeof(double), st, pd, g);
+    hipLaunchKernelGGL(k_rigid, dim3(uint32_t(pd.np)), dim3(64), 0, st, pd, g);
     return hipGetLastError();
 }
 
@@ -416,25 +395,18 @@ hipError_t launch_setup_boxes(const PartData &pd, const Geo &g, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t launch_remap(int sk, bool next_odd, void *f, int32_t *pid, const PartData &pd, const Geo &g,
-                        double rho0, double scale, hipStream_t st)
+hipError_t launch_map(int sk, bool next_odd, void *f, int32_t *pid, uint8_t *flags, uint32_t *list_cell,
+                      uint32_t *list_mask, const PartData &pd, const Geo &g, double rho0, double scale, bool advance,
+                      hipStream_t st)
 {
-    const int no = next_odd ? 1 : 0;
+    const int no = next_odd ? 1 : 0, ad = advance ? 1 : 0;
     const dim3 gr(pd.np * pd.nslab), bl(256);
     switch (sk) {
-    case S_F32: hipLaunchKernelGGL(k_remap<float>, gr, bl, 0, st, (float *)f, pid, pd, g, no, rho0, scale); break;
-    case S_F16: hipLaunchKernelGGL(k_remap<_Float16>, gr, bl, 0, st, (_Float16 *)f, pid, pd, g, no, rho0, scale); break;
-    case S_BF16: hipLaunchKernelGGL(k_remap<uint16_t>, gr, bl, 0, st, (uint16_t *)f, pid, pd, g, no, rho0, scale); break;
-    default: hipLaunchKernelGGL(k_remap<double>, gr, bl, 0, st, (double *)f, pid, pd, g, no, rho0, scale); break;
+    case S_F32: hipLaunchKernelGGL(k_map<float>, gr, bl, 0, st, (float *)f, pid, flags, list_cell, list_mask, pd, g, no, rho0, scale, ad); break;
+    case S_F16: hipLaunchKernelGGL(k_map<_Float16>, gr, bl, 0, st, (_Float16 *)f, pid, flags, list_cell, list_mask, pd, g, no, rho0, scale, ad); break;
+    case S_BF16: hipLaunchKernelGGL(k_map<uint16_t>, gr, bl, 0, st, (uint16_t *)f, pid, flags, list_cell, list_mask, pd, g, no, rho0, scale, ad); break;
+    default: hipLaunchKernelGGL(k_map<double>, gr, bl, 0, st, (double *)f, pid, flags, list_cell, list_mask, pd, g, no, rho0, scale, ad); break;
     }
-    return hipGetLastError();
-}
-
-hipError_t launch_near(uint8_t *flags, const int32_t *pid, uint32_t *list_cell, uint32_t *list_mask,
-                       const PartData &pd, const Geo &g, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_near, dim3(pd.np * pd.nslab), dim3(256), 0, st, flags, pid, list_cell, list_mask,
-                       pd, g);
     return hipGetLastError();
 }
 
