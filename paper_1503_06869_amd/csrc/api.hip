@@ -130,12 +130,13 @@ static void free_particles(lbm_ctx *c)
 
 // buffers of the momentum stabilization, sized for the current sweep and
 // boundary grids and boundary list
+static uint32_t stab_slots_saved(const lbm_ctx *c);
 static lbm_status alloc_stab(lbm_ctx *c)
 {
     if (!c->p.stabilize) return LBM_OK;
     dfree(c->stab);
     dfree(c->cov);
-    const uint32_t nslot = std::max(STAB_SCAN_GRID, c->sweep_grid + c->bnd_grid);
+    const uint32_t nslot = std::max(stab_slots_saved(c), c->sweep_grid + c->bnd_grid);
     HIPCHK(c, dalloc(c, &c->stab, size_t(STAB_HEAD) + 4 * size_t(nslot)));
     HIPCHK(c, hipMemsetAsync(c->stab, 0, (size_t(STAB_HEAD) + 4 * size_t(nslot)) * sizeof(double), c->st));
     // cells changing owner in one remap: fewer than the boundary list holds
@@ -545,9 +546,14 @@ lbm_status lbm_create(const lbm_params *p, lbm_ctx **out)
     // resident workgroups per CU keeps the 38 access streams compact
     {
         const uint32_t nchunk = uint32_t((double(p->nx) * p->ny * p->nz + 255.0) / 256.0);
-        // measured on the 256^3 cell: FP32/FP64 best near 512 workgroups
-        // (leaving room for the boundary branch), 16-bit storage near 4096
-        const uint32_t dflt = (p->storage == LBM_F16DEV || p->storage == LBM_BF16DEV) ? 4096u : 512u;
+        // measured: FP32/FP64 best near 512 workgroups (256^3: 507 us against
+        // 520 at 768 and 548 at 1024), 16-bit storage near 4096 (280 us, 360
+        // at 512, 302 at 1024); with walls on the x or y faces or free-slip z
+        // walls the odd sweep selects its sources and 768 hide that
+        // arithmetic better (160^2 x 1200: 983 us against 1076 at 512 and 1013
+        // at 1024)
+        const bool walls = p->x_walls || p->y_walls || p->z_free_slip;
+        const uint32_t dflt = (p->storage == LBM_F16DEV || p->storage == LBM_BF16DEV) ? 4096u : (walls ? 768u : 512u);
         uint32_t gsz = p->sweep_grid > 0 ? uint32_t(p->sweep_grid) : dflt;
         c->sweep_grid = gsz < nchunk ? gsz : nchunk;
     }
@@ -1046,14 +1052,17 @@ struct BufRef {
 };
 // Workgroup slots of the stabilization buffer in a checkpoint.  Only the head
 // carries state (a step writes its slots before it reads them); the count is
-// part of the file format: the sweep's workgroups and one slot per 256
+// part of the file format: 512 workgroups of the sweep (4096 with 16-bit
+// storage; or as asked for), at most one per 256 cells, and one slot per 256
 // expected boundary cells of the largest fiber, at most 16, for every fiber.
 static uint32_t stab_slots_saved(const lbm_ctx *c)
 {
     double m = 0.0;
     for (const lbm_fiber &f : c->fib) m = std::max(m, shell_cells(f));
     const int per = std::max(1, std::min(16, int(std::ceil(m / 256.0))));
-    return std::max(STAB_SCAN_GRID, c->sweep_grid + uint32_t(c->np) * uint32_t(per));
+    const uint32_t nchunk = uint32_t((uint64_t(c->g.ncell) + 255u) / 256u);
+    const uint32_t grid = c->p.sweep_grid > 0 ? uint32_t(c->p.sweep_grid) : (c->esz == 2 ? 4096u : 512u);
+    return std::max(STAB_SCAN_GRID, std::min(grid, nchunk) + uint32_t(c->np) * uint32_t(per));
 }
 static std::vector<BufRef> state_buffers(lbm_ctx *c)
 {

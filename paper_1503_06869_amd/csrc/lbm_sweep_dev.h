@@ -4,15 +4,21 @@
 // wall and fiber bounce-back, and the momentum-exchange terms of a link.
 #pragma once
 #include "lbm_dev.h"
+#include <type_traits>
 
 namespace lbm {
 
 // ------------------------------------------------------------------ storage
+// Collision type R; a stored value (Raw) is read by raw() and converted by
+// val(), apart where the conversion must not wait for the load.
 template <typename S>
 struct St;
 template <>
 struct St<float> {
     using R = float;
+    using Raw = float;
+    static __device__ __forceinline__ Raw raw(const float *p, uint64_t i) { return p[i]; }
+    static __device__ __forceinline__ float val(Raw v, float) { return v; }
     static __device__ __forceinline__ float ld(const float *p, uint64_t i, float) { return p[i]; }
     static __device__ __forceinline__ void st(float *p, uint64_t i, float v, float)
     {
@@ -22,6 +28,9 @@ struct St<float> {
 template <>
 struct St<double> {
     using R = double;
+    using Raw = double;
+    static __device__ __forceinline__ Raw raw(const double *p, uint64_t i) { return p[i]; }
+    static __device__ __forceinline__ double val(Raw v, double) { return v; }
     static __device__ __forceinline__ double ld(const double *p, uint64_t i, double) { return p[i]; }
     static __device__ __forceinline__ void st(double *p, uint64_t i, double v, double)
     {
@@ -31,10 +40,10 @@ struct St<double> {
 template <>
 struct St<_Float16> {
     using R = float;
-    static __device__ __forceinline__ float ld(const _Float16 *p, uint64_t i, float inv)
-    {
-        return float(p[i]) * inv;
-    }
+    using Raw = _Float16;
+    static __device__ __forceinline__ Raw raw(const _Float16 *p, uint64_t i) { return p[i]; }
+    static __device__ __forceinline__ float val(Raw v, float inv) { return float(v) * inv; }
+    static __device__ __forceinline__ float ld(const _Float16 *p, uint64_t i, float inv) { return val(raw(p, i), inv); }
     static __device__ __forceinline__ void st(_Float16 *p, uint64_t i, float v, float scale)
     {
         __builtin_nontemporal_store(_Float16(v * scale), p + i);   // v_cvt_f16_f32: RNE
@@ -46,11 +55,13 @@ struct bf16s {
 template <>
 struct St<bf16s> {
     using R = float;
-    static __device__ __forceinline__ float ld(const bf16s *p, uint64_t i, float)
+    using Raw = uint16_t;
+    static __device__ __forceinline__ Raw raw(const bf16s *p, uint64_t i)
     {
-        const uint16_t *u = reinterpret_cast<const uint16_t *>(p);
-        return __uint_as_float(uint32_t(u[i]) << 16);
+        return reinterpret_cast<const uint16_t *>(p)[i];
     }
+    static __device__ __forceinline__ float val(Raw v, float) { return __uint_as_float(uint32_t(v) << 16); }
+    static __device__ __forceinline__ float ld(const bf16s *p, uint64_t i, float inv) { return val(raw(p, i), inv); }
     static __device__ __forceinline__ void st(bf16s *p, uint64_t i, float v, float)
     {
         uint32_t u = __float_as_uint(v);
@@ -186,9 +197,13 @@ __device__ __forceinline__ void stab_flush(const StabAcc<R> &sa, double *out)
 // lambda_e = -omega_e, lambda_o = -omega_o (Eq. LBMCollide).  With a body
 // force the velocity carries +g/2 and the odd part gains (1 - omega_o/2) 3 w rho0 c.g.
 // STAB: the equilibrium velocity is u - sa.ub, and j and the cell are counted.
-template <typename R, bool STAB = false>
+// The fused multiply-adds are written out, so that a cell's update has the
+// same bits in every kernel that it is compiled into; SPLIT rounds omega_e e
+// of the second value of a pair by itself.
+template <typename R, bool SPLIT, bool STAB>
 __device__ __forceinline__ void collide(R (&f)[Q], const Phys<R> &ph, R inv_rho0, StabAcc<R> *sa = nullptr)
 {
+#pragma clang fp contract(off)
     R drho = R(0), jx = R(0), jy = R(0), jz = R(0);
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
@@ -197,12 +212,11 @@ __device__ __forceinline__ void collide(R (&f)[Q], const Phys<R> &ph, R inv_rho0
         if (CY[q]) jy += CY[q] > 0 ? f[q] : -f[q];
         if (CZ[q]) jz += CZ[q] > 0 ? f[q] : -f[q];
     }
-    R ux = jx * inv_rho0, uy = jy * inv_rho0, uz = jz * inv_rho0;
-    if (ph.has_g) {
-        ux += R(0.5) * ph.g[0];
-        uy += R(0.5) * ph.g[1];
-        uz += R(0.5) * ph.g[2];
-    }
+    const R half = R(0.5), r0 = ph.rho0, we = ph.omega_e, wo = ph.omega_o;
+    const bool hg = ph.has_g != 0;
+    R ux = hg ? fma(jx, inv_rho0, half * ph.g[0]) : jx * inv_rho0;
+    R uy = hg ? fma(jy, inv_rho0, half * ph.g[1]) : jy * inv_rho0;
+    R uz = hg ? fma(jz, inv_rho0, half * ph.g[2]) : jz * inv_rho0;
     if constexpr (STAB) {
         sa->j[0] += jx;
         sa->j[1] += jy;
@@ -212,24 +226,22 @@ __device__ __forceinline__ void collide(R (&f)[Q], const Phys<R> &ph, R inv_rho0
         uy -= sa->ub[1];
         uz -= sa->ub[2];
     }
-    const R r0 = ph.rho0, we = ph.omega_e, wo = ph.omega_o;
-    const R base = drho - R(1.5) * r0 * (ux * ux + uy * uy + uz * uz);
-    f[0] = f[0] - we * (f[0] - R(wq(0)) * base);
+    const R uu = fma(uz, uz, fma(ux, ux, uy * uy));
+    const R base = fma(-(R(1.5) * r0), uu, drho);
+    f[0] = fma(-we, fma(-R(wq(0)), base, f[0]), f[0]);
 #pragma unroll
     for (int q = 1; q <= 9; ++q) {
         const R w = R(wq(q));
         const R cu = R(CX[q]) * ux + R(CY[q]) * uy + R(CZ[q]) * uz;
-        const R eeq = w * (base + R(4.5) * r0 * cu * cu);
+        const R eeq = w * fma(R(4.5) * r0 * cu, cu, base);
         const R oeq = R(3) * w * r0 * cu;
-        const R e = R(0.5) * (f[q] + f[q + 9]);
-        const R o = R(0.5) * (f[q] - f[q + 9]);
-        const R de = we * (e - eeq);
-        R dd = wo * (o - oeq);
-        if (ph.has_g)
-            dd -= (R(1) - R(0.5) * wo) * R(3) * w * r0 *
-                  (R(CX[q]) * ph.g[0] + R(CY[q]) * ph.g[1] + R(CZ[q]) * ph.g[2]);
-        f[q] = f[q] - de - dd;
-        f[q + 9] = f[q + 9] - de + dd;
+        const R e = fma(half, f[q] + f[q + 9], -eeq);
+        const R o = fma(half, f[q] - f[q + 9], -oeq);
+        const R T = (R(1) - half * wo) * R(3) * w * r0 *
+                    (R(CX[q]) * ph.g[0] + R(CY[q]) * ph.g[1] + R(CZ[q]) * ph.g[2]);
+        const R dd = hg ? fma(wo, o, -T) : wo * o;
+        f[q] = fma(-we, e, f[q]) - dd;
+        f[q + 9] = (SPLIT ? f[q + 9] - we * e : fma(-we, e, f[q + 9])) + dd;
     }
 }
 
@@ -288,6 +300,22 @@ __device__ __forceinline__ void link_terms(long long *acc, double ft, double w, 
     for (int k = 0; k < 6; ++k) acc[k] += fx(t[k], k);
 }
 
+// First element of a wall cell's slot: gathering (IN), slot q where the
+// population returns from a no-slip wall, else opp(refl(q, m)), m the
+// free-slip walls crossed; scattering, slot opp(q) where it bounces, else
+// refl(q, m).  m has only bits of nonzero components of c_q.
+template <int q, bool IN>
+__device__ __forceinline__ uint64_t slot_sel(int m, bool back, uint64_t qs)
+{
+    constexpr int M = (CX[q] ? 1 : 0) | (CY[q] ? 2 : 0) | (CZ[q] ? 4 : 0);
+    uint64_t s = uint64_t(IN ? opp(q) : q) * qs;
+    static_for<1, 8>([&](auto mc) {
+        constexpr int k = decltype(mc)::value;
+        if constexpr ((k & ~M) == 0) s = m == k ? uint64_t(IN ? opp(refl(q, k)) : refl(q, k)) * qs : s;
+    });
+    return back ? uint64_t(IN ? q : opp(q)) * qs : s;
+}
+
 // sink of the cells without fiber links
 struct NoLinks {
     template <int q, typename R>
@@ -316,94 +344,129 @@ struct NoLinks {
 // refl(q) of x + t, which no other cell touches in that sweep (the slot it
 // gathered from for the reverse link), so both sweeps stay in place.  A
 // link that crosses walls of both kinds bounces back.
+// The update is in two parts, the gather of a cell's populations and
+// everything after it, so that a loop over cells can gather the next cell
+// before it finishes this one (the slots of different cells are disjoint).
+struct CellPos {
+    uint32_t x, y, z;
+    uint32_t xo[3], yo[3], zo[3];   // offsets of the neighbours' coordinates (wrapped; planes shifted by one)
+    uint32_t own;
+};
+__device__ __forceinline__ CellPos cell_pos(const Geo &g, uint32_t cell)
+{
+    CellPos c;
+    c.z = fdiv(cell, g.dnxy);
+    const uint32_t rr = cell - c.z * g.nxy;
+    c.y = fdiv(rr, g.dnx);
+    c.x = rr - c.y * g.nx;
+    c.xo[0] = c.x == 0 ? g.nx - 1 : c.x - 1;
+    c.xo[1] = c.x;
+    c.xo[2] = c.x + 1 == g.nx ? 0 : c.x + 1;
+    c.yo[0] = (c.y == 0 ? g.ny - 1 : c.y - 1) * g.nx;
+    c.yo[1] = c.y * g.nx;
+    c.yo[2] = (c.y + 1 == g.ny ? 0 : c.y + 1) * g.nx;
+    c.zo[0] = (g.zper && c.z == 0 ? g.nz : c.z) * g.nxy;
+    c.zo[1] = (c.z + 1) * g.nxy;
+    c.zo[2] = (g.zper && c.z + 1 == g.nz ? 1 : c.z + 2) * g.nxy;
+    c.own = c.zo[1] + c.yo[1] + c.xo[1];
+    return c;
+}
+
+// the walls a cell lies at (x and y only with XYW)
+struct CellWalls {
+    bool lo, hi, x0, x1, y0, y1, zs;
+    bool any;   // a cell of the wave lies at a wall that changes slots
+};
+template <bool XYW>
+__device__ __forceinline__ CellWalls cell_walls(const Geo &g, const CellPos &c)
+{
+    CellWalls w{!g.zper && c.z == 0, !g.zper && c.z + 1 == g.nz, false, false, false, false, false, false};
+    if constexpr (XYW) {
+        w.x0 = g.xw && c.x == 0;
+        w.x1 = g.xw && c.x + 1 == g.nx;
+        w.y0 = g.yw && c.y == 0;
+        w.y1 = g.yw && c.y + 1 == g.ny;
+        w.zs = g.zs != 0;
+        // (of the z walls only free-slip ones change the slots)
+        w.any = __any(w.x0 || w.x1 || w.y0 || w.y1 || (w.zs && (w.lo || w.hi)));
+    }
+    return w;
+}
+
+template <typename S, bool ODD, bool XYW>
+__device__ __forceinline__ void gather_cell(const S *__restrict__ f, const Geo &g, const CellPos &c,
+                                            typename St<S>::Raw (&rv)[Q])
+{
+    const uint64_t qs = g.qstride;
+    CellWalls w{};
+    if constexpr (ODD && XYW) w = cell_walls<XYW>(g, c);
+    static_for<0, Q>([&](auto qc) {
+        constexpr int q = decltype(qc)::value;
+        if (!ODD) {
+            rv[q] = St<S>::raw(f, uint64_t(q) * qs + c.own);
+        } else {
+            if constexpr (XYW) {
+                if (w.any) {
+                    // walls crossed on the way in (a no-slip z wall: its
+                    // mailbox, a normal read); the source is selected, not
+                    // branched to, so that all loads are in flight together
+                    bool ix = (CX[q] > 0 && w.x0) || (CX[q] < 0 && w.x1);
+                    bool iy = (CY[q] > 0 && w.y0) || (CY[q] < 0 && w.y1);
+                    const bool oz = (CZ[q] > 0 && w.lo) || (CZ[q] < 0 && w.hi), iz = w.zs && oz;
+                    if (oz && !w.zs) ix = iy = false;
+                    const bool side_in = (ix && g.xw == 1) || (iy && g.yw == 1);
+                    const int m = (ix ? 1 : 0) | (iy ? 2 : 0) | (iz ? 4 : 0);
+                    uint32_t src = (iz ? c.zo[1] : c.zo[1 - CZ[q]]) + (iy ? c.yo[1] : c.yo[1 - CY[q]]) +
+                                   (ix ? c.xo[1] : c.xo[1 - CX[q]]);
+                    src = side_in ? c.own : src;
+                    rv[q] = St<S>::raw(f, slot_sel<q, true>(m, side_in, qs) + src);
+                    return;
+                }
+            }
+            const uint32_t src = c.zo[1 - CZ[q]] + c.yo[1 - CY[q]] + c.xo[1 - CX[q]];
+            rv[q] = St<S>::raw(f, uint64_t(opp(q)) * qs + src);
+        }
+    });
+}
+
 template <typename S, bool ODD, bool BND, bool STAB, bool XYW, typename Sink>
-__device__ __forceinline__ void update_cell(S *__restrict__ f, const Geo &g,
-                                            const Phys<typename St<S>::R> &ph, uint32_t cell,
-                                            uint32_t mask, Sink &sink, StabAcc<typename St<S>::R> *sa = nullptr)
+__device__ __forceinline__ void finish_cell(S *__restrict__ f, const Geo &g, const Phys<typename St<S>::R> &ph,
+                                            const CellPos &c, const typename St<S>::Raw (&rv)[Q], uint32_t mask, Sink &sink,
+                                            StabAcc<typename St<S>::R> *sa = nullptr)
 {
     using R = typename St<S>::R;
-    const uint32_t z = fdiv(cell, g.dnxy);
-    const uint32_t rr = cell - z * g.nxy;
-    const uint32_t y = fdiv(rr, g.dnx);
-    const uint32_t x = rr - y * g.nx;
-    const uint32_t xo[3] = {x == 0 ? g.nx - 1 : x - 1, x, x + 1 == g.nx ? 0 : x + 1};
-    const uint32_t yo[3] = {(y == 0 ? g.ny - 1 : y - 1) * g.nx, y * g.nx,
-                            (y + 1 == g.ny ? 0 : y + 1) * g.nx};
-    uint32_t zo[3];
-    if (g.zper) {
-        zo[0] = ((z == 0 ? g.nz - 1 : z - 1) + 1) * g.nxy;
-        zo[1] = (z + 1) * g.nxy;
-        zo[2] = ((z + 1 == g.nz ? 0 : z + 1) + 1) * g.nxy;
-    } else {
-        zo[0] = z * g.nxy;
-        zo[1] = (z + 1) * g.nxy;
-        zo[2] = (z + 2) * g.nxy;
-    }
     const uint64_t qs = g.qstride;
-    const R inv = ph.inv_scale, sc = ph.scale;
-    const bool wall_lo = !g.zper && z == 0;
-    const bool wall_hi = !g.zper && z + 1 == g.nz;
-    bool wx0 = false, wx1 = false, wy0 = false, wy1 = false, zs = false;
-    if constexpr (XYW) {
-        wx0 = g.xw && x == 0;
-        wx1 = g.xw && x + 1 == g.nx;
-        wy0 = g.yw && y == 0;
-        wy1 = g.yw && y + 1 == g.ny;
-        zs = g.zs != 0;
-    }
-    const uint32_t own = zo[1] + yo[1] + xo[1];
+    const R sc = ph.scale;
+    const CellWalls w = cell_walls<XYW>(g, c);
     R fv[Q];
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        if (!ODD) {
-            fv[q] = St<S>::ld(f, uint64_t(q) * qs + own, inv);
-        } else {
-            // walls crossed on the way in (a no-slip z wall: its mailbox, a normal read)
-            bool ix = false, iy = false, iz = false, side_in = false;
-            if constexpr (XYW) {
-                ix = (CX[q] > 0 && wx0) || (CX[q] < 0 && wx1);
-                iy = (CY[q] > 0 && wy0) || (CY[q] < 0 && wy1);
-                iz = zs && ((CZ[q] > 0 && wall_lo) || (CZ[q] < 0 && wall_hi));
-                const bool nsz = !zs && ((CZ[q] > 0 && wall_lo) || (CZ[q] < 0 && wall_hi));
-                if (nsz) ix = iy = false;
-                side_in = (ix && g.xw == 1) || (iy && g.yw == 1);
-            }
-            if (side_in) {
-                fv[q] = St<S>::ld(f, uint64_t(q) * qs + own, inv);
-            } else if (ix || iy || iz) {
-                const int m = (ix ? 1 : 0) | (iy ? 2 : 0) | (iz ? 4 : 0);
-                const uint32_t src = zo[1 - (iz ? 0 : CZ[q])] + yo[1 - (iy ? 0 : CY[q])] + xo[1 - (ix ? 0 : CX[q])];
-                fv[q] = St<S>::ld(f, uint64_t(opp(refl_sel(q, m))) * qs + src, inv);
-            } else {
-                const uint32_t src = zo[1 - CZ[q]] + yo[1 - CY[q]] + xo[1 - CX[q]];
-                fv[q] = St<S>::ld(f, uint64_t(opp(q)) * qs + src, inv);
-            }
-        }
-    }
-    collide<R, STAB>(fv, ph, R(1) / ph.rho0, sa);
-
+    for (int q = 0; q < Q; ++q) fv[q] = St<S>::val(rv[q], ph.inv_scale);
+    // the forms that round a pair's second value in two steps (collide)
+    constexpr bool split = BND || STAB || (ODD && (XYW || std::is_same_v<S, bf16s>));
+    collide<R, split, STAB>(fv, ph, R(1) / ph.rho0, sa);
     const R six_r0 = R(6) * ph.rho0;
     static_for<0, Q>([&](auto qc) {
         constexpr int q = decltype(qc)::value;
-        const uint32_t nb = zo[1 + CZ[q]] + yo[1 + CY[q]] + xo[1 + CX[q]];
-        const bool oz = (CZ[q] < 0 && wall_lo) || (CZ[q] > 0 && wall_hi);
-        const bool to_wall = oz && !zs;
+        const uint32_t nb = c.zo[1 + CZ[q]] + c.yo[1 + CY[q]] + c.xo[1 + CX[q]];
+        const bool oz = (CZ[q] < 0 && w.lo) || (CZ[q] > 0 && w.hi);
+        const bool to_wall = oz && !w.zs;
         bool to_side = false, to_slip = false;
         int slip_m = 0;
         if constexpr (XYW) {
-            const bool ox = (CX[q] < 0 && wx0) || (CX[q] > 0 && wx1);
-            const bool oy = (CY[q] < 0 && wy0) || (CY[q] > 0 && wy1);
+            const bool ox = (CX[q] < 0 && w.x0) || (CX[q] > 0 && w.x1);
+            const bool oy = (CY[q] < 0 && w.y0) || (CY[q] > 0 && w.y1);
             to_side = !to_wall && ((ox && g.xw == 1) || (oy && g.yw == 1));
             to_slip = !to_wall && !to_side && (ox || oy || oz);
             slip_m = (ox ? 1 : 0) | (oy ? 2 : 0) | (oz ? 4 : 0);
         }
         if constexpr (BND && q > 0) {
             const bool lk = ((mask >> q) & 1u) && !to_slip && !to_side;
-            sink.template link<q>(lk, fv[q], own, nb, x, y, z);
+            sink.template link<q>(lk, fv[q], c.own, nb, c.x, c.y, c.z);
             if (lk) return;
         }
         R out = fv[q];
         if (CX[q] != 0 && to_wall) {
+#pragma clang fp contract(off)
             const R uw = CZ[q] < 0 ? -ph.wall_u : ph.wall_u;
             out -= six_r0 * R(wq(q)) * R(CX[q]) * uw;
         }
@@ -428,21 +491,34 @@ __device__ __forceinline__ void update_cell(S *__restrict__ f, const Geo &g,
             // mailbox for z walls; normal streaming, side walls and
             // reflections: own slot
             if (to_wall) St<S>::st(f, uint64_t(q) * qs + nb, out, sc);
-            else St<S>::st(f, uint64_t(opp(q)) * qs + own, out, sc);
+            else St<S>::st(f, uint64_t(opp(q)) * qs + c.own, out, sc);
         } else {
-            if (to_slip) {
-                const uint32_t dst = zo[1 + ((slip_m & 4) ? 0 : CZ[q])] + yo[1 + ((slip_m & 2) ? 0 : CY[q])] +
-                                     xo[1 + ((slip_m & 1) ? 0 : CX[q])];
-                St<S>::st(f, uint64_t(refl_sel(q, slip_m)) * qs + dst, out, sc);
-            } else if (bounce) {
-                St<S>::st(f, uint64_t(opp(q)) * qs + own, out, sc);
-            } else {
-                St<S>::st(f, uint64_t(q) * qs + nb, out, sc);
+            if constexpr (XYW) {
+                if (w.any) {
+                    uint32_t dst = ((slip_m & 4) ? c.zo[1] : c.zo[1 + CZ[q]]) + ((slip_m & 2) ? c.yo[1] : c.yo[1 + CY[q]]) +
+                                   ((slip_m & 1) ? c.xo[1] : c.xo[1 + CX[q]]);
+                    dst = bounce ? c.own : dst;
+                    St<S>::st(f, slot_sel<q, false>(slip_m, bounce, qs) + dst, out, sc);
+                    return;
+                }
             }
+            if (bounce) St<S>::st(f, uint64_t(opp(q)) * qs + c.own, out, sc);
+            else St<S>::st(f, uint64_t(q) * qs + nb, out, sc);
         }
     });
     (void)six_r0;
     (void)sink;
+}
+
+template <typename S, bool ODD, bool BND, bool STAB, bool XYW, typename Sink>
+__device__ __forceinline__ void update_cell(S *__restrict__ f, const Geo &g, const Phys<typename St<S>::R> &ph,
+                                            uint32_t cell, uint32_t mask, Sink &sink,
+                                            StabAcc<typename St<S>::R> *sa = nullptr)
+{
+    typename St<S>::Raw rv[Q];
+    const CellPos c = cell_pos(g, cell);
+    gather_cell<S, ODD, XYW>(f, g, c, rv);
+    finish_cell<S, ODD, BND, STAB, XYW>(f, g, ph, c, rv, mask, sink, sa);
 }
 
 // The moving-obstacle bounce-back (Eq. LBMMovWall) of one fiber link from
