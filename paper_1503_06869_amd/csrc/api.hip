@@ -50,7 +50,8 @@ struct lbm_ctx {
     uint32_t *list_cell = nullptr, *list_mask = nullptr;
     uint32_t list_cap = 0;
     DevCounters *ctr = nullptr;
-    uint32_t remap_grid = 0, bnd_grid = 0, sweep_grid = 0;
+    uint32_t bnd_grid = 0, sweep_grid = 0;
+    uint32_t nbulk = 0;       // small lattice: waves of the sweep inside the boundary launch
     int64_t steps = 0;
     int64_t device_bytes = 0;
     // graph of one even + one odd step
@@ -136,7 +137,7 @@ static lbm_status alloc_stab(lbm_ctx *c)
     if (!c->p.stabilize) return LBM_OK;
     dfree(c->stab);
     dfree(c->cov);
-    const uint32_t nslot = std::max(stab_slots_saved(c), c->sweep_grid + c->bnd_grid);
+    const uint32_t nslot = std::max(stab_slots_saved(c), std::max(c->sweep_grid, c->nbulk) + c->bnd_grid);
     HIPCHK(c, dalloc(c, &c->stab, size_t(STAB_HEAD) + 4 * size_t(nslot)));
     HIPCHK(c, hipMemsetAsync(c->stab, 0, (size_t(STAB_HEAD) + 4 * size_t(nslot)) * sizeof(double), c->st));
     // cells changing owner in one remap: fewer than the boundary list holds
@@ -287,7 +288,6 @@ static lbm_status upload_particles(lbm_ctx *c)
     // so extra passes add latency, not throughput; waves beyond the list's
     // end return at once).  A segment holds about 1.2 shells.
     c->bpf = std::max(1, std::min(64, int(std::ceil(1.35 * maxsurf / 64.0))));
-    c->remap_grid = uint32_t(np * c->nslab);
     c->bnd_grid = uint32_t(np * c->bpf);
     std::vector<PState> hs(np);
     int64_t off = 0;
@@ -356,7 +356,8 @@ static lbm_status check_device_errors(lbm_ctx *c)
     return LBM_OK;
 }
 
-// One time step as a two-branch graph of kernels:
+// One time step as a two-branch graph of kernels (small lattices: one branch,
+// with the bulk sweep in the boundary launch):
 //   st : bulk sweep -----------------------------------------------------------+
 //   st2: boundary cells and their links' sums -> rigid -> map and list ---------+--> next step
 // The bulk sweep touches only slots of bulk cells; the boundary update, the
@@ -406,6 +407,25 @@ static void launch_one_step(lbm_ctx *c, int64_t step_index, bool with_events, hi
         e = launch_closure_step(c->sk, odd, c->f, c->flags[step_index & 1], c->pid, cur, c->pc, c->np, c->g, c->ph,
                                 gamma, md, c->p.rho0, nu, c->corr, c->cstats, c->st);
     }
+    PartData pd = part_data(c, cur, next);
+    if (stab) {
+        pd.cov = c->cov;
+        pd.cov_cap = c->cov_cap;
+    }
+    if (c->nbulk && !with_events) {
+        // small lattice: one branch, the sweep inside the boundary launch
+        if (e == hipSuccess)
+            e = launch_boundary(c->sk, odd, c->f, c->g, c->ph, b, c->st, su, sp, c->flags[step_index & 1], c->nbulk);
+        if (e == hipSuccess) e = launch_rigid(pd, c->g, c->st);
+        if (e == hipSuccess)
+            e = launch_map(c->sk, !odd, c->f, c->pid, c->flags[(step_index + 1) & 1], c->list_cell, c->list_mask, pd,
+                           c->g, c->p.rho0, c->scale, true, c->st);
+        if (e == hipSuccess && stab)
+            e = launch_stab_update(c->sk, !odd, c->f, c->g, c->ph, c->stab, c->nbulk + c->bnd_grid, c->cov, c->cov_cap,
+                                   c->st);
+        if (e != hipSuccess && *err == hipSuccess) *err = e;
+        return;
+    }
     if (e == hipSuccess) e = hipEventRecord(c->ev_fork, c->st);
     if (e == hipSuccess) e = hipStreamWaitEvent(c->st2, c->ev_fork, 0);
     // Launch order of the two branches (measured): the branch expected to be
@@ -418,17 +438,12 @@ static void launch_one_step(lbm_ctx *c, int64_t step_index, bool with_events, hi
     // fibers: the particle branch is the longer one).
     const bool bulk_first = c->sweep_grid <= 1024u && uint64_t(c->g.ncell) >= 32ull * c->list_cap;
     if (e == hipSuccess && !bulk_first)
-        e = launch_boundary(c->sk, odd, c->f, c->g, c->ph, b, c->st2, su, sp_b);
+        e = launch_boundary(c->sk, odd, c->f, c->g, c->ph, b, c->st2, su, sp_b, nullptr, 0u);
     if (e == hipSuccess)
         e = launch_sweep(c->sk, odd, c->f, c->flags[step_index & 1], c->g, c->ph, c->sweep_grid, c->st,
                          with_events ? e0 : nullptr, with_events ? e1 : nullptr, su, sp);
     if (e == hipSuccess && bulk_first)
-        e = launch_boundary(c->sk, odd, c->f, c->g, c->ph, b, c->st2, su, sp_b);
-    PartData pd = part_data(c, cur, next);
-    if (stab) {
-        pd.cov = c->cov;
-        pd.cov_cap = c->cov_cap;
-    }
+        e = launch_boundary(c->sk, odd, c->f, c->g, c->ph, b, c->st2, su, sp_b, nullptr, 0u);
     if (e == hipSuccess) e = launch_rigid(pd, c->g, c->st2);
     if (e == hipSuccess)
         e = launch_map(c->sk, !odd, c->f, c->pid, c->flags[(step_index + 1) & 1], c->list_cell, c->list_mask, pd, c->g,
@@ -569,6 +584,12 @@ lbm_status lbm_create(const lbm_params *p, lbm_ctx **out)
     // not start at addresses that are equal modulo a large power of two.
     const uint64_t pad = p->q_pad >= 0 ? uint64_t(p->q_pad) : 1088u;
     g.qstride = uint64_t(p->nz + 2) * g.nxy + pad;
+    // small lattices (with the automatic sweep grid) take a step in one branch,
+    // the sweep inside the boundary launch.  Measured per step in one and in
+    // two branches (FP32; FP16 alike): 32^3 with one fiber 29 and 38 us, 64^3
+    // with six 35 and 44, 96^3 with twelve 56 and 60, 112^3 with sixteen 63 and
+    // 71, 128^3 with two 71 and 70, 144^3 with four 93 and 85.
+    if (p->sweep_grid == 0 && g.ncell <= 1750000u) c->nbulk = (g.ncell + 63u) / 64u;
     g.dnx = make_fastdiv(g.nx);
     g.dnxy = make_fastdiv(g.nxy);
     g.zper = p->z_periodic ? 1 : 0;

@@ -100,25 +100,50 @@ __device__ __forceinline__ long long wave_totals(long long (&v)[32])
     return v[0] + __shfl_xor(v[0], 1, 64);
 }
 
+// 4 sums over the wave to out
+__device__ __forceinline__ void wave_sum4(const double (&v)[4], double *out)
+{
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        double x = v[k];
+        for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+        if (threadIdx.x == 0) out[k] = x;
+    }
+}
+
 // Register budget: the bulk sweep keeps 2 waves of 80 VGPRs per SIMD
 // resident for its whole grid-stride run; this kernel runs beside it with
 // up to 2 waves per SIMD, so it must stay within 176 VGPRs, or bulk
 // workgroups launched after it start late and the sweep stretches.
 // Grid: np * bpf waves; wave (fiber p, part j) takes entries 64 j, 64 (j +
 // bpf), ... of the fiber's list segment.
-// STAB: momentum stabilization (mean velocity stab[0..2]; wave blk writes
-// its sums to part[4 blk .. 4 blk + 3]).  XYW: walls on the x and/or y
-// faces.
+// nbulk further waves take 64 cells each of the bulk sweep.  STAB: momentum
+// stabilization (mean velocity stab[0..2]; every wave writes its sums to a
+// slot of part, the bulk waves first).  XYW: walls on the x and/or y faces.
 template <typename S, bool ODD, bool STAB, bool XYW>
 __global__ __launch_bounds__(64, 2) void k_boundary(S *__restrict__ f, Geo g, Phys<typename St<S>::R> ph, BndData b,
-                                                    const double *stab, double *part)
+                                                    const double *stab, double *part,
+                                                    const uint8_t *__restrict__ flags, uint32_t nbulk)
 {
     using R = typename St<S>::R;
     __shared__ uint32_t s_code[QCAP];
     __shared__ R s_val[QCAP];
     __shared__ uint32_t s_cell[64];
-    const int p = int(blockIdx.x) / b.bpf, j = int(blockIdx.x) % b.bpf;   // wave-uniform
-    const uint32_t lane = threadIdx.x;
+    const uint32_t lane = threadIdx.x, nb = uint32_t(b.np * b.bpf);
+    StabAcc<R> st;
+    if constexpr (STAB) stab_begin(st, stab);
+    if (blockIdx.x >= nb) {   // wave-uniform
+        const uint32_t k = xcd_block(blockIdx.x - nb, nbulk), cell = k * 64u + lane;
+        NoLinks none;
+        if (cell < g.ncell && !flags[cell]) update_cell<S, ODD, false, STAB, XYW>(f, g, ph, cell, 0u, none, &st);
+        if constexpr (STAB) {
+            const double t[4] = {double(st.j[0]), double(st.j[1]), double(st.j[2]), double(st.n)};
+            wave_sum4(t, part + 4 * size_t(k));
+        }
+        return;
+    }
+    const int blk = int(xcd_block(blockIdx.x, nb));   // a fiber's waves share one XCD's L2
+    const int p = blk / b.bpf, j = blk % b.bpf;       // wave-uniform
     const uint32_t cap = b.seg_cap[p], off = b.seg_off[p];
     // the fiber's state (home links) and the reference point of its sums
     double X[3], V[3], W[3];
@@ -133,9 +158,7 @@ __global__ __launch_bounds__(64, 2) void k_boundary(S *__restrict__ f, Geo g, Ph
     const double r0 = double(ph.rho0);
     long long fm[6] = {0, 0, 0, 0, 0, 0}, sb[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0}, sc[6] = {0, 0, 0, 0, 0, 0};
     int32_t sa[6] = {0, 0, 0, 0, 0, 0};
-    StabAcc<R> st;
     double lj[3] = {0.0, 0.0, 0.0};   // momentum change of the links (stabilization)
-    if constexpr (STAB) stab_begin(st, stab);
     for (uint32_t e0 = uint32_t(j) * 64u; e0 < n; e0 += uint32_t(b.bpf) * 64u) {
         LinkQueue<R> queue{s_code, s_val, 0u, lane};
         if (e0 + lane < n) {
@@ -215,45 +238,41 @@ __global__ __launch_bounds__(64, 2) void k_boundary(S *__restrict__ f, Geo g, Ph
     if ((lane & 1u) == 0u && lane < 2u * NACC && tot)
         atomicAdd(reinterpret_cast<unsigned long long *>(b.mea + size_t(p) * NACC + (lane >> 1)), (unsigned long long)tot);
     if constexpr (STAB) {
-        double t[4] = {double(st.j[0]) + lj[0], double(st.j[1]) + lj[1], double(st.j[2]) + lj[2], double(st.n)};
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            for (int o = 32; o > 0; o >>= 1) t[k] += __shfl_xor(t[k], o, 64);
-        if (lane == 0)
-            for (int k = 0; k < 4; ++k) part[4 * size_t(blockIdx.x) + k] = t[k];
+        const double t[4] = {double(st.j[0]) + lj[0], double(st.j[1]) + lj[1], double(st.j[2]) + lj[2], double(st.n)};
+        wave_sum4(t, part + 4 * size_t(nbulk + uint32_t(blk)));
     }
 }
 
 template <typename S>
 static hipError_t boundary_t(bool odd, void *f, const Geo &g, const Phys<double> &ph, const BndData &b,
-                             hipStream_t st, const double *stab, double *part)
+                             hipStream_t st, const double *stab, double *part, const uint8_t *flags, uint32_t nbulk)
 {
     using R = typename St<S>::R;
     const Phys<R> p = cast_phys<R>(ph);
-    const dim3 grid(uint32_t(b.np * b.bpf)), bl(64);
+    const dim3 grid(uint32_t(b.np * b.bpf) + nbulk), bl(64);
     const int mode = (odd ? 1 : 0) | (stab ? 2 : 0) | ((g.xw || g.yw || g.zs) ? 4 : 0);
     switch (mode) {
-    case 0: hipLaunchKernelGGL((k_boundary<S, false, false, false>), grid, bl, 0, st, (S *)f, g, p, b, stab, part); break;
-    case 1: hipLaunchKernelGGL((k_boundary<S, true, false, false>), grid, bl, 0, st, (S *)f, g, p, b, stab, part); break;
-    case 2: hipLaunchKernelGGL((k_boundary<S, false, true, false>), grid, bl, 0, st, (S *)f, g, p, b, stab, part); break;
-    case 3: hipLaunchKernelGGL((k_boundary<S, true, true, false>), grid, bl, 0, st, (S *)f, g, p, b, stab, part); break;
-    case 4: hipLaunchKernelGGL((k_boundary<S, false, false, true>), grid, bl, 0, st, (S *)f, g, p, b, stab, part); break;
-    case 5: hipLaunchKernelGGL((k_boundary<S, true, false, true>), grid, bl, 0, st, (S *)f, g, p, b, stab, part); break;
-    case 6: hipLaunchKernelGGL((k_boundary<S, false, true, true>), grid, bl, 0, st, (S *)f, g, p, b, stab, part); break;
-    default: hipLaunchKernelGGL((k_boundary<S, true, true, true>), grid, bl, 0, st, (S *)f, g, p, b, stab, part); break;
+    case 0: hipLaunchKernelGGL((k_boundary<S, false, false, false>), grid, bl, 0, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
+    case 1: hipLaunchKernelGGL((k_boundary<S, true, false, false>), grid, bl, 0, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
+    case 2: hipLaunchKernelGGL((k_boundary<S, false, true, false>), grid, bl, 0, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
+    case 3: hipLaunchKernelGGL((k_boundary<S, true, true, false>), grid, bl, 0, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
+    case 4: hipLaunchKernelGGL((k_boundary<S, false, false, true>), grid, bl, 0, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
+    case 5: hipLaunchKernelGGL((k_boundary<S, true, false, true>), grid, bl, 0, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
+    case 6: hipLaunchKernelGGL((k_boundary<S, false, true, true>), grid, bl, 0, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
+    default: hipLaunchKernelGGL((k_boundary<S, true, true, true>), grid, bl, 0, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
     }
     return hipGetLastError();
 }
 
 hipError_t launch_boundary(int sk, bool odd, void *f, const Geo &g, const Phys<double> &ph, const BndData &b,
-                           hipStream_t st, const double *stab, double *part)
+                           hipStream_t st, const double *stab, double *part, const uint8_t *flags, uint32_t nbulk)
 {
     if (b.np <= 0 || b.bpf <= 0) return hipSuccess;
     switch (sk) {
-    case S_F32: return boundary_t<float>(odd, f, g, ph, b, st, stab, part);
-    case S_F16: return boundary_t<_Float16>(odd, f, g, ph, b, st, stab, part);
-    case S_BF16: return boundary_t<bf16s>(odd, f, g, ph, b, st, stab, part);
-    default: return boundary_t<double>(odd, f, g, ph, b, st, stab, part);
+    case S_F32: return boundary_t<float>(odd, f, g, ph, b, st, stab, part, flags, nbulk);
+    case S_F16: return boundary_t<_Float16>(odd, f, g, ph, b, st, stab, part, flags, nbulk);
+    case S_BF16: return boundary_t<bf16s>(odd, f, g, ph, b, st, stab, part, flags, nbulk);
+    default: return boundary_t<double>(odd, f, g, ph, b, st, stab, part, flags, nbulk);
     }
 }
 

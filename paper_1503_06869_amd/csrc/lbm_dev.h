@@ -268,10 +268,11 @@ constexpr uint32_t STAB_SCAN_GRID = 1024;
 hipError_t launch_sweep(int sk, bool odd, void *f, const uint8_t *flags, const Geo &g, const Phys<double> &ph,
                         uint32_t sweep_grid, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1, const double *stab,
                         double *part);
-// boundary cells of the list (update, F0, M0) and the integer A, B, C sums
-// of their links, one launch (boundary.hip); stab and part as for the sweep
+// boundary cells of the list (update, links, momentum exchange), one launch
+// (boundary.hip); stab as for the sweep.  nbulk > 0: the bulk sweep too, 64
+// cells per wave (flags; part: nbulk slots of the bulk waves first)
 hipError_t launch_boundary(int sk, bool odd, void *f, const Geo &g, const Phys<double> &ph, const BndData &b,
-                           hipStream_t st, const double *stab, double *part);
+                           hipStream_t st, const double *stab, double *part, const uint8_t *flags, uint32_t nbulk);
 hipError_t launch_decode(int sk, bool swapped, const void *f, const uint8_t *flags,
                          const int32_t *pid, const PState *ps, const Geo &g, const Phys<double> &ph,
                          void *rho, void *u, double *fout, hipStream_t st);

@@ -290,7 +290,8 @@ __global__ __launch_bounds__(256) void k_map(S *__restrict__ f, int32_t *__restr
                                              double rho0, double scale, int advance)
 {
     const int ns = pd.nslab;
-    const int p = blockIdx.x / ns, sl = blockIdx.x % ns;
+    const int blk = int(xcd_block(blockIdx.x, gridDim.x));   // a fiber's blocks share one XCD's L2
+    const int p = blk / ns, sl = blk % ns;
     __shared__ NbrStage sh;
     __shared__ uint32_t s_cell[LSTAGE], s_mask[LSTAGE];
     __shared__ uint32_t s_n, s_base;
