@@ -3,21 +3,25 @@
 // the training loop.  The per-step closure (features, one-sample forward,
 // correction in one launch) is in features.hip.
 //
-// Work layout.  A workgroup of 256 threads takes a tile of 32 samples: the
-// tile's inputs, both hidden layers and the BF16 weights sit in LDS; thread
-// (j, g) owns output unit j of a layer for samples g, g+4, ... (so a wave
-// reads one input value per step, broadcast from LDS).  The gradient kernel
-// runs a fixed grid; workgroup b accumulates the weight gradients of its
-// tiles b, b+G, ... in its own slice of a partial buffer, and a reduction
-// kernel adds the slices in order b = 0..G-1, so the gradient is the same
-// on every run.  These products are tiny (about 20k multiply-adds per
-// sample), far from the matrix cores' break-even size, and are written as
-// plain FP32 FMA loops.
+// Work layout.  One wave takes a sample through the network and back: lane j
+// owns unit j of a hidden layer, the BF16 weights sit in the workgroup's LDS,
+// and the activations stay in registers (a layer reads them lane by lane as
+// scalar operands), so samples need no barrier.  A gradient is three launches: the waves leave every
+// sample's activations and deltas in a work buffer (2 KiB a sample); the
+// products delta x activation, one tile of 32 samples a workgroup and a few
+// rows of a weight matrix each, go to a partial buffer; a reduction adds the
+// partials in order.  Partial b holds the tiles b, b + 64, ... in that order,
+// so the gradient is the same on every run.  The products are tiny (about 20k
+// multiply-adds a sample, in FP32): what bounds a training batch is the chain
+// of short dependent kernels, not the matrix units.  Measured, batch of 256:
+// gradient and update 20 us (105 with one workgroup per tile of 32 samples
+// doing all of it, eight workgroups on the card).
 #include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "lbm_mlp_dev.h"
@@ -25,6 +29,12 @@
 namespace lbm {
 
 constexpr int TILE = 32, MB = 256, GRAD_BLOCKS = 64;
+constexpr int ROWS_MAX = 4 * GRAD_BLOCKS * TILE;   // samples of one pass through the work buffer (16 MiB)
+constexpr int ROW_GRID = 768;                      // resident workgroups of k_mlp_rows: three a CU
+// a sample in the work buffer: normalised inputs and a one (the bias column),
+// both hidden activations, dL/dz of both layers, dL/dy
+constexpr int RX = 0, RH1 = 248, RH2 = RH1 + NH, RD1 = RH2 + NH, RD2 = RD1 + NH, RDY = RD2 + NH, ROW = 512;
+static_assert(RDY + NO <= ROW && RX + NI < RH1, "work row");
 
 __host__ __device__ inline uint16_t to_bf16(float v)
 {
@@ -40,235 +50,236 @@ __device__ __forceinline__ float gelu_d(float z)
     return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) + z * 0.39894228040143268f * expf(-0.5f * z * z);
 }
 
-struct MlpTile {
-    uint16_t w1[NH * NI];
-    uint16_t w2[NH * NH];
-    uint16_t w3[NO * NH];
-    float b[NH + NH + NO];
-    float x[TILE][NI];
-    float z1[TILE][NH], h1[TILE][NH];
-    float z2[TILE][NH], h2[TILE][NH];
-    float y[TILE][NO];
-    float dy[TILE][NO];
-    float d2[TILE][NH];   // dL/dz2
-    float d1[TILE][NH];   // dL/dz1
+// v of lane i, as a scalar operand
+__device__ __forceinline__ float lane_val(float v, int i)
+{
+    return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), i));
+}
+
+// acc + sum over i < NH of w[i] v(lane i) in order; w: 64 BF16 values
+__device__ __forceinline__ float dot64(const uint4 (&w)[NH / 8], float v, float acc)
+{
+#pragma unroll
+    for (int k = 0; k < NH / 8; ++k) {
+        const uint32_t u[4] = {w[k].x, w[k].y, w[k].z, w[k].w};
+#pragma unroll
+        for (int l = 0; l < 4; ++l) {
+            acc = fmaf(__uint_as_float(u[l] << 16), lane_val(v, 8 * k + 2 * l), acc);
+            acc = fmaf(__uint_as_float(u[l] & 0xFFFF0000u), lane_val(v, 8 * k + 2 * l + 1), acc);
+        }
+    }
+    return acc;
+}
+
+// Samples first + r (through idx if given), r < n.  !GRAD: y = the outputs
+// times out_scale.  GRAD: the work rows r < nrow (zero rows from n on) and the
+// workgroup's sum of squared errors, added to lpart[b] if add.
+// Bound by a sample's serial chain (247 + 64 + 64 multiply-adds forward, 64
+// back, each with its lane-to-scalar read) and the copy of the weights to LDS
+// when there are few: 13 us for 256 samples; 37 us for 8192 forward (93 and
+// 70 us with a layer's activations in LDS and 32 samples to a workgroup).
+template <bool GRAD>
+__global__ __launch_bounds__(MB, 3) void k_mlp_rows(const uint16_t *__restrict__ wb, const float *__restrict__ x,
+                                                 const float *__restrict__ t, const int32_t *__restrict__ idx,
+                                                 int first, int n, int nrow, const float *__restrict__ mean,
+                                                 const float *__restrict__ inv_std,
+                                                 const float *__restrict__ out_scale, float gscale,
+                                                 float *__restrict__ y, float *__restrict__ work,
+                                                 double *__restrict__ lpart, int add)
+{
+    __shared__ alignas(16) uint16_t w[(NP + 7) / 8 * 8];
+    __shared__ double sl[MB / 64];
+    static_assert(OW2 % 8 == 0 && OW3 % 8 == 0, "16-byte rows of w2 and w3");
+    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (int i = threadIdx.x; i < NP / 8; i += MB)
+        reinterpret_cast<uint4 *>(w)[i] = reinterpret_cast<const uint4 *>(wb)[i];
+    if (threadIdx.x < NP % 8) w[NP / 8 * 8 + threadIdx.x] = wb[NP / 8 * 8 + threadIdx.x];
+    __syncthreads();
+    const int o = lane < NO ? lane : 0;
+    uint4 w2[NH / 8];   // row `lane` of w2
+#pragma unroll
+    for (int k = 0; k < NH / 8; ++k) w2[k] = *reinterpret_cast<const uint4 *>(&w[OW2 + lane * NH + 8 * k]);
+    const float b1 = bf(w[OB1 + lane]), b2 = bf(w[OB2 + lane]), b3 = bf(w[OB3 + o]);
+    double lsum = 0.0;
+    for (int r = blockIdx.x * (MB / 64) + wid; r < nrow; r += gridDim.x * (MB / 64)) {   // wave-uniform
+        float *row = GRAD ? work + size_t(r) * ROW : nullptr;
+        if (GRAD && r >= n) {
+            const float4 z = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            reinterpret_cast<float4 *>(row)[lane] = z;
+            reinterpret_cast<float4 *>(row)[64 + lane] = z;
+            continue;
+        }
+        const int src = idx ? idx[first + r] : first + r;
+        constexpr int NX = (NI + 63) / 64;
+        float xv[NX];   // input lane + 64 k; a one in column NI
+#pragma unroll
+        for (int k = 0; k < NX; ++k) {
+            const int i = lane + 64 * k;
+            xv[k] = i < NI ? (x[size_t(src) * NI + i] - mean[i]) * inv_std[i] : 1.0f;
+        }
+        float z1 = b1;
+#pragma unroll
+        for (int k = 0; k < NX; ++k) {
+            constexpr int last = NI - 64 * (NX - 1);
+            asm volatile("" ::: "memory");   // the weights of 64 columns at a time in registers
+            const uint16_t *wr = &w[OW1 + lane * NI + 64 * k];
+#pragma unroll
+            for (int i = 0; i < 64; ++i)
+                if (k < NX - 1 || i < last) z1 = fmaf(bf(wr[i]), lane_val(xv[k], i), z1);
+        }
+        const float h1 = gelu(z1);
+        const float z2 = dot64(w2, h1, b2), h2 = gelu(z2);
+        asm volatile("" ::: "memory");
+        uint4 w3[NH / 8];
+#pragma unroll
+        for (int k = 0; k < NH / 8; ++k) w3[k] = *reinterpret_cast<const uint4 *>(&w[OW3 + o * NH + 8 * k]);
+        const float out = dot64(w3, h2, b3);
+        if constexpr (!GRAD) {
+            if (lane < NO) y[size_t(r) * NO + lane] = out * out_scale[lane];
+        } else {
+            const float d = lane < NO ? out - t[size_t(src) * NO + lane] : 0.0f, dy = gscale * d;
+            lsum += double(d) * double(d);
+            float a = 0.0f;
+#pragma unroll
+            for (int k = 0; k < NO; ++k) a = fmaf(bf(w[OW3 + k * NH + lane]), lane_val(dy, k), a);
+            const float d2 = a * gelu_d(z2);
+            a = 0.0f;
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int j = 0; j < NH; ++j) a = fmaf(bf(w[OW2 + j * NH + lane]), lane_val(d2, j), a);
+#pragma unroll
+            for (int k = 0; k < NX; ++k)
+                if (lane + 64 * k < RH1) row[RX + lane + 64 * k] = xv[k];
+            row[RH1 + lane] = h1;
+            row[RH2 + lane] = h2;
+            row[RD1 + lane] = a * gelu_d(z1);
+            row[RD2 + lane] = d2;
+            if (lane < ROW - RDY) row[RDY + lane] = dy;
+        }
+    }
+    if constexpr (GRAD) {
+        for (int d = 32; d > 0; d >>= 1) lsum += __shfl_xor(lsum, d, 64);
+        if (lane == 0) sl[wid] = lsum;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double v = add ? lpart[blockIdx.x] : 0.0;
+            for (int k = 0; k < MB / 64; ++k) v += sl[k];
+            lpart[blockIdx.x] = v;
+        }
+    }
+}
+
+// Workgroups of k_mlp_prod along x: four rows of dW1 each, sixteen of dW2,
+// and one for dW3 and the biases of the layers after the first.
+constexpr int PROD_W1 = NH / 4, PROD_W2 = NH / 16, PROD_GRID = PROD_W1 + PROD_W2 + 1;
+
+// The gradient's products over the tiles b, b + GRAD_BLOCKS, ... of the work
+// rows (b = blockIdx.y), each tile's sum from zero, into part[b] (added to
+// what is there if add).  A lane owns a column: its activations are coalesced
+// loads, all 32 of a tile in flight, and the deltas of the rows are scalar.
+// Bound by one trip to memory and the launch: 4 us for 8 tiles.
+__global__ __launch_bounds__(MB) void k_mlp_prod(const float *__restrict__ work, int ntile, float *__restrict__ part,
+                                                 int add)
+{
+    float *gp = part + size_t(blockIdx.y) * NP;
+    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    auto put = [&](int p, float v) { gp[p] = (add ? gp[p] : 0.0f) + v; };
+    // NR rows of deltas from offset d against the column at offset c
+    auto prod = [&](auto nr, int d, int c, float *g) {
+        constexpr int NR = decltype(nr)::value;
+#pragma unroll
+        for (int k = 0; k < NR; ++k) g[k] = 0.0f;
+        for (int tl = blockIdx.y; tl < ntile; tl += GRAD_BLOCKS) {
+            const float *w = work + size_t(tl) * TILE * ROW;
+            float a[NR], v[TILE];
+#pragma unroll
+            for (int k = 0; k < NR; ++k) a[k] = 0.0f;
+#pragma unroll
+            for (int r = 0; r < TILE; ++r) v[r] = w[r * ROW + c];
+#pragma unroll
+            for (int r = 0; r < TILE; ++r)
+#pragma unroll
+                for (int k = 0; k < NR; ++k) a[k] = fmaf(w[r * ROW + d + k], v[r], a[k]);
+#pragma unroll
+            for (int k = 0; k < NR; ++k) g[k] += a[k];
+        }
+    };
+    const int bx = blockIdx.x;
+    if (bx < PROD_W1) {
+        const int j = bx * 4, i = threadIdx.x;
+        if (i > NI) return;   // column NI: the bias
+        float g[4];
+        prod(std::integral_constant<int, 4>{}, RD1 + j, RX + i, g);
+        for (int k = 0; k < 4; ++k) put(i < NI ? OW1 + (j + k) * NI + i : OB1 + j + k, g[k]);
+    } else if (bx < PROD_W1 + PROD_W2) {
+        const int j = (bx - PROD_W1) * 16 + wid * 4;
+        float g[4];
+        prod(std::integral_constant<int, 4>{}, RD2 + j, RH1 + lane, g);
+        for (int k = 0; k < 4; ++k) put(OW2 + (j + k) * NH + lane, g[k]);
+    } else if (wid == 0) {
+        float g[NO];
+        prod(std::integral_constant<int, NO>{}, RDY, RH2 + lane, g);
+        for (int k = 0; k < NO; ++k) put(OW3 + k * NH + lane, g[k]);
+    } else if (wid == 1 || (wid == 2 && lane < NO)) {   // a bias: the deltas against the ones
+        float g = 0.0f;
+        for (int tl = blockIdx.y; tl < ntile; tl += GRAD_BLOCKS) {
+            const float *w = work + size_t(tl) * TILE * ROW + (wid == 1 ? RD2 : RDY) + lane;
+            float a = 0.0f;
+#pragma unroll
+            for (int r = 0; r < TILE; ++r) a += w[r * ROW];
+            g += a;
+        }
+        put((wid == 1 ? OB2 : OB3) + lane, g);
+    }
+}
+
+struct AdamArgs {
+    float *w, *m, *v;
+    uint16_t *wb;
+    float lr, b1, b2, eps, c1, c2;   // c1, c2: the bias corrections 1 - b^t
 };
 
-__device__ void load_weights(const uint16_t *wb, MlpTile &s)
+// Adam on the FP32 master: parameter p with gradient gg
+__device__ __forceinline__ void adam_one(const AdamArgs &a, int p, float gg)
 {
-    for (int i = threadIdx.x; i < NH * NI; i += MB) s.w1[i] = wb[OW1 + i];
-    for (int i = threadIdx.x; i < NH * NH; i += MB) s.w2[i] = wb[OW2 + i];
-    for (int i = threadIdx.x; i < NO * NH; i += MB) s.w3[i] = wb[OW3 + i];
-    for (int i = threadIdx.x; i < NH; i += MB) {
-        s.b[i] = bf(wb[OB1 + i]);
-        s.b[NH + i] = bf(wb[OB2 + i]);
-    }
-    if (threadIdx.x < NO) s.b[2 * NH + threadIdx.x] = bf(wb[OB3 + threadIdx.x]);
+    const float mm = a.b1 * a.m[p] + (1.0f - a.b1) * gg;
+    const float vv = a.b2 * a.v[p] + (1.0f - a.b2) * gg * gg;
+    a.m[p] = mm;
+    a.v[p] = vv;
+    const float mh = mm / a.c1, vh = vv / a.c2;
+    const float nw = a.w[p] - a.lr * mh / (sqrtf(vh) + a.eps);
+    a.w[p] = nw;
+    a.wb[p] = to_bf16(nw);
 }
 
-// inputs of samples base .. base+cnt-1 (through idx if given), normalised
-__device__ void load_inputs(const float *x, const int32_t *idx, int base, int cnt, const float *mean,
-                            const float *inv_std, MlpTile &s)
-{
-    for (int e = threadIdx.x; e < TILE * NI; e += MB) {
-        const int r = e / NI, i = e - r * NI;
-        float v = 0.0f;
-        if (r < cnt) {
-            const int src = idx ? idx[base + r] : base + r;
-            v = (x[size_t(src) * NI + i] - mean[i]) * inv_std[i];
-        }
-        s.x[r][i] = v;
-    }
-}
-
-// forward pass of the tile (all TILE rows; rows past cnt hold zeros)
-__device__ void forward_tile(MlpTile &s)
-{
-    __syncthreads();
-    const int j = threadIdx.x & 63, g = threadIdx.x >> 6;
-    {
-        float acc[TILE / 4];
-        for (int k = 0; k < TILE / 4; ++k) acc[k] = s.b[j];
-        for (int i = 0; i < NI; ++i) {
-            const float w = bf(s.w1[j * NI + i]);
-#pragma unroll
-            for (int k = 0; k < TILE / 4; ++k) acc[k] = fmaf(w, s.x[g + 4 * k][i], acc[k]);
-        }
-#pragma unroll
-        for (int k = 0; k < TILE / 4; ++k) {
-            s.z1[g + 4 * k][j] = acc[k];
-            s.h1[g + 4 * k][j] = gelu(acc[k]);
-        }
-    }
-    __syncthreads();
-    {
-        float acc[TILE / 4];
-        for (int k = 0; k < TILE / 4; ++k) acc[k] = s.b[NH + j];
-        for (int i = 0; i < NH; ++i) {
-            const float w = bf(s.w2[j * NH + i]);
-#pragma unroll
-            for (int k = 0; k < TILE / 4; ++k) acc[k] = fmaf(w, s.h1[g + 4 * k][i], acc[k]);
-        }
-#pragma unroll
-        for (int k = 0; k < TILE / 4; ++k) {
-            s.z2[g + 4 * k][j] = acc[k];
-            s.h2[g + 4 * k][j] = gelu(acc[k]);
-        }
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < TILE * NO; e += MB) {
-        const int r = e / NO, o = e - r * NO;
-        float acc = s.b[2 * NH + o];
-        for (int i = 0; i < NH; ++i) acc = fmaf(bf(s.w3[o * NH + i]), s.h2[r][i], acc);
-        s.y[r][o] = acc;
-    }
-    __syncthreads();
-}
-
-__global__ __launch_bounds__(MB) void k_mlp_forward(const uint16_t *__restrict__ wb, const float *__restrict__ x,
-                                                    int n, const float *__restrict__ mean,
-                                                    const float *__restrict__ inv_std,
-                                                    const float *__restrict__ out_scale, float *__restrict__ y)
-{
-    __shared__ MlpTile s;
-    const int base = blockIdx.x * TILE, cnt = min(TILE, n - base);
-    load_weights(wb, s);
-    load_inputs(x, nullptr, base, cnt, mean, inv_std, s);
-    forward_tile(s);
-    for (int e = threadIdx.x; e < cnt * NO; e += MB) {
-        const int r = e / NO, o = e - r * NO;
-        y[size_t(base + r) * NO + o] = s.y[r][o] * out_scale[o];
-    }
-}
-
-// Squared-error sums and parameter gradients of the samples idx[first ..
-// first+n-1] (or first .. first+n-1), scaled by gscale; workgroup b writes
-// its partial sums to part[b][NP] and lpart[b].
-__global__ __launch_bounds__(MB) void k_mlp_grad(const uint16_t *__restrict__ wb, const float *__restrict__ x,
-                                                 const float *__restrict__ t, const int32_t *__restrict__ idx,
-                                                 int first, int n, const float *__restrict__ mean,
-                                                 const float *__restrict__ inv_std, float gscale,
-                                                 float *__restrict__ part, double *__restrict__ lpart)
-{
-    __shared__ MlpTile s;
-    __shared__ double sl[MB / 64];
-    float *gp = part + size_t(blockIdx.x) * NP;
-    for (int p = threadIdx.x; p < NP; p += MB) gp[p] = 0.0f;
-    load_weights(wb, s);
-    double lsum = 0.0;
-    const int ntile = (n + TILE - 1) / TILE;
-    for (int tl = blockIdx.x; tl < ntile; tl += gridDim.x) {
-        const int base = tl * TILE, cnt = min(TILE, n - base);
-        __syncthreads();
-        load_inputs(x, idx, first + base, cnt, mean, inv_std, s);
-        forward_tile(s);
-        for (int e = threadIdx.x; e < TILE * NO; e += MB) {
-            const int r = e / NO, o = e - r * NO;
-            float d = 0.0f;
-            if (r < cnt) {
-                const int src = idx ? idx[first + base + r] : first + base + r;
-                d = s.y[r][o] - t[size_t(src) * NO + o];
-                lsum += double(d) * double(d);
-            }
-            s.dy[r][o] = gscale * d;
-        }
-        __syncthreads();
-        // output layer: dW3, db3 and dL/dz2
-        for (int p = threadIdx.x; p < NO * NH; p += MB) {
-            const int o = p / NH, i = p - o * NH;
-            float a = 0.0f;
-            for (int r = 0; r < TILE; ++r) a = fmaf(s.dy[r][o], s.h2[r][i], a);
-            gp[OW3 + p] += a;
-        }
-        if (threadIdx.x < NO) {
-            float a = 0.0f;
-            for (int r = 0; r < TILE; ++r) a += s.dy[r][threadIdx.x];
-            gp[OB3 + threadIdx.x] += a;
-        }
-        for (int e = threadIdx.x; e < TILE * NH; e += MB) {
-            const int r = e / NH, j = e - r * NH;
-            float a = 0.0f;
-            for (int o = 0; o < NO; ++o) a = fmaf(bf(s.w3[o * NH + j]), s.dy[r][o], a);
-            s.d2[r][j] = a * gelu_d(s.z2[r][j]);
-        }
-        __syncthreads();
-        // second layer: dW2, db2 and dL/dz1
-        for (int p = threadIdx.x; p < NH * NH; p += MB) {
-            const int j = p / NH, i = p - j * NH;
-            float a = 0.0f;
-            for (int r = 0; r < TILE; ++r) a = fmaf(s.d2[r][j], s.h1[r][i], a);
-            gp[OW2 + p] += a;
-        }
-        if (threadIdx.x < NH) {
-            float a = 0.0f;
-            for (int r = 0; r < TILE; ++r) a += s.d2[r][threadIdx.x];
-            gp[OB2 + threadIdx.x] += a;
-        }
-        for (int e = threadIdx.x; e < TILE * NH; e += MB) {
-            const int r = e / NH, i = e - r * NH;
-            float a = 0.0f;
-            for (int j = 0; j < NH; ++j) a = fmaf(bf(s.w2[j * NH + i]), s.d2[r][j], a);
-            s.d1[r][i] = a * gelu_d(s.z1[r][i]);
-        }
-        __syncthreads();
-        // first layer: dW1, db1
-        for (int p = threadIdx.x; p < NH * NI; p += MB) {
-            const int j = p / NI, i = p - j * NI;
-            float a = 0.0f;
-            for (int r = 0; r < TILE; ++r) a = fmaf(s.d1[r][j], s.x[r][i], a);
-            gp[OW1 + p] += a;
-        }
-        if (threadIdx.x < NH) {
-            float a = 0.0f;
-            for (int r = 0; r < TILE; ++r) a += s.d1[r][threadIdx.x];
-            gp[OB1 + threadIdx.x] += a;
-        }
-    }
-    // loss partial: waves, then workgroup
-    for (int o = 32; o > 0; o >>= 1) lsum += __shfl_xor(lsum, o, 64);
-    if ((threadIdx.x & 63) == 0) sl[threadIdx.x >> 6] = lsum;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double v = 0.0;
-        for (int w = 0; w < MB / 64; ++w) v += sl[w];
-        lpart[blockIdx.x] = v;
-    }
-}
-
-// grad[p] = sum over b of part[b][p] in order b; loss = sum of lpart
+// grad[p] = sum over b of part[b][p] in order b, and with ADAM the update by
+// it; loss = lscale times the sum of lpart
+template <bool ADAM>
 __global__ void k_mlp_reduce(const float *__restrict__ part, int nb, float *__restrict__ grad,
-                             const double *__restrict__ lpart, double *__restrict__ loss, double lscale,
-                             double *__restrict__ loss_acc)
+                             const double *__restrict__ lpart, int nl, double *__restrict__ loss, double lscale,
+                             double *__restrict__ loss_acc, AdamArgs adam)
 {
     for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < NP; p += gridDim.x * blockDim.x) {
         float a = 0.0f;
+#pragma unroll 8
         for (int b = 0; b < nb; ++b) a += part[size_t(b) * NP + p];
         grad[p] = a;
+        if constexpr (ADAM) adam_one(adam, p, a);
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (blockIdx.x == 0 && threadIdx.x < 64) {
         double l = 0.0;
-        for (int b = 0; b < nb; ++b) l += lpart[b];
-        *loss = l * lscale;
-        if (loss_acc) *loss_acc += l * lscale;
+        for (int b = threadIdx.x; b < nl; b += 64) l += lpart[b];
+        for (int d = 32; d > 0; d >>= 1) l += __shfl_xor(l, d, 64);
+        if (threadIdx.x == 0) {
+            *loss = l * lscale;
+            if (loss_acc) *loss_acc += l * lscale;
+        }
     }
 }
 
-// Adam on the FP32 master; corrected step size from the step counter t
-__global__ void k_adam(float *__restrict__ w, float *__restrict__ m, float *__restrict__ v,
-                       const float *__restrict__ g, uint16_t *__restrict__ wb, float lr, float b1, float b2,
-                       float eps, float c1, float c2)
+__global__ void k_adam(AdamArgs a, const float *__restrict__ g)
 {
-    for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < NP; p += gridDim.x * blockDim.x) {
-        const float gg = g[p];
-        const float mm = b1 * m[p] + (1.0f - b1) * gg;
-        const float vv = b2 * v[p] + (1.0f - b2) * gg * gg;
-        m[p] = mm;
-        v[p] = vv;
-        const float mh = mm / c1, vh = vv / c2;
-        const float nw = w[p] - lr * mh / (sqrtf(vh) + eps);
-        w[p] = nw;
-        wb[p] = to_bf16(nw);
-    }
+    for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < NP; p += gridDim.x * blockDim.x) adam_one(a, p, g[p]);
 }
 
 __global__ void k_bf16_copy(const float *__restrict__ w, uint16_t *__restrict__ wb)
@@ -292,7 +303,7 @@ struct lbm_mlp {
     uint16_t *wb = nullptr;
     float *in_mean = nullptr, *in_inv_std = nullptr, *out_scale = nullptr, *env_min = nullptr,
           *env_max = nullptr;
-    float *part = nullptr;
+    float *work = nullptr, *part = nullptr;
     double *lpart = nullptr, *loss = nullptr, *loss_acc = nullptr;
     int64_t t = 0;   // Adam steps taken
 };
@@ -313,8 +324,8 @@ MlpDev mlp_device_view(const lbm_mlp *m)
 hipError_t launch_mlp_forward(const MlpDev &m, const float *x, int n, float *y, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_mlp_forward, dim3((n + TILE - 1) / TILE), dim3(MB), 0, st, m.wb, x, n, m.in_mean,
-                       m.in_inv_std, m.out_scale, y);
+    hipLaunchKernelGGL(k_mlp_rows<false>, dim3(std::min((n - 1) / (MB / 64) + 1, ROW_GRID)), dim3(MB), 0, st, m.wb, x,
+                       nullptr, nullptr, 0, n, n, m.in_mean, m.in_inv_std, m.out_scale, 0.0f, y, nullptr, nullptr, 0);
     return hipGetLastError();
 }
 
@@ -374,8 +385,9 @@ lbm_status lbm_mlp_create(uint64_t seed, void *stream, lbm_mlp **out)
         hipMalloc(&m->wb, NP * 2) != hipSuccess || hipMalloc(&m->in_mean, NI * 4) != hipSuccess ||
         hipMalloc(&m->in_inv_std, NI * 4) != hipSuccess || hipMalloc(&m->out_scale, NO * 4) != hipSuccess ||
         hipMalloc(&m->env_min, NI * 4) != hipSuccess || hipMalloc(&m->env_max, NI * 4) != hipSuccess ||
+        hipMalloc(&m->work, size_t(ROWS_MAX) * ROW * 4) != hipSuccess ||
         hipMalloc(&m->part, size_t(GRAD_BLOCKS) * NP * 4) != hipSuccess ||
-        hipMalloc(&m->lpart, GRAD_BLOCKS * 8) != hipSuccess || hipMalloc(&m->loss, 8) != hipSuccess ||
+        hipMalloc(&m->lpart, ROW_GRID * 8) != hipSuccess || hipMalloc(&m->loss, 8) != hipSuccess ||
         hipMalloc(&m->loss_acc, 8) != hipSuccess)
         return bail(LBM_E_NOMEM);
     std::vector<float> w(NP, 0.0f);
@@ -402,7 +414,7 @@ lbm_status lbm_mlp_destroy(lbm_mlp *m)
     else hipDeviceSynchronize();
     for (void *p : {(void *)m->w, (void *)m->m, (void *)m->v, (void *)m->g, (void *)m->wb, (void *)m->in_mean,
                     (void *)m->in_inv_std, (void *)m->out_scale, (void *)m->env_min, (void *)m->env_max,
-                    (void *)m->part, (void *)m->lpart, (void *)m->loss, (void *)m->loss_acc})
+                    (void *)m->work, (void *)m->part, (void *)m->lpart, (void *)m->loss, (void *)m->loss_acc})
         if (p) hipFree(p);
     delete m;
     return LBM_OK;
@@ -446,48 +458,62 @@ lbm_status lbm_mlp_forward(lbm_mlp *m, const float *x, int32_t n, float *y)
     return LBM_OK;
 }
 
-// gradient of the mean squared error over samples first .. first+n-1 of
-// the order idx (or natural order), into m->g; loss into m->loss
-static hipError_t grad_pass(lbm_mlp *m, const float *x, const float *t, const int32_t *idx, int first, int n,
-                            bool accumulate)
+static AdamArgs adam_args(lbm_mlp *m, float lr, float b1, float b2, float eps)
 {
-    const int ntile = (n + TILE - 1) / TILE;
-    const int nb = std::min(GRAD_BLOCKS, ntile);
+    m->t += 1;
+    return {m->w, m->m, m->v, m->wb, lr, b1, b2, eps, float(1.0 - std::pow(double(b1), double(m->t))),
+            float(1.0 - std::pow(double(b2), double(m->t)))};
+}
+
+// gradient of the mean squared error over samples first .. first+n-1 of
+// the order idx (or natural order), into m->g; loss into m->loss (and added
+// to m->loss_acc if accumulate); adam: the update by the gradient
+static hipError_t grad_pass(lbm_mlp *m, const float *x, const float *t, const int32_t *idx, int first, int n,
+                            bool accumulate, const AdamArgs *adam)
+{
     const float gscale = 2.0f / float(n * NO);
-    hipLaunchKernelGGL(k_mlp_grad, dim3(nb), dim3(MB), 0, m->st, m->wb, x, t, idx, first, n, m->in_mean,
-                       m->in_inv_std, gscale, m->part, m->lpart);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_mlp_reduce, dim3(80), dim3(256), 0, m->st, m->part, nb, m->g, m->lpart, m->loss,
-                       1.0 / double(n * NO), accumulate ? m->loss_acc : nullptr);
+    const int nb = std::min(GRAD_BLOCKS, (n - 1) / TILE + 1);
+    int nl = 0;
+    for (int at = 0; at < n; at += std::min(ROWS_MAX, n - at)) {
+        const int k = std::min(ROWS_MAX, n - at), ntile = (k + TILE - 1) / TILE;
+        const int grid = std::min(ntile * TILE / (MB / 64), ROW_GRID);
+        nl = std::max(nl, grid);
+        hipLaunchKernelGGL(k_mlp_rows<true>, dim3(grid), dim3(MB), 0, m->st, m->wb, x, t, idx, first + at, k,
+                           ntile * TILE, m->in_mean, m->in_inv_std, nullptr, gscale, nullptr, m->work, m->lpart, at > 0);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_mlp_prod, dim3(PROD_GRID, std::min(nb, ntile)), dim3(MB), 0, m->st, m->work, ntile, m->part,
+                           at > 0);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    const double lscale = 1.0 / double(n * NO);
+    double *acc = accumulate ? m->loss_acc : nullptr;
+    if (adam)
+        hipLaunchKernelGGL(k_mlp_reduce<true>, dim3(80), dim3(256), 0, m->st, m->part, nb, m->g, m->lpart, nl, m->loss,
+                           lscale, acc, *adam);
+    else
+        hipLaunchKernelGGL(k_mlp_reduce<false>, dim3(80), dim3(256), 0, m->st, m->part, nb, m->g, m->lpart, nl, m->loss,
+                           lscale, acc, AdamArgs{});
     return hipGetLastError();
 }
 
 lbm_status lbm_mlp_loss_grad(lbm_mlp *m, const float *x, const float *t, int32_t n, double *loss, float *grad)
 {
     if (!m || !x || !t || n < 1) return mfail(m, LBM_E_ARG, "bad argument");
-    MHIP(m, grad_pass(m, x, t, nullptr, 0, n, false));
+    MHIP(m, grad_pass(m, x, t, nullptr, 0, n, false, nullptr));
     if (loss) MHIP(m, hipMemcpyAsync(loss, m->loss, 8, hipMemcpyDeviceToHost, m->st));
     if (grad) MHIP(m, hipMemcpyAsync(grad, m->g, NP * 4, hipMemcpyDeviceToHost, m->st));
     MHIP(m, hipStreamSynchronize(m->st));
     return LBM_OK;
 }
 
-static hipError_t adam_pass(lbm_mlp *m, float lr, float b1, float b2, float eps)
-{
-    m->t += 1;
-    const float c1 = float(1.0 - std::pow(double(b1), double(m->t)));
-    const float c2 = float(1.0 - std::pow(double(b2), double(m->t)));
-    hipLaunchKernelGGL(k_adam, dim3(80), dim3(256), 0, m->st, m->w, m->m, m->v, m->g, m->wb, lr, b1, b2, eps, c1,
-                       c2);
-    return hipGetLastError();
-}
-
 lbm_status lbm_mlp_adam(lbm_mlp *m, float lr, float beta1, float beta2, float eps)
 {
     if (!m || !(lr > 0.0f) || !(beta1 >= 0.0f && beta1 < 1.0f) || !(beta2 >= 0.0f && beta2 < 1.0f))
         return mfail(m, LBM_E_ARG, "bad Adam parameters");
-    MHIP(m, adam_pass(m, lr, beta1, beta2, eps));
+    hipLaunchKernelGGL(k_adam, dim3(80), dim3(256), 0, m->st, adam_args(m, lr, beta1, beta2, eps), m->g);
+    MHIP(m, hipGetLastError());
     MHIP(m, hipStreamSynchronize(m->st));
     return LBM_OK;
 }
@@ -516,8 +542,8 @@ lbm_status lbm_mlp_train(lbm_mlp *m, const float *x, const float *t, int32_t n, 
         }
         for (int b = 0; b < nbatch && e == hipSuccess; ++b) {
             const int first = b * batch, cnt = std::min(batch, n - first);
-            e = grad_pass(m, x, t, didx, first, cnt, true);
-            if (e == hipSuccess) e = adam_pass(m, lr, 0.9f, 0.999f, 1e-8f);
+            const AdamArgs adam = adam_args(m, lr, 0.9f, 0.999f, 1e-8f);
+            e = grad_pass(m, x, t, didx, first, cnt, true, &adam);
         }
         double acc = 0.0;
         if (e == hipSuccess) e = hipMemcpyAsync(&acc, m->loss_acc, 8, hipMemcpyDeviceToHost, m->st);
