@@ -16,8 +16,8 @@ on the stream it runs on), and the FP64 oracle's rate on bounded samples on
 the host cores (the same workload on all cores; the 32^3 single-fiber cell
 in full on all cores and on one core).  The FP16/BF16 deviation-storage
 forms of the same workload, the batched form (512 independent one-fiber
-shear cells of uneven size, edges 24..64, in one persistent graph-captured
-launch with autotuned workgroup size and bin count), and the learned-coarse
+shear cells of uneven size, edges 24..64, advanced together in graph-captured
+steps with autotuned workgroup size and bin count), and the learned-coarse
 form (128^3, 200 under-resolved fibers with the trained closure attached,
 beside the same run without it) are timed too and reported under "forms",
 each with its error: the storage forms against the FP64 oracle on the 32^3
@@ -103,7 +103,7 @@ def time_form(sc, storage, steps, warmup, torch, stabilize=False):
 
 
 def time_batched(steps, warmup, torch, trial_steps=6):
-    """Batched form: 512 cases, one persistent launch of `steps` steps."""
+    """Batched form: `steps` steps of 512 cases."""
     from paper_1503_06869_amd import lbm, scenarios
     cases = scenarios.batched_cases(seed=0)
     stream = torch.cuda.Stream()

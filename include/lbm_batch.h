@@ -1,8 +1,7 @@
 /*
  * lbm_batch.h -- C ABI of the batched form: many small, independent shear
  * cells of uneven size, each with one rigid cylinder fiber, advanced
- * together by one persistent kernel launch (captured in a HIP graph) on one
- * GPU.  Every case runs exactly the coupled method of include/lbm.h (Sec. 4
+ * together (pairs of steps captured in a HIP graph) on one GPU.  Every case runs exactly the coupled method of include/lbm.h (Sec. 4
  * of Bartuschat et al., Computers & Fluids 2015: D3Q19 TRT/SRT AA sweep with
  * moving-wall and moving-obstacle bounce-back, Eqs. LBMMovWall and
  * BBBC; momentum exchange, Eq. LBMhydrodynForce and the torque after it;
@@ -10,11 +9,12 @@
  * per-cell and per-fiber arithmetic, so a case's results equal those of an
  * lbm_ctx created with the same parameters, bit for bit.
  *
- * Work layout: the cases are packed into bins (longest-processing-time
- * order by cell count); one workgroup owns a bin and runs its cases' steps
- * with only intra-workgroup barriers between the phases of a step, so no
- * workgroup ever waits for another.  The number of bins and the workgroup
- * size are tunables, picked by lbm_batch_autotune() from timed trials.
+ * Work layout: a step is one launch over the cells of all cases and one over
+ * the fibers, for which the cases are packed into bins (longest-processing-
+ * time order); a workgroup takes the cases of its bin one after the other,
+ * and no workgroup ever waits for another.  The number of bins and the size
+ * of these workgroups are tunables, picked by lbm_batch_autotune() from timed
+ * trials.
  *
  * Conventions: as in lbm.h (lattice units, [z][y][x] arrays with x fastest,
  * lbm_status returns, lbm_batch_last_error()).  A batch is not thread-safe;
@@ -106,8 +106,7 @@ lbm_status lbm_batch_autotune(lbm_batch *b, int32_t trial_steps, const char *cac
 /* Choose threads and bins directly (0 keeps the current value). */
 lbm_status lbm_batch_set_config(lbm_batch *b, int32_t threads, int32_t bins);
 
-/* Enqueue n steps of every case as one persistent launch (replayed from a
- * captured HIP graph when n repeats). */
+/* Enqueue n steps of every case (pairs of steps from a captured HIP graph). */
 lbm_status lbm_batch_step(lbm_batch *b, int64_t n);
 lbm_status lbm_batch_sync(lbm_batch *b);
 

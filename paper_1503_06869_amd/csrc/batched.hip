@@ -1,22 +1,21 @@
 // batched.hip -- the batched form: many small independent shear cells, one
-// fiber each, advanced by one persistent launch.
+// fiber each, advanced together.
 //
 // Each case is the full coupled method (Sec. 4): the AA stream-collide sweep
 // with wall and fiber bounce-back and the momentum exchange, the rigid-body
-// update, the remap with refill and the boundary-list rebuild.  The cases
-// are packed into bins; workgroup b runs the cases of bin b, one after the
-// other, all steps of a case in a row, with __syncthreads() between the
-// phases of a step.  No workgroup waits for another, so the launch cannot
-// stall on residency, and there are no device-wide fences or atomics.
+// update, the remap with refill and the boundary-list rebuild.  A step of all
+// cases is two launches: the lattices (k_bsweep: boundary cells and bulk cells
+// of every case, spread over the whole card whatever the cases' sizes) and the
+// fibers (k_bparticles: the cases are packed into bins, and workgroup b takes
+// the cases of bin b one after the other).  No workgroup waits for another.
 //
 // The per-cell update, the link terms of the momentum exchange, the rigid
 // update, the cell predicate, the rectangles and the refill are the same
 // device functions the single-lattice kernels use, and the momentum-exchange
 // sums are exact int64 fixed point, so a case reproduces the single-lattice
-// run of the same parameters bit for bit.  One difference of organisation
-// keeps the sweep's register use low: the population-free sums of the
+// run of the same parameters bit for bit.  The population-free sums of the
 // exchange (the A, B, C matrices, terms 6..26) are formed while the list is
-// rebuilt, from the new pose, and the sweep accumulates only F0 and M0.
+// rebuilt, from the new pose; the sweep adds only F0 and M0.
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
@@ -41,6 +40,9 @@ struct BatchDev {
     const CaseDev *cases;
     const int32_t *bin_case;   // case ids of all bins, concatenated
     const int32_t *bin_off;    // [bins + 1]
+    const uint32_t *chunk_case;   // case of each 256 cells of the cell arrays
+    const uint32_t *bnd_blk;       // [nblk][2] boundary workgroups: case, index in the case | count << 16
+    uint32_t nchunk, nblk;
     void *f;
     uint8_t *flags;
     int32_t *pid;
@@ -49,6 +51,7 @@ struct BatchDev {
     PState *ps;                // [ncase][2]: state at even / odd time levels
     Box *box_cur;              // [ncase]
     long long *abc;            // [ncase][NABC] population-free integer sums (SA, SB, SC) for the next step
+    long long *mea;            // [ncase][6] F0, M0 sums of the sweep; zero between steps
     double *ft;                // [ncase][6]
     double *hist;              // [ncase][hist_cap][19]
     int64_t hist_cap;
@@ -130,25 +133,50 @@ struct OwnLinks {
     }
 };
 
-// ------------------------------------------------------------------ sweep of one case
-template <typename S, bool ODD, int BS>
-__device__ __forceinline__ void case_sweep(const BatchDev &bd, S *__restrict__ f, const uint8_t *__restrict__ flags,
-                                           int c, const CaseDev &cd, int64_t s, BShared<BS> &sh)
+// ------------------------------------------------------------------ sweep of all cases
+// Workgroups [0, nblk) take the boundary cells of the cases, 256 list entries
+// of one case at a time; the others stride over the 256-cell chunks of all
+// cases together, so that the card works on one compact band of memory and
+// the cases' sizes do not matter.  Bound by HBM: 512 cases of edges 24 to 64
+// in FP32, 1.43 ms for the bulk cells (4.6 TB/s) and 1.64 with the boundary
+// cells, whose lines are scattered; with a workgroup to a case, all steps in a
+// row, the sweep took 1.80 ms, as the cases of one edge 64 outlast the rest.
+template <typename S, bool ODD>
+__global__ __launch_bounds__(256, 3) void k_bsweep(BatchDev bd, S *__restrict__ f, const uint8_t *__restrict__ flags,
+                                                const CaseDev *__restrict__ cases,
+                                                const uint32_t *__restrict__ chunk_case)
 {
     using R = typename St<S>::R;
-    const Phys<R> &ph = case_phys<R>(cd);
-    S *fc = f + cd.f_off;
-    const uint8_t *flc = flags + cd.cell_off;
+    if (blockIdx.x < bd.nblk) {
+        const uint32_t c = uniform(bd.bnd_blk[2 * blockIdx.x]), at = uniform(bd.bnd_blk[2 * blockIdx.x + 1]);
+        const CaseDev &cd = cases[c];
+        const uint32_t cnt = uniform(bd.list_n[c]), n = cnt < cd.list_cap ? cnt : cd.list_cap;
+        const uint32_t *lc = bd.list_cell + cd.list_off, *lm = bd.list_mask + cd.list_off;
+        OwnLinks<S, ODD> links{f + cd.f_off, cd.g, case_phys<R>(cd), uniform(bd.ps[size_t(c) * 2 + (ODD ? 1 : 0)]), bd.ctr,
+                               {0, 0, 0, 0, 0, 0}};
+        bool any = false;
+        for (uint32_t r = (at & 0xFFFFu) * 256u + threadIdx.x; r < n; r += (at >> 16) * 256u) {
+            update_cell<S, ODD, true, false, false>(links.f, cd.g, links.ph, lc[r], lm[r], links);
+            any = true;
+        }
+        if (!__any(any)) return;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            long long v = links.acc[k];
+            for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+            if ((threadIdx.x & 63) == 0)
+                atomicAdd(reinterpret_cast<unsigned long long *>(bd.mea + size_t(c) * 6 + k), (unsigned long long)v);
+        }
+        return;
+    }
     NoLinks none;
-    for (uint32_t cell = threadIdx.x; cell < cd.g.ncell; cell += BS)
-        if (!flc[cell]) update_cell<S, ODD, false, false, false>(fc, cd.g, ph, cell, 0u, none);
-    const uint32_t cnt = uniform(bd.list_n[c]);
-    const uint32_t n = cnt < cd.list_cap ? cnt : cd.list_cap;
-    const uint32_t *lc = bd.list_cell + cd.list_off, *lm = bd.list_mask + cd.list_off;
-    OwnLinks<S, ODD> links{fc, cd.g, ph, uniform(bd.ps[size_t(c) * 2 + size_t(s & 1)]), bd.ctr, {0, 0, 0, 0, 0, 0}};
-    for (uint32_t r = threadIdx.x; r < n; r += BS)
-        update_cell<S, ODD, true, false, false>(fc, cd.g, ph, lc[r], lm[r], links);
-    block_sum<BS, 6>(links.acc, sh, sh.tot);
+    for (uint32_t ch = blockIdx.x - bd.nblk; ch < bd.nchunk; ch += gridDim.x - bd.nblk) {
+        const CaseDev &cd = cases[chunk_case[ch]];
+        const uint64_t at = uint64_t(ch) * 256u + threadIdx.x;
+        const uint32_t cell = uint32_t(at - cd.cell_off);
+        if (cell < cd.g.ncell && !flags[at])
+            update_cell<S, ODD, false, false, false>(f + cd.f_off, cd.g, case_phys<R>(cd), cell, 0u, none);
+    }
 }
 
 // ------------------------------------------------------------------ particle phase of one case
@@ -169,10 +197,11 @@ __device__ __forceinline__ void case_particles(const BatchDev &bd, int c, const 
         PState o = so;
         if (!setup) {
             if (lane < NACC)
-                sh.ac[lane] = lane < 6 ? ldexp(double(sh.tot[lane]), -fx_shift(lane))
+                sh.ac[lane] = lane < 6 ? ldexp(double(bd.mea[size_t(c) * 6 + lane]), -fx_shift(lane))
                                        : double(bd.abc[size_t(c) * NABC + (lane < 6 ? 0 : lane - 6)]);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
+            if (lane < 6) bd.mea[size_t(c) * 6 + lane] = 0;
             abc_restore(sh.ac, so.X, double(case_phys<R>(cd).rho0), lane);
             const double *row = nullptr;
             if (cd.pc.traj_off >= 0) {
@@ -332,14 +361,11 @@ __device__ __forceinline__ void case_particles(const BatchDev &bd, int c, const 
     __syncthreads();
 }
 
-// ------------------------------------------------------------------ persistent kernel
-// Workgroup b runs every case of bin b through nsteps steps (setup != 0:
-// maps the initial poses instead).  Register budget: two waves per SIMD for
-// 256- and 512-thread workgroups (256 VGPRs: the bulk loop does not spill),
-// four for 1024 threads (128 VGPRs: more waves, but spills).
+// ------------------------------------------------------------------ particles of all cases
+// Workgroup b takes the cases of bin b through the particle phase of a step
+// (setup != 0: maps the initial poses instead).
 template <typename S, int BS>
-__global__ __launch_bounds__(BS, BS == 1024 ? 4 : 2) void k_batch(BatchDev bd, S *__restrict__ f, const uint8_t *__restrict__ flags,
-                                                 int32_t nsteps, int32_t setup)
+__global__ __launch_bounds__(BS, BS == 1024 ? 4 : 2) void k_bparticles(BatchDev bd, int32_t setup)
 {
     __shared__ BShared<BS> sh;
     const int bin = blockIdx.x;
@@ -347,40 +373,51 @@ __global__ __launch_bounds__(BS, BS == 1024 ? 4 : 2) void k_batch(BatchDev bd, S
     for (int i = i0; i < i1; ++i) {
         const int c = uniform(bd.bin_case[i]);
         const CaseDev cd = uniform(bd.cases[c]);
-        int64_t s = uniform(bd.steps[c]);
-        if (setup) {
-            case_particles<S, BS>(bd, c, cd, s, sh, true);
-            continue;
-        }
-        for (int k = 0; k < nsteps; ++k, ++s) {
-            if (s & 1) case_sweep<S, true, BS>(bd, f, flags, c, cd, s, sh);
-            else case_sweep<S, false, BS>(bd, f, flags, c, cd, s, sh);
-            case_particles<S, BS>(bd, c, cd, s, sh, false);
-        }
-        if (threadIdx.x == 0) bd.steps[c] = s;
+        const int64_t s = uniform(bd.steps[c]);
+        case_particles<S, BS>(bd, c, cd, s, sh, setup != 0);
+        if (!setup && threadIdx.x == 0) bd.steps[c] = s + 1;
     }
 }
 
 template <typename S>
-static hipError_t launch_batch_t(const BatchDev &bd, int threads, int bins, int nsteps, int setup, hipStream_t st)
+static hipError_t launch_particles_t(const BatchDev &bd, int threads, int bins, int setup, hipStream_t st)
 {
-    S *f = reinterpret_cast<S *>(bd.f);
     switch (threads) {
-    case 256: hipLaunchKernelGGL((k_batch<S, 256>), dim3(bins), dim3(256), 0, st, bd, f, bd.flags, nsteps, setup); break;
-    case 1024: hipLaunchKernelGGL((k_batch<S, 1024>), dim3(bins), dim3(1024), 0, st, bd, f, bd.flags, nsteps, setup); break;
-    default: hipLaunchKernelGGL((k_batch<S, 512>), dim3(bins), dim3(512), 0, st, bd, f, bd.flags, nsteps, setup); break;
+    case 256: hipLaunchKernelGGL((k_bparticles<S, 256>), dim3(bins), dim3(256), 0, st, bd, setup); break;
+    case 1024: hipLaunchKernelGGL((k_bparticles<S, 1024>), dim3(bins), dim3(1024), 0, st, bd, setup); break;
+    default: hipLaunchKernelGGL((k_bparticles<S, 512>), dim3(bins), dim3(512), 0, st, bd, setup); break;
     }
     return hipGetLastError();
 }
 
-static hipError_t launch_batch(int sk, const BatchDev &bd, int threads, int bins, int nsteps, int setup,
-                               hipStream_t st)
+static hipError_t launch_particles(int sk, const BatchDev &bd, int threads, int bins, int setup, hipStream_t st)
 {
     switch (sk) {
-    case S_F32: return launch_batch_t<float>(bd, threads, bins, nsteps, setup, st);
-    case S_F16: return launch_batch_t<_Float16>(bd, threads, bins, nsteps, setup, st);
-    case S_BF16: return launch_batch_t<bf16s>(bd, threads, bins, nsteps, setup, st);
-    default: return launch_batch_t<double>(bd, threads, bins, nsteps, setup, st);
+    case S_F32: return launch_particles_t<float>(bd, threads, bins, setup, st);
+    case S_F16: return launch_particles_t<_Float16>(bd, threads, bins, setup, st);
+    case S_BF16: return launch_particles_t<bf16s>(bd, threads, bins, setup, st);
+    default: return launch_particles_t<double>(bd, threads, bins, setup, st);
+    }
+}
+
+template <typename S>
+static hipError_t launch_bsweep_t(const BatchDev &bd, bool odd, uint32_t grid, hipStream_t st)
+{
+    S *f = reinterpret_cast<S *>(bd.f);
+    if (odd) hipLaunchKernelGGL((k_bsweep<S, true>), dim3(bd.nblk + grid), dim3(256), 0, st, bd, f, bd.flags, bd.cases,
+                               bd.chunk_case);
+    else hipLaunchKernelGGL((k_bsweep<S, false>), dim3(bd.nblk + grid), dim3(256), 0, st, bd, f, bd.flags, bd.cases,
+                               bd.chunk_case);
+    return hipGetLastError();
+}
+
+static hipError_t launch_bsweep(int sk, const BatchDev &bd, bool odd, uint32_t grid, hipStream_t st)
+{
+    switch (sk) {
+    case S_F32: return launch_bsweep_t<float>(bd, odd, grid, st);
+    case S_F16: return launch_bsweep_t<_Float16>(bd, odd, grid, st);
+    case S_BF16: return launch_bsweep_t<bf16s>(bd, odd, grid, st);
+    default: return launch_bsweep_t<double>(bd, odd, grid, st);
     }
 }
 
@@ -407,6 +444,9 @@ struct lbm_batch {
     int threads = 512, bins = 1;
     CaseDev *cases = nullptr;
     int32_t *bin_case = nullptr, *bin_off = nullptr;
+    uint32_t *chunk_case = nullptr, *bnd_blk = nullptr;
+    uint32_t nchunk = 0, nblk = 0, sweep_grid = 0;
+    long long *mea = nullptr;
     void *f = nullptr;
     uint8_t *flags = nullptr;
     int32_t *pid = nullptr;
@@ -422,9 +462,8 @@ struct lbm_batch {
     uint64_t nlist = 0;
     int64_t steps = 0;
     int64_t device_bytes = 0;
-    hipGraph_t graph = nullptr;
+    hipGraph_t graph = nullptr;              // an even and an odd step
     hipGraphExec_t gexec = nullptr;
-    int64_t graph_n = -1;
 };
 
 static std::string g_create_err;
@@ -466,7 +505,6 @@ static void drop_bgraph(lbm_batch *b)
     if (b->graph) hipGraphDestroy(b->graph);
     b->gexec = nullptr;
     b->graph = nullptr;
-    b->graph_n = -1;
 }
 
 static void host_axis_b(const double q[4], double t[3])
@@ -528,6 +566,11 @@ static BatchDev batch_dev(lbm_batch *b)
     d.cases = b->cases;
     d.bin_case = b->bin_case;
     d.bin_off = b->bin_off;
+    d.chunk_case = b->chunk_case;
+    d.bnd_blk = b->bnd_blk;
+    d.nchunk = b->nchunk;
+    d.nblk = b->nblk;
+    d.mea = b->mea;
     d.f = b->f;
     d.flags = b->flags;
     d.pid = b->pid;
@@ -548,8 +591,15 @@ static BatchDev batch_dev(lbm_batch *b)
     return d;
 }
 
+static hipError_t launch_bstep(lbm_batch *b, bool odd)
+{
+    const BatchDev bd = batch_dev(b);
+    const hipError_t e = launch_bsweep(b->sk, bd, odd, b->sweep_grid, b->st);
+    return e != hipSuccess ? e : launch_particles(b->sk, bd, b->threads, b->bins, 0, b->st);
+}
+
 // Longest-processing-time packing of the cases into nb bins: cases by
-// descending cost (cells plus a per-step constant for the particle phase),
+// descending cost (the expected region around the fiber plus a constant),
 // each into the currently lightest bin.
 static lbm_status set_bins(lbm_batch *b, int nb)
 {
@@ -557,7 +607,7 @@ static lbm_status set_bins(lbm_batch *b, int nb)
     nb = std::max(1, std::min(nb, b->ncase));
     std::vector<int> order(b->ncase);
     for (int i = 0; i < b->ncase; ++i) order[i] = i;
-    auto cost = [&](int i) { return double(b->hcd[i].g.ncell) + 4096.0; };
+    auto cost = [&](int i) { return double(b->hcd[i].list_cap) + 512.0; };
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return cost(x) > cost(y); });
     std::vector<std::vector<int>> bin(nb);
     std::vector<double> load(nb, 0.0);
@@ -599,6 +649,7 @@ static lbm_status reset_state(lbm_batch *b)
     BHIP(b, hipMemsetAsync(b->list_n, 0, b->ncase * sizeof(uint32_t), b->st));
     BHIP(b, hipMemsetAsync(b->box_cur, 0, b->ncase * sizeof(Box), b->st));
     BHIP(b, hipMemsetAsync(b->abc, 0, size_t(b->ncase) * NABC * sizeof(long long), b->st));
+    BHIP(b, hipMemsetAsync(b->mea, 0, size_t(b->ncase) * 6 * sizeof(long long), b->st));
     BHIP(b, hipMemsetAsync(b->ft, 0, size_t(b->ncase) * 6 * sizeof(double), b->st));
     BHIP(b, hipMemsetAsync(b->steps_d, 0, b->ncase * sizeof(int64_t), b->st));
     BHIP(b, hipMemsetAsync(b->traj_pos, 0, b->ncase * sizeof(int64_t), b->st));
@@ -608,7 +659,7 @@ static lbm_status reset_state(lbm_batch *b)
     BHIP(b, hipMemcpyAsync(b->ps, ps.data(), ps.size() * sizeof(PState), hipMemcpyHostToDevice, b->st));
     BHIP(b, hipStreamSynchronize(b->st));
     b->steps = 0;
-    BHIP(b, launch_batch(b->sk, batch_dev(b), b->threads, b->bins, 0, 1, b->st));
+    BHIP(b, launch_particles(b->sk, batch_dev(b), b->threads, b->bins, 1, b->st));
     BHIP(b, hipStreamSynchronize(b->st));
     return LBM_OK;
 }
@@ -673,6 +724,9 @@ lbm_status lbm_batch_destroy(lbm_batch *b)
     bfree(b->cases);
     bfree(b->bin_case);
     bfree(b->bin_off);
+    bfree(b->chunk_case);
+    bfree(b->bnd_blk);
+    bfree(b->mea);
     bfree(b->f);
     bfree(b->flags);
     bfree(b->pid);
@@ -753,7 +807,9 @@ lbm_status lbm_batch_create(const lbm_batch_params *p, const lbm_batch_case *cas
         g.nz = k.nz;
         g.nxy = uint32_t(k.nx) * uint32_t(k.ny);
         g.ncell = g.nxy * uint32_t(k.nz);
-        g.qstride = uint64_t(k.nz + 2) * g.nxy + 64;
+        // cell 0 of every direction at a multiple of 64 elements, so that the
+        // 256-cell chunks of the sweep cover whole cache lines
+        g.qstride = (uint64_t(k.nz + 2) * g.nxy + 63) / 64 * 64 + 64;
         g.dnx = make_fastdiv(g.nx);
         g.dnxy = make_fastdiv(g.nxy);
         g.zper = 0;
@@ -776,8 +832,8 @@ lbm_status lbm_batch_create(const lbm_batch_params *p, const lbm_batch_case *cas
         pf.has_g = 0;
         pf.scale = float(ph.scale);
         pf.inv_scale = float(ph.inv_scale);
-        cd.f_off = foff;
-        foff += (uint64_t(Q) * g.qstride + 63) / 64 * 64;
+        cd.f_off = foff + (64 - g.nxy % 64) % 64;
+        foff += 64 + uint64_t(Q) * g.qstride;
         cd.cell_off = coff;
         coff += (uint64_t(g.ncell) + 255) / 256 * 256;
         const lbm_fiber &fb = k.fiber;
@@ -794,6 +850,26 @@ lbm_status lbm_batch_create(const lbm_batch_params *p, const lbm_batch_case *cas
     b->nf = foff;
     b->ncells = coff;
     b->nlist = loff;
+    // the sweep's tables: the case of every 256 cells, and the workgroups of a
+    // case's boundary cells (a list holds at most about 0.8 of its capacity;
+    // what a workgroup's share leaves it takes in further rounds)
+    std::vector<uint32_t> chunk(coff / 256), blk;
+    for (int i = 0; i < ncases; ++i) {
+        const CaseDev &cd = b->hcd[i];
+        for (uint64_t k = cd.cell_off / 256; k < (cd.cell_off + cd.g.ncell + 255) / 256; ++k) chunk[k] = uint32_t(i);
+        const uint32_t nb = std::min((cd.list_cap + 511u) / 512u, 65535u);
+        for (uint32_t k = 0; k < nb; ++k) {
+            blk.push_back(uint32_t(i));
+            blk.push_back(k | nb << 16);
+        }
+    }
+    b->nchunk = uint32_t(chunk.size());
+    b->nblk = uint32_t(blk.size() / 2);
+    // workgroups that stride over the chunks: three a CU are resident.  512
+    // cases of edges 24 to 64 (43 million cells), ms a step at two, three, four
+    // and sixteen a CU: FP32 1.95, 1.76, 1.97, 1.75; FP16 1.43, 1.09, 1.35,
+    // 1.11; FP64 3.83, 3.47, 3.47, 2.80.
+    b->sweep_grid = std::min(b->nchunk, uint32_t((b->sk == S_F64 ? 16 : 3) * b->cu));
     if (hipMalloc(&b->f, b->nf * b->esz) != hipSuccess) return bail(LBM_E_NOMEM, "populations");
     b->device_bytes += int64_t(b->nf * b->esz);
     if (balloc(b, &b->cases, ncases) != hipSuccess || balloc(b, &b->flags, b->ncells) != hipSuccess ||
@@ -803,11 +879,16 @@ lbm_status lbm_batch_create(const lbm_batch_params *p, const lbm_batch_case *cas
         balloc(b, &b->abc, size_t(ncases) * NABC) != hipSuccess ||
         balloc(b, &b->ft, size_t(ncases) * 6) != hipSuccess ||
         balloc(b, &b->hist, size_t(ncases) * size_t(p->history_capacity) * 19) != hipSuccess ||
+        balloc(b, &b->mea, size_t(ncases) * 6) != hipSuccess || balloc(b, &b->chunk_case, b->nchunk) != hipSuccess ||
+        balloc(b, &b->bnd_blk, blk.size()) != hipSuccess ||
         balloc(b, &b->traj, 13) != hipSuccess || balloc(b, &b->steps_d, ncases) != hipSuccess ||
         balloc(b, &b->traj_pos, ncases) != hipSuccess || balloc(b, &b->ctr, 1) != hipSuccess)
         return bail(LBM_E_NOMEM, "device buffers");
     if (hipMemcpy(b->cases, b->hcd.data(), ncases * sizeof(CaseDev), hipMemcpyHostToDevice) != hipSuccess)
         return bail(LBM_E_HIP, "case table");
+    if (hipMemcpy(b->chunk_case, chunk.data(), chunk.size() * 4, hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(b->bnd_blk, blk.data(), blk.size() * 4, hipMemcpyHostToDevice) != hipSuccess)
+        return bail(LBM_E_HIP, "sweep tables");
     b->threads = p->threads ? p->threads : 512;
     if (set_bins(b, p->bins ? p->bins : b->cu) != LBM_OK) return bail(LBM_E_HIP, "bins");
     lbm_status s = reset_state(b);
@@ -867,11 +948,11 @@ lbm_status lbm_batch_step(lbm_batch *b, int64_t n)
     if (!b) return LBM_E_ARG;
     if (n < 0 || n > (1ll << 30)) return bfail(b, LBM_E_ARG, "step count");
     if (n == 0) return LBM_OK;
-    if (!b->gexec || b->graph_n != n) {
-        drop_bgraph(b);
+    if (n > 1 && !b->gexec) {
         hipError_t e = hipStreamBeginCapture(b->st, hipStreamCaptureModeThreadLocal);
         if (e != hipSuccess) return bfail(b, LBM_E_HIP, std::string("capture: ") + hipGetErrorString(e));
-        hipError_t le = launch_batch(b->sk, batch_dev(b), b->threads, b->bins, int(n), 0, b->st);
+        hipError_t le = launch_bstep(b, false);
+        if (le == hipSuccess) le = launch_bstep(b, true);
         e = hipStreamEndCapture(b->st, &b->graph);
         if (le != hipSuccess || e != hipSuccess) {
             drop_bgraph(b);
@@ -882,10 +963,19 @@ lbm_status lbm_batch_step(lbm_batch *b, int64_t n)
             drop_bgraph(b);
             return bfail(b, LBM_E_HIP, std::string("instantiate: ") + hipGetErrorString(e));
         }
-        b->graph_n = n;
     }
-    BHIP(b, hipGraphLaunch(b->gexec, b->st));
-    b->steps += n;
+    // single steps at the ends, pairs between them
+    for (int64_t left = n; left > 0;) {
+        if ((b->steps & 1) || left == 1) {
+            BHIP(b, launch_bstep(b, (b->steps & 1) != 0));
+            b->steps += 1;
+            left -= 1;
+        } else {
+            BHIP(b, hipGraphLaunch(b->gexec, b->st));
+            b->steps += 2;
+            left -= 2;
+        }
+    }
     return LBM_OK;
 }
 
@@ -932,13 +1022,19 @@ lbm_status lbm_batch_autotune(lbm_batch *b, int32_t trial_steps, const char *cac
         BHIP(b, hipEventCreate(&e0));
         BHIP(b, hipEventCreate(&e1));
         double best = 1e300;
+        int64_t at = 0;
+        auto run = [&](int n) {
+            hipError_t e = hipSuccess;
+            for (int k = 0; k < n && e == hipSuccess; ++k, ++at) e = launch_bstep(b, (at & 1) != 0);
+            return e;
+        };
         for (auto &cb : cand) {
             b->threads = cb.first;
             lbm_status s = set_bins(b, cb.second);
             if (s != LBM_OK) return s;
-            BHIP(b, launch_batch(b->sk, batch_dev(b), b->threads, b->bins, 1, 0, b->st));   // warm-up
+            BHIP(b, run(1));   // warm-up
             BHIP(b, hipEventRecord(e0, b->st));
-            BHIP(b, launch_batch(b->sk, batch_dev(b), b->threads, b->bins, trial_steps, 0, b->st));
+            BHIP(b, run(trial_steps));
             BHIP(b, hipEventRecord(e1, b->st));
             BHIP(b, hipEventSynchronize(e1));
             float ms = 0.f;

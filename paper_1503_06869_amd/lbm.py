@@ -433,8 +433,8 @@ def _fiber_struct(X, q, length, radius, density_ratio=1.0, V=(0, 0, 0), W=(0, 0,
 
 
 class Batch:
-    """Many independent one-fiber shear cells advanced by one persistent
-    launch (owns an lbm_batch).  ``cases``: objects with nx, ny, nz, tau,
+    """Many independent one-fiber shear cells advanced
+    together (owns an lbm_batch).  ``cases``: objects with nx, ny, nz, tau,
     wall_u and fibers[0] (X, q, length, radius, density_ratio, V, W, and
     optionally shape, force, torque)."""
 
