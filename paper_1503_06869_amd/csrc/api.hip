@@ -13,6 +13,7 @@
 #include "../../include/lbm.h"
 #include "../../include/lbm_mlp.h"
 #include "lbm_dev.h"
+#include "readback.h"
 
 using namespace lbm;
 
@@ -50,6 +51,7 @@ struct lbm_ctx {
     uint32_t *list_cell = nullptr, *list_mask = nullptr;
     uint32_t list_cap = 0;
     DevCounters *ctr = nullptr;
+    Readback rb;
     uint32_t bnd_grid = 0, sweep_grid = 0;
     uint32_t nbulk = 0;       // small lattice: waves of the sweep inside the boundary launch
     int64_t steps = 0;
@@ -338,11 +340,12 @@ static lbm_status setup_mapping(lbm_ctx *c, PState *old_states)
     return LBM_OK;
 }
 
-static lbm_status check_device_errors(lbm_ctx *c)
+// waits for the work enqueued so far; src, bytes, out: a device buffer read in
+// the same wait if it is small
+static lbm_status check_device_errors(lbm_ctx *c, const void *src = nullptr, size_t bytes = 0, void *out = nullptr)
 {
     DevCounters h;
-    HIPCHK(c, hipMemcpyAsync(&h, c->ctr, sizeof h, hipMemcpyDeviceToHost, c->st));
-    HIPCHK(c, hipStreamSynchronize(c->st));
+    HIPCHK(c, c->rb.read(c->st, c->ctr, h, src, bytes <= Readback::CAP ? bytes : 0));
     if (h.err_unstable)
         return fail(c, LBM_E_UNSTABLE, (h.err_unstable & 1) ? "non-finite force or torque on the device"
                                                             : "non-finite population on the device");
@@ -353,6 +356,8 @@ static lbm_status check_device_errors(lbm_ctx *c)
                         ((h.err_capacity & 4) ? "changed-cell list"
                                                   : (h.err_capacity & 2) ? "boundary list" : "neighbour list") +
                         ")");
+    if (bytes > Readback::CAP) HIPCHK(c, hipMemcpy(out, src, bytes, hipMemcpyDeviceToHost));
+    else if (bytes) c->rb.take(out, bytes);
     return LBM_OK;
 }
 
@@ -615,7 +620,7 @@ lbm_status lbm_create(const lbm_params *p, lbm_ctx **out)
     c->device_bytes += int64_t(size_t(Q) * g.qstride * c->esz);
     if (dalloc(c, &c->flags[0], g.ncell) != hipSuccess || dalloc(c, &c->flags[1], g.ncell) != hipSuccess ||
         dalloc(c, &c->pid, g.ncell) != hipSuccess ||
-        dalloc(c, &c->ctr, 1) != hipSuccess)
+        dalloc(c, &c->ctr, 1) != hipSuccess || c->rb.create() != hipSuccess)
         return bail(LBM_E_NOMEM, "fields");
     if (hipMemsetAsync(c->flags[0], 0, g.ncell, c->st) != hipSuccess ||
         hipMemsetAsync(c->flags[1], 0, g.ncell, c->st) != hipSuccess ||
@@ -639,6 +644,7 @@ lbm_status lbm_destroy(lbm_ctx *c)
     drop_graph(c);
     for (hipEvent_t e : c->ev) hipEventDestroy(e);
     free_particles(c);
+    c->rb.destroy();
     dfree(c->stab);
     dfree(c->cov);
     dfree(c->corr);
@@ -819,18 +825,15 @@ lbm_status lbm_sync(lbm_ctx *c)
 {
     if (!c) return LBM_E_ARG;
     HIPCHK(c, launch_check_finite(c->sk, c->f, uint64_t(Q) * c->g.qstride, c->ctr, c->st));
-    HIPCHK(c, hipStreamSynchronize(c->st));
     return check_device_errors(c);
 }
 
 lbm_status lbm_get_force_torque(lbm_ctx *c, double *F, double *M)
 {
     if (!c) return LBM_E_ARG;
-    lbm_status s = check_device_errors(c);
-    if (s != LBM_OK) return s;
-    if (c->np == 0) return LBM_OK;
     std::vector<double> h(size_t(c->np) * 6);
-    HIPCHK(c, hipMemcpy(h.data(), c->ft, h.size() * sizeof(double), hipMemcpyDeviceToHost));
+    lbm_status s = check_device_errors(c, c->ft, h.size() * sizeof(double), h.data());
+    if (s != LBM_OK) return s;
     for (int i = 0; i < c->np; ++i)
         for (int k = 0; k < 3; ++k) {
             if (F) F[3 * i + k] = h[6 * i + k];
@@ -954,11 +957,9 @@ lbm_status lbm_get_fields_static(lbm_ctx *c, void *rho, void *u, uint8_t *flags,
 lbm_status lbm_get_fiber_state(lbm_ctx *c, double *X, double *q, double *V, double *W)
 {
     if (!c) return LBM_E_ARG;
-    lbm_status s = check_device_errors(c);
-    if (s != LBM_OK) return s;
-    if (c->np == 0) return LBM_OK;
     std::vector<PState> h(c->np);
-    HIPCHK(c, hipMemcpy(h.data(), c->ps[c->steps & 1], c->np * sizeof(PState), hipMemcpyDeviceToHost));
+    lbm_status s = check_device_errors(c, c->ps[c->steps & 1], c->np * sizeof(PState), h.data());
+    if (s != LBM_OK) return s;
     for (int i = 0; i < c->np; ++i) {
         for (int k = 0; k < 3; ++k) {
             if (X) X[3 * i + k] = h[i].X[k];
@@ -999,20 +1000,16 @@ lbm_status lbm_set_fiber_state(lbm_ctx *c, int32_t id, const double X[3], const 
 lbm_status lbm_get_history(lbm_ctx *c, int64_t first, int64_t count, double *out)
 {
     if (!c || !out || count < 0) return fail(c, LBM_E_ARG, "bad argument");
-    lbm_status s = check_device_errors(c);
-    if (s != LBM_OK) return s;
     const int64_t cap = c->p.history_capacity;
-    if (first < 0 || first + count > c->steps || first < c->steps - cap)
-        return fail(c, LBM_E_ARG, "history window not available");
-    if (c->np == 0 || count == 0) return LBM_OK;
+    const bool window = first >= 0 && first + count <= c->steps && first >= c->steps - cap;
     const size_t rec = size_t(c->np) * 19;
-    for (int64_t i = 0; i < count;) {
-        const int64_t slot = (first + i) % cap;
-        const int64_t run = std::min<int64_t>(count - i, cap - slot);
-        HIPCHK(c, hipMemcpy(out + i * rec, c->hist + slot * rec, size_t(run) * rec * sizeof(double),
-                            hipMemcpyDeviceToHost));
-        i += run;
-    }
+    // the window's run up to the ring's end with the errors, then the rest
+    const int64_t slot = window ? first % cap : 0, run = window ? std::min<int64_t>(count, cap - slot) : 0;
+    lbm_status s = check_device_errors(c, c->hist + slot * rec, size_t(run) * rec * sizeof(double), out);
+    if (s != LBM_OK) return s;
+    if (!window) return fail(c, LBM_E_ARG, "history window not available");
+    if (count > run && rec)
+        HIPCHK(c, hipMemcpy(out + run * rec, c->hist, size_t(count - run) * rec * sizeof(double), hipMemcpyDeviceToHost));
     return LBM_OK;
 }
 

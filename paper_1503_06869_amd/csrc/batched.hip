@@ -29,6 +29,7 @@
 
 #include "../../include/lbm_batch.h"
 #include "../../include/lbm_mlp.h"
+#include "readback.h"
 #include "lbm_sweep_dev.h"
 #include "lbm_particle_dev.h"   // FP contraction off from here on, as in particles.hip
 
@@ -457,6 +458,7 @@ struct lbm_batch {
     double *ft = nullptr, *hist = nullptr, *traj = nullptr;
     int64_t *steps_d = nullptr, *traj_pos = nullptr;
     DevCounters *ctr = nullptr;
+    Readback rb;
     float *feat = nullptr;                   // features of all cases on their way to the host
     uint64_t nf = 0, ncells = 0;
     uint64_t nlist = 0;
@@ -664,13 +666,16 @@ static lbm_status reset_state(lbm_batch *b)
     return LBM_OK;
 }
 
-static lbm_status check_batch_errors(lbm_batch *b)
+// waits for the work enqueued so far; src, bytes, out: a device buffer read in
+// the same wait if it is small
+static lbm_status check_batch_errors(lbm_batch *b, const void *src = nullptr, size_t bytes = 0, void *out = nullptr)
 {
     DevCounters h{};
-    BHIP(b, hipMemcpyAsync(&h, b->ctr, sizeof h, hipMemcpyDeviceToHost, b->st));
-    BHIP(b, hipStreamSynchronize(b->st));
+    BHIP(b, b->rb.read(b->st, b->ctr, h, src, bytes <= Readback::CAP ? bytes : 0));
     if (h.err_unstable) return bfail(b, LBM_E_UNSTABLE, "non-finite force or torque on the device");
     if (h.err_capacity) return bfail(b, LBM_E_STATE, "internal capacity exceeded (boundary list)");
+    if (bytes > Readback::CAP) BHIP(b, hipMemcpy(out, src, bytes, hipMemcpyDeviceToHost));
+    else if (bytes) b->rb.take(out, bytes);
     return LBM_OK;
 }
 
@@ -742,6 +747,7 @@ lbm_status lbm_batch_destroy(lbm_batch *b)
     bfree(b->steps_d);
     bfree(b->traj_pos);
     bfree(b->ctr);
+    b->rb.destroy();
     bfree(b->feat);
     if (b->own_stream && b->st) hipStreamDestroy(b->st);
     delete b;
@@ -882,7 +888,8 @@ lbm_status lbm_batch_create(const lbm_batch_params *p, const lbm_batch_case *cas
         balloc(b, &b->mea, size_t(ncases) * 6) != hipSuccess || balloc(b, &b->chunk_case, b->nchunk) != hipSuccess ||
         balloc(b, &b->bnd_blk, blk.size()) != hipSuccess ||
         balloc(b, &b->traj, 13) != hipSuccess || balloc(b, &b->steps_d, ncases) != hipSuccess ||
-        balloc(b, &b->traj_pos, ncases) != hipSuccess || balloc(b, &b->ctr, 1) != hipSuccess)
+        balloc(b, &b->traj_pos, ncases) != hipSuccess || balloc(b, &b->ctr, 1) != hipSuccess ||
+        b->rb.create() != hipSuccess)
         return bail(LBM_E_NOMEM, "device buffers");
     if (hipMemcpy(b->cases, b->hcd.data(), ncases * sizeof(CaseDev), hipMemcpyHostToDevice) != hipSuccess)
         return bail(LBM_E_HIP, "case table");
@@ -982,7 +989,6 @@ lbm_status lbm_batch_step(lbm_batch *b, int64_t n)
 lbm_status lbm_batch_sync(lbm_batch *b)
 {
     if (!b) return LBM_E_ARG;
-    BHIP(b, hipStreamSynchronize(b->st));
     return check_batch_errors(b);
 }
 
@@ -1071,10 +1077,9 @@ lbm_status lbm_batch_autotune(lbm_batch *b, int32_t trial_steps, const char *cac
 lbm_status lbm_batch_get_force_torque(lbm_batch *b, double *F, double *M)
 {
     if (!b) return LBM_E_ARG;
-    lbm_status s = check_batch_errors(b);
-    if (s != LBM_OK) return s;
     std::vector<double> h(size_t(b->ncase) * 6);
-    BHIP(b, hipMemcpy(h.data(), b->ft, h.size() * sizeof(double), hipMemcpyDeviceToHost));
+    lbm_status s = check_batch_errors(b, b->ft, h.size() * sizeof(double), h.data());
+    if (s != LBM_OK) return s;
     for (int i = 0; i < b->ncase; ++i)
         for (int k = 0; k < 3; ++k) {
             if (F) F[3 * i + k] = h[6 * i + k];
@@ -1086,10 +1091,9 @@ lbm_status lbm_batch_get_force_torque(lbm_batch *b, double *F, double *M)
 lbm_status lbm_batch_get_fiber_state(lbm_batch *b, double *X, double *q, double *V, double *W)
 {
     if (!b) return LBM_E_ARG;
-    lbm_status s = check_batch_errors(b);
-    if (s != LBM_OK) return s;
     std::vector<PState> h(size_t(b->ncase) * 2);
-    BHIP(b, hipMemcpy(h.data(), b->ps, h.size() * sizeof(PState), hipMemcpyDeviceToHost));
+    lbm_status s = check_batch_errors(b, b->ps, h.size() * sizeof(PState), h.data());
+    if (s != LBM_OK) return s;
     const int cur = int(b->steps & 1);
     for (int i = 0; i < b->ncase; ++i) {
         const PState &p = h[size_t(i) * 2 + cur];
@@ -1107,18 +1111,16 @@ lbm_status lbm_batch_get_fiber_state(lbm_batch *b, double *X, double *q, double 
 lbm_status lbm_batch_get_history(lbm_batch *b, int32_t c, int64_t first, int64_t count, double *out)
 {
     if (!b || !out || count < 0 || c < 0 || c >= b->ncase) return bfail(b, LBM_E_ARG, "bad argument");
-    lbm_status s = check_batch_errors(b);
-    if (s != LBM_OK) return s;
     const int64_t cap = b->p.history_capacity;
-    if (first < 0 || first + count > b->steps || first < b->steps - cap)
-        return bfail(b, LBM_E_ARG, "history window not available");
+    const bool window = first >= 0 && first + count <= b->steps && first >= b->steps - cap;
     const double *base = b->hist + size_t(c) * size_t(cap) * 19;
-    for (int64_t i = 0; i < count;) {
-        const int64_t slot = (first + i) % cap;
-        const int64_t run = std::min<int64_t>(count - i, cap - slot);
-        BHIP(b, hipMemcpy(out + i * 19, base + slot * 19, size_t(run) * 19 * sizeof(double), hipMemcpyDeviceToHost));
-        i += run;
-    }
+    // the window's run up to the ring's end with the errors, then the rest
+    const int64_t slot = window ? first % cap : 0, run = window ? std::min<int64_t>(count, cap - slot) : 0;
+    lbm_status s = check_batch_errors(b, base + slot * 19, size_t(run) * 19 * sizeof(double), out);
+    if (s != LBM_OK) return s;
+    if (!window) return bfail(b, LBM_E_ARG, "history window not available");
+    if (count > run)
+        BHIP(b, hipMemcpy(out + run * 19, base, size_t(count - run) * 19 * sizeof(double), hipMemcpyDeviceToHost));
     return LBM_OK;
 }
 
