@@ -44,8 +44,8 @@ HBM_PEAK_GBS = 8000.0
 # scaled by the counters' readings for a plain copy of known size.  Valid only
 # for the sources it was measured on (SHA-1 of sweep.hip followed by
 # lbm_sweep_dev.h, below); otherwise reported null.
-SWEEP_TRAFFIC = {"sweep_sha1": "0faaf7ca95c52b06ca254e84f08c38c1ffc95d3a",
-                 "bytes_per_launch": 2.5726e+09}
+SWEEP_TRAFFIC = {"sweep_sha1": "1f38325e61ccaaf5f94f81575a6f5143b53325c9",
+                 "bytes_per_launch": 2.5730e+09}
 # algorithmic bytes per lattice update of the bulk sweep: 19 loads + 19
 # stores of the population type + the 1-byte cell flag
 BYTES_PER_LUP = {"f32": 19 * 4 * 2 + 1, "f16": 19 * 2 * 2 + 1, "bf16": 19 * 2 * 2 + 1,
@@ -203,7 +203,8 @@ def time_sbf(torch, m=1024, steps=10, warmup=2):
     parameters) in free space; a step is the moments of every fiber pair,
     GMRES to 1e-10, the velocities and the Adams-Bashforth-2 update.
     Roofline of its two kernels: the moments (FP64 ALU: per pair
-    Q^2 (33 + 15 (N + 1)) + 21 Q (N + 1)^2 flops over m (m - 1)/2 pairs) and
+    Q^2 (35 + 4 (N + 1)) + 2 Q ((N + 1)^2 + (N + 3)^2) + 200 (N + 1)^2 flops
+    over m (m - 1)/2 pairs: scalar moments, their outer sums, the blocks) and
     the product with the symmetric moment matrix (HBM: its D (D + 1)/2
     distinct entries x 8 bytes, D = 3 m (N + 1))."""
     from paper_1503_06869_amd import scenarios, sbf
@@ -223,7 +224,7 @@ def time_sbf(torch, m=1024, steps=10, warmup=2):
     X, _ = g.state()
     g.close()
     Q, NP1 = 3 * nq, N + 1
-    flops = (m * (m - 1) / 2) * (Q * Q * (33 + 15 * NP1) + 21 * Q * NP1 * NP1)
+    flops = (m * (m - 1) / 2) * (Q * Q * (35 + 4 * NP1) + 2 * Q * (NP1 ** 2 + (NP1 + 2) ** 2) + 200 * NP1 * NP1)
     D = 3 * m * NP1
     th_ms, gv_ms = tm / nm, tg / ng
     return {"fibers": m, "modes": N, "quadrature_points": Q, "ms_per_step": round(wall * 1e3, 3),
