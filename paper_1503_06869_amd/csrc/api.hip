@@ -53,6 +53,7 @@ struct lbm_ctx {
     DevCounters *ctr = nullptr;
     Readback rb;
     uint32_t bnd_grid = 0, sweep_grid = 0;
+    uint32_t bulk_lds = 0;    // LDS reserved by a bulk workgroup beside the particle branch
     uint32_t nbulk = 0;       // small lattice: waves of the sweep inside the boundary launch
     int64_t steps = 0;
     int64_t device_bytes = 0;
@@ -281,6 +282,19 @@ static lbm_status upload_particles(lbm_ctx *c)
     }
     if (total >= 4294967295.0) return fail(c, LBM_E_ARG, "boundary list too large");
     c->list_cap = uint32_t(total);
+    // The 4096 workgroups of the 16-bit sweep fill every register of the card,
+    // and the particle branch finds room only as they end: with 64 fibers at
+    // 256^3 the odd boundary launch took 296 us, the mapping 250, and the branch
+    // outlasted the sweep.  Four workgroups a CU (36000 of 160 K bytes of LDS
+    // each) leave it room where the branch is the longer one: many fibers for
+    // the lattice, or a short sweep.  us a step with and without, at cells over
+    // list capacity: 256^3 FP16 342 and 352 (61), 333 and 338 (82), 330 and 325
+    // (122), 313 and 303 (245); 192^3 147 and 151 (104); 160^3 83 and 95 (60);
+    // 144^3 66 and 72 (88); 128^3 53 and 56 (300).
+    c->bulk_lds = c->esz == 2 && c->p.sweep_grid == 0 &&
+                          (c->g.ncell < 110ull * c->list_cap || c->g.ncell <= 4200000u)
+                      ? 36000u
+                      : 0u;
     HIPCHK(c, dalloc(c, &c->list_cell, c->list_cap));
     HIPCHK(c, dalloc(c, &c->list_mask, c->list_cap));
     HIPCHK(c, hipMemcpyAsync(c->seg_off, soff.data(), np * sizeof(uint32_t), hipMemcpyHostToDevice, c->st));
@@ -398,7 +412,7 @@ static void launch_one_step(lbm_ctx *c, int64_t step_index, bool with_events, hi
     double *sp_b = stab ? sp + 4 * size_t(c->sweep_grid) : nullptr;
     if (!c->np) {
         e = launch_sweep(c->sk, odd, c->f, c->flags[step_index & 1], c->g, c->ph, c->sweep_grid, c->st,
-                         with_events ? e0 : nullptr, with_events ? e1 : nullptr, su, sp);
+                         with_events ? e0 : nullptr, with_events ? e1 : nullptr, su, sp, 0u);
         if (e == hipSuccess && stab)
             e = launch_stab_update(c->sk, !odd, c->f, c->g, c->ph, c->stab, c->sweep_grid, c->cov, c->cov_cap, c->st);
         if (e != hipSuccess && *err == hipSuccess) *err = e;
@@ -446,7 +460,7 @@ static void launch_one_step(lbm_ctx *c, int64_t step_index, bool with_events, hi
         e = launch_boundary(c->sk, odd, c->f, c->g, c->ph, b, c->st2, su, sp_b, nullptr, 0u);
     if (e == hipSuccess)
         e = launch_sweep(c->sk, odd, c->f, c->flags[step_index & 1], c->g, c->ph, c->sweep_grid, c->st,
-                         with_events ? e0 : nullptr, with_events ? e1 : nullptr, su, sp);
+                         with_events ? e0 : nullptr, with_events ? e1 : nullptr, su, sp, c->bulk_lds);
     if (e == hipSuccess && bulk_first)
         e = launch_boundary(c->sk, odd, c->f, c->g, c->ph, b, c->st2, su, sp_b, nullptr, 0u);
     if (e == hipSuccess) e = launch_rigid(pd, c->g, c->st2);

@@ -264,10 +264,11 @@ constexpr uint32_t STAB_SCAN_GRID = 1024;
 
 // bulk sweep on st (bracketed by ev0/ev1 if given); skipped when the grid is
 // 0; with stab (else null) the stabilized collision writing its workgroup
-// sums to part
+// sums to part.  lds: bytes of LDS that each workgroup reserves (and does not
+// use), to bound how many of them a CU holds
 hipError_t launch_sweep(int sk, bool odd, void *f, const uint8_t *flags, const Geo &g, const Phys<double> &ph,
                         uint32_t sweep_grid, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1, const double *stab,
-                        double *part);
+                        double *part, uint32_t lds);
 // boundary cells of the list (update, links, momentum exchange), one launch
 // (boundary.hip); stab as for the sweep.  nbulk > 0: the bulk sweep too, 64
 // cells per wave (flags; part: nbulk slots of the bulk waves first)

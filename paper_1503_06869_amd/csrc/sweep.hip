@@ -147,7 +147,7 @@ __global__ __launch_bounds__(256) void k_copy(uint4 *__restrict__ dst, const uin
 template <typename S>
 static hipError_t sweep_t(bool odd, void *f, const uint8_t *flags, const Geo &g, const Phys<double> &ph,
                           uint32_t sweep_grid, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1,
-                          const double *stab, double *part)
+                          const double *stab, double *part, uint32_t lds)
 {
     using R = typename St<S>::R;
     const Phys<R> p = cast_phys<R>(ph);
@@ -156,14 +156,14 @@ static hipError_t sweep_t(bool odd, void *f, const uint8_t *flags, const Geo &g,
     const dim3 gr(sweep_grid), bl(256);
     const int mode = (odd ? 1 : 0) | (stab ? 2 : 0) | ((g.xw || g.yw || g.zs) ? 4 : 0);
     switch (mode) {
-    case 0: hipLaunchKernelGGL((k_sweep_bulk<S, false, false, false>), gr, bl, 0, st, (S *)f, flags, g, p, stab, part); break;
-    case 1: hipLaunchKernelGGL((k_sweep_bulk<S, true, false, false>), gr, bl, 0, st, (S *)f, flags, g, p, stab, part); break;
-    case 2: hipLaunchKernelGGL((k_sweep_bulk<S, false, true, false>), gr, bl, 0, st, (S *)f, flags, g, p, stab, part); break;
-    case 3: hipLaunchKernelGGL((k_sweep_bulk<S, true, true, false>), gr, bl, 0, st, (S *)f, flags, g, p, stab, part); break;
-    case 4: hipLaunchKernelGGL((k_sweep_bulk<S, false, false, true>), gr, bl, 0, st, (S *)f, flags, g, p, stab, part); break;
-    case 5: hipLaunchKernelGGL((k_sweep_bulk<S, true, false, true>), gr, bl, 0, st, (S *)f, flags, g, p, stab, part); break;
-    case 6: hipLaunchKernelGGL((k_sweep_bulk<S, false, true, true>), gr, bl, 0, st, (S *)f, flags, g, p, stab, part); break;
-    default: hipLaunchKernelGGL((k_sweep_bulk<S, true, true, true>), gr, bl, 0, st, (S *)f, flags, g, p, stab, part); break;
+    case 0: hipLaunchKernelGGL((k_sweep_bulk<S, false, false, false>), gr, bl, lds, st, (S *)f, flags, g, p, stab, part); break;
+    case 1: hipLaunchKernelGGL((k_sweep_bulk<S, true, false, false>), gr, bl, lds, st, (S *)f, flags, g, p, stab, part); break;
+    case 2: hipLaunchKernelGGL((k_sweep_bulk<S, false, true, false>), gr, bl, lds, st, (S *)f, flags, g, p, stab, part); break;
+    case 3: hipLaunchKernelGGL((k_sweep_bulk<S, true, true, false>), gr, bl, lds, st, (S *)f, flags, g, p, stab, part); break;
+    case 4: hipLaunchKernelGGL((k_sweep_bulk<S, false, false, true>), gr, bl, lds, st, (S *)f, flags, g, p, stab, part); break;
+    case 5: hipLaunchKernelGGL((k_sweep_bulk<S, true, false, true>), gr, bl, lds, st, (S *)f, flags, g, p, stab, part); break;
+    case 6: hipLaunchKernelGGL((k_sweep_bulk<S, false, true, true>), gr, bl, lds, st, (S *)f, flags, g, p, stab, part); break;
+    default: hipLaunchKernelGGL((k_sweep_bulk<S, true, true, true>), gr, bl, lds, st, (S *)f, flags, g, p, stab, part); break;
     }
     if (ev1) hipEventRecord(ev1, st);
     return hipGetLastError();
@@ -171,13 +171,13 @@ static hipError_t sweep_t(bool odd, void *f, const uint8_t *flags, const Geo &g,
 
 hipError_t launch_sweep(int sk, bool odd, void *f, const uint8_t *flags, const Geo &g, const Phys<double> &ph,
                         uint32_t sweep_grid, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1, const double *stab,
-                        double *part)
+                        double *part, uint32_t lds)
 {
     switch (sk) {
-    case S_F32: return sweep_t<float>(odd, f, flags, g, ph, sweep_grid, st, ev0, ev1, stab, part);
-    case S_F16: return sweep_t<_Float16>(odd, f, flags, g, ph, sweep_grid, st, ev0, ev1, stab, part);
-    case S_BF16: return sweep_t<bf16s>(odd, f, flags, g, ph, sweep_grid, st, ev0, ev1, stab, part);
-    default: return sweep_t<double>(odd, f, flags, g, ph, sweep_grid, st, ev0, ev1, stab, part);
+    case S_F32: return sweep_t<float>(odd, f, flags, g, ph, sweep_grid, st, ev0, ev1, stab, part, lds);
+    case S_F16: return sweep_t<_Float16>(odd, f, flags, g, ph, sweep_grid, st, ev0, ev1, stab, part, lds);
+    case S_BF16: return sweep_t<bf16s>(odd, f, flags, g, ph, sweep_grid, st, ev0, ev1, stab, part, lds);
+    default: return sweep_t<double>(odd, f, flags, g, ph, sweep_grid, st, ev0, ev1, stab, part, lds);
     }
 }
 

@@ -62,3 +62,15 @@ def test_one_and_two_branches_agree(shape, fibers, walls, storage):
     for x, y in zip(a, b):
         assert np.array_equal(x, y)
     assert np.isfinite(a[-1]).all()
+
+
+@pytest.mark.parametrize("storage", ["f16", "bf16"])
+@pytest.mark.parametrize("shape,n", [((127, 126, 128), 1), ((163, 160, 162), 1), ((163, 160, 162), 16)])
+def test_bulk_sweep_beside_the_branch(storage, shape, n):
+    """16-bit storage: the workgroups of the bulk sweep that leave the particle
+    branch room (small lattice; many fibers for the lattice) and those that do
+    not (an explicit grid; few fibers) do the same arithmetic."""
+    fibers = [([20.0 + 38.0 * (i % 4), 20.0 + 38.0 * (i // 4), 60.0], [0.5, 0.4, 0.1, 0.2], 24.0) for i in range(n)]
+    a, b = (run(shape, fibers, (1, 6, 2), grid, storage=storage, **WALLS["couette"]) for grid in (0, 512))
+    for x, y in zip(a, b):
+        assert np.array_equal(x, y)
