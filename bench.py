@@ -44,7 +44,7 @@ HBM_PEAK_GBS = 8000.0
 # scaled by the counters' readings for a plain copy of known size.  Valid only
 # for the sources it was measured on (SHA-1 of sweep.hip followed by
 # lbm_sweep_dev.h, below); otherwise reported null.
-SWEEP_TRAFFIC = {"sweep_sha1": "1f38325e61ccaaf5f94f81575a6f5143b53325c9",
+SWEEP_TRAFFIC = {"sweep_sha1": "eab16654fc5ad227e92e0626921d60e2b7133355",
                  "bytes_per_launch": 2.5730e+09}
 # algorithmic bytes per lattice update of the bulk sweep: 19 loads + 19
 # stores of the population type + the 1-byte cell flag
