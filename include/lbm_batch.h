@@ -99,7 +99,8 @@ lbm_status lbm_batch_set_kinematics(lbm_batch *b, int32_t c, const double *traj,
  * bins in {CU/2, CU, 2 CU, 4 CU} capped at ncases) and keep the fastest.
  * The trials run on the initial state, which is then restored; only before
  * the first step.  cache_path (may be NULL): a text file of earlier choices,
- * keyed by the case sizes, storage and device; read first and appended to. */
+ * keyed by the lattice and fiber sizes of the cases, storage, device and the
+ * layout of a step; read first and appended to. */
 lbm_status lbm_batch_autotune(lbm_batch *b, int32_t trial_steps, const char *cache_path,
                               lbm_batch_tuning *out);
 

@@ -689,16 +689,23 @@ static uint64_t fnv(uint64_t h, const void *p, size_t n)
     return h;
 }
 
+// Key of a choice in the tuning cache: everything that the timed work depends
+// on.  The particle phase, whose workgroups are tuned, works on the region
+// around each fiber, so the fibers' sizes count as the lattices do.  v2: that
+// phase in a launch of its own (before, a workgroup ran whole cases, and lines
+// without a version hold times of that).
 static std::string tune_key(const lbm_batch *b)
 {
     uint64_t h = 1469598103934665603ull;
     for (const auto &k : b->hc) {
-        const int32_t d[3] = {k.nx, k.ny, k.nz};
+        const int32_t d[4] = {k.nx, k.ny, k.nz, k.fiber.shape};
+        const double r[2] = {k.fiber.length, k.fiber.radius};
         h = fnv(h, d, sizeof d);
+        h = fnv(h, r, sizeof r);
     }
     h = fnv(h, &b->sk, sizeof b->sk);
     char buf[160];
-    std::snprintf(buf, sizeof buf, "%s-cu%d-n%d-%016llx", b->arch.c_str(), b->cu, b->ncase, (unsigned long long)h);
+    std::snprintf(buf, sizeof buf, "v2-%s-cu%d-n%d-%016llx", b->arch.c_str(), b->cu, b->ncase, (unsigned long long)h);
     return buf;
 }
 
