@@ -608,7 +608,15 @@ lbm_status lbm_create(const lbm_params *p, lbm_ctx **out)
     // two branches (FP32; FP16 alike): 32^3 with one fiber 29 and 38 us, 64^3
     // with six 35 and 44, 96^3 with twelve 56 and 60, 112^3 with sixteen 63 and
     // 71, 128^3 with two 71 and 70, 144^3 with four 93 and 85.
-    if (p->sweep_grid == 0 && g.ncell <= 1750000u) c->nbulk = (g.ncell + 63u) / 64u;
+    // With stabilization the waves take their cells in turn (STAB_WAVES) and the
+    // two branches win earlier, with two fibers: 64^3 43 and 58 us (FP16 42 and
+    // 58, FP64 51 and 62, side walls 45 and 57), 80^3 49 and 59 (45 and 48, 61
+    // and 69, 62 and 64), 96^3 58 and 65 (54 and 54, 77 and 84, 76 and 67), 112^3
+    // 70 and 73 (67 and 60, 100 and 109, 101 and 76).
+    if (p->sweep_grid == 0 && g.ncell <= (p->stabilize ? 700000u : 1750000u)) {
+        c->nbulk = (g.ncell + 63u) / 64u;
+        if (p->stabilize) c->nbulk = std::min(c->nbulk, STAB_WAVES);
+    }
     g.dnx = make_fastdiv(g.nx);
     g.dnxy = make_fastdiv(g.nxy);
     g.zper = p->z_periodic ? 1 : 0;

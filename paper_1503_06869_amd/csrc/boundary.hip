@@ -117,9 +117,10 @@ __device__ __forceinline__ void wave_sum4(const double (&v)[4], double *out)
 // workgroups launched after it start late and the sweep stretches.
 // Grid: np * bpf waves; wave (fiber p, part j) takes entries 64 j, 64 (j +
 // bpf), ... of the fiber's list segment.
-// nbulk further waves take 64 cells each of the bulk sweep.  STAB: momentum
-// stabilization (mean velocity stab[0..2]; every wave writes its sums to a
-// slot of part, the bulk waves first).  XYW: walls on the x and/or y faces.
+// nbulk further waves take the cells of the bulk sweep, 64 each (STAB: 64 at a
+// time, strided).  STAB: momentum stabilization (mean velocity stab[0..2]; every
+// wave writes its sums to a slot of part, the bulk waves first).  XYW: walls on
+// the x and/or y faces.
 template <typename S, bool ODD, bool STAB, bool XYW>
 __global__ __launch_bounds__(64, 2) void k_boundary(S *__restrict__ f, Geo g, Phys<typename St<S>::R> ph, BndData b,
                                                     const double *stab, double *part,
@@ -133,12 +134,25 @@ __global__ __launch_bounds__(64, 2) void k_boundary(S *__restrict__ f, Geo g, Ph
     StabAcc<R> st;
     if constexpr (STAB) stab_begin(st, stab);
     if (blockIdx.x >= nb) {   // wave-uniform
-        const uint32_t k = xcd_block(blockIdx.x - nb, nbulk), cell = k * 64u + lane;
+        const uint32_t k = xcd_block(blockIdx.x - nb, nbulk);
         NoLinks none;
-        if (cell < g.ncell && !flags[cell]) update_cell<S, ODD, false, STAB, XYW>(f, g, ph, cell, 0u, none, &st);
         if constexpr (STAB) {
-            const double t[4] = {double(st.j[0]), double(st.j[1]), double(st.j[2]), double(st.n)};
+            // strided: every wave leaves a slot that one workgroup adds up at
+            // the end of the step, so there are few of them (STAB_WAVES)
+            double t[4] = {0.0, 0.0, 0.0, 0.0};
+            for (uint32_t cell = k * 64u + lane; cell < g.ncell; cell += nbulk * 64u) {
+                if (flags[cell]) continue;
+                update_cell<S, ODD, false, STAB, XYW>(f, g, ph, cell, 0u, none, &st);
+                for (int e = 0; e < 3; ++e) {
+                    t[e] += double(st.j[e]);
+                    st.j[e] = R(0);
+                }
+                t[3] += 1.0;
+            }
             wave_sum4(t, part + 4 * size_t(k));
+        } else {
+            const uint32_t cell = k * 64u + lane;
+            if (cell < g.ncell && !flags[cell]) update_cell<S, ODD, false, STAB, XYW>(f, g, ph, cell, 0u, none, &st);
         }
         return;
     }

@@ -261,6 +261,11 @@ hipError_t launch_stab_update(int sk, bool swapped, const void *f, const Geo &g,
 hipError_t launch_stab_scan(int sk, bool swapped, const void *f, const int32_t *pid, const Geo &g,
                             const Phys<double> &ph, double *stab, uint32_t *cov, hipStream_t st);
 constexpr uint32_t STAB_SCAN_GRID = 1024;
+// bulk waves of the boundary launch at most: more slots take k_stab_update
+// longer than the waves gain.  96^3 FP32 with two fibers, us a step at 512,
+// 1024, 1536, 2048, 4096 waves and one per 64 cells (13824): 78, 61, 58, 61,
+// 62, 67; 64^3 48, 44, 43, 44, 45, 45
+constexpr uint32_t STAB_WAVES = 1536;
 
 // bulk sweep on st (bracketed by ev0/ev1 if given); skipped when the grid is
 // 0; with stab (else null) the stabilized collision writing its workgroup
@@ -270,8 +275,9 @@ hipError_t launch_sweep(int sk, bool odd, void *f, const uint8_t *flags, const G
                         uint32_t sweep_grid, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1, const double *stab,
                         double *part, uint32_t lds);
 // boundary cells of the list (update, links, momentum exchange), one launch
-// (boundary.hip); stab as for the sweep.  nbulk > 0: the bulk sweep too, 64
-// cells per wave (flags; part: nbulk slots of the bulk waves first)
+// (boundary.hip); stab as for the sweep.  nbulk > 0: the bulk sweep too, by
+// nbulk waves of 64 cells each, or with stab as many as it takes (flags; part:
+// nbulk slots of the bulk waves first)
 hipError_t launch_boundary(int sk, bool odd, void *f, const Geo &g, const Phys<double> &ph, const BndData &b,
                            hipStream_t st, const double *stab, double *part, const uint8_t *flags, uint32_t nbulk);
 hipError_t launch_decode(int sk, bool swapped, const void *f, const uint8_t *flags,

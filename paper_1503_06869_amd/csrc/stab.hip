@@ -47,8 +47,22 @@ __global__ __launch_bounds__(256) void k_stab_update(const S *__restrict__ f, Ge
     using R = typename St<S>::R;
     const double *part = stab + STAB_HEAD;
     double a[4] = {0.0, 0.0, 0.0, 0.0};
-    for (uint32_t s = threadIdx.x; s < nslot; s += blockDim.x)
-        for (int k = 0; k < 4; ++k) a[k] += part[4 * size_t(s) + k];
+    // eight slots a thread in flight: a slot at a time, each round of 256 waits
+    // for memory before the next
+    constexpr uint32_t NF = 8;
+    for (uint32_t s0 = threadIdx.x; s0 < nslot; s0 += NF * blockDim.x) {
+        double v[NF][4];
+#pragma unroll
+        for (uint32_t u = 0; u < NF; ++u) {
+            const uint32_t s = s0 + u * blockDim.x;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[u][k] = s < nslot ? part[4 * size_t(s) + k] : 0.0;
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < NF; ++u)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) a[k] += v[u][k];
+    }
     // changed cells in fixed point (2^-32): exact, so the list order (set by
     // atomics) does not change the result
     long long c[4] = {0, 0, 0, 0};
