@@ -9,16 +9,12 @@
 namespace lbm {
 
 // ------------------------------------------------------------------ storage
-// Collision type R; a stored value (Raw) is read by raw() and converted by
-// val(), apart where the conversion must not wait for the load.
+// collision type R, and the load and store of a stored value
 template <typename S>
 struct St;
 template <>
 struct St<float> {
     using R = float;
-    using Raw = float;
-    static __device__ __forceinline__ Raw raw(const float *p, uint64_t i) { return p[i]; }
-    static __device__ __forceinline__ float val(Raw v, float) { return v; }
     static __device__ __forceinline__ float ld(const float *p, uint64_t i, float) { return p[i]; }
     static __device__ __forceinline__ void st(float *p, uint64_t i, float v, float)
     {
@@ -28,9 +24,6 @@ struct St<float> {
 template <>
 struct St<double> {
     using R = double;
-    using Raw = double;
-    static __device__ __forceinline__ Raw raw(const double *p, uint64_t i) { return p[i]; }
-    static __device__ __forceinline__ double val(Raw v, double) { return v; }
     static __device__ __forceinline__ double ld(const double *p, uint64_t i, double) { return p[i]; }
     static __device__ __forceinline__ void st(double *p, uint64_t i, double v, double)
     {
@@ -40,10 +33,10 @@ struct St<double> {
 template <>
 struct St<_Float16> {
     using R = float;
-    using Raw = _Float16;
-    static __device__ __forceinline__ Raw raw(const _Float16 *p, uint64_t i) { return p[i]; }
-    static __device__ __forceinline__ float val(Raw v, float inv) { return float(v) * inv; }
-    static __device__ __forceinline__ float ld(const _Float16 *p, uint64_t i, float inv) { return val(raw(p, i), inv); }
+    static __device__ __forceinline__ float ld(const _Float16 *p, uint64_t i, float inv)
+    {
+        return float(p[i]) * inv;
+    }
     static __device__ __forceinline__ void st(_Float16 *p, uint64_t i, float v, float scale)
     {
         __builtin_nontemporal_store(_Float16(v * scale), p + i);   // v_cvt_f16_f32: RNE
@@ -55,13 +48,11 @@ struct bf16s {
 template <>
 struct St<bf16s> {
     using R = float;
-    using Raw = uint16_t;
-    static __device__ __forceinline__ Raw raw(const bf16s *p, uint64_t i)
+    static __device__ __forceinline__ float ld(const bf16s *p, uint64_t i, float)
     {
-        return reinterpret_cast<const uint16_t *>(p)[i];
+        const uint16_t *u = reinterpret_cast<const uint16_t *>(p);
+        return __uint_as_float(uint32_t(u[i]) << 16);
     }
-    static __device__ __forceinline__ float val(Raw v, float) { return __uint_as_float(uint32_t(v) << 16); }
-    static __device__ __forceinline__ float ld(const bf16s *p, uint64_t i, float inv) { return val(raw(p, i), inv); }
     static __device__ __forceinline__ void st(bf16s *p, uint64_t i, float v, float)
     {
         uint32_t u = __float_as_uint(v);
@@ -344,9 +335,6 @@ struct NoLinks {
 // refl(q) of x + t, which no other cell touches in that sweep (the slot it
 // gathered from for the reverse link), so both sweeps stay in place.  A
 // link that crosses walls of both kinds bounces back.
-// The update is in two parts, the gather of a cell's populations and
-// everything after it, so that a loop over cells can gather the next cell
-// before it finishes this one (the slots of different cells are disjoint).
 struct CellPos {
     uint32_t x, y, z;
     uint32_t xo[3], yo[3], zo[3];   // offsets of the neighbours' coordinates (wrapped; planes shifted by one)
@@ -393,17 +381,21 @@ __device__ __forceinline__ CellWalls cell_walls(const Geo &g, const CellPos &c)
     return w;
 }
 
-template <typename S, bool ODD, bool XYW>
-__device__ __forceinline__ void gather_cell(const S *__restrict__ f, const Geo &g, const CellPos &c,
-                                            typename St<S>::Raw (&rv)[Q])
+template <typename S, bool ODD, bool BND, bool STAB, bool XYW, typename Sink>
+__device__ __forceinline__ void update_cell(S *__restrict__ f, const Geo &g, const Phys<typename St<S>::R> &ph,
+                                            uint32_t cell, uint32_t mask, Sink &sink,
+                                            StabAcc<typename St<S>::R> *sa = nullptr)
 {
+    using R = typename St<S>::R;
     const uint64_t qs = g.qstride;
-    CellWalls w{};
-    if constexpr (ODD && XYW) w = cell_walls<XYW>(g, c);
+    const R inv = ph.inv_scale, sc = ph.scale;
+    const CellPos c = cell_pos(g, cell);
+    const CellWalls w = cell_walls<XYW>(g, c);
+    R fv[Q];
     static_for<0, Q>([&](auto qc) {
         constexpr int q = decltype(qc)::value;
         if (!ODD) {
-            rv[q] = St<S>::raw(f, uint64_t(q) * qs + c.own);
+            fv[q] = St<S>::ld(f, uint64_t(q) * qs + c.own, inv);
         } else {
             if constexpr (XYW) {
                 if (w.any) {
@@ -419,28 +411,14 @@ __device__ __forceinline__ void gather_cell(const S *__restrict__ f, const Geo &
                     uint32_t src = (iz ? c.zo[1] : c.zo[1 - CZ[q]]) + (iy ? c.yo[1] : c.yo[1 - CY[q]]) +
                                    (ix ? c.xo[1] : c.xo[1 - CX[q]]);
                     src = side_in ? c.own : src;
-                    rv[q] = St<S>::raw(f, slot_sel<q, true>(m, side_in, qs) + src);
+                    fv[q] = St<S>::ld(f, slot_sel<q, true>(m, side_in, qs) + src, inv);
                     return;
                 }
             }
             const uint32_t src = c.zo[1 - CZ[q]] + c.yo[1 - CY[q]] + c.xo[1 - CX[q]];
-            rv[q] = St<S>::raw(f, uint64_t(opp(q)) * qs + src);
+            fv[q] = St<S>::ld(f, uint64_t(opp(q)) * qs + src, inv);
         }
     });
-}
-
-template <typename S, bool ODD, bool BND, bool STAB, bool XYW, typename Sink>
-__device__ __forceinline__ void finish_cell(S *__restrict__ f, const Geo &g, const Phys<typename St<S>::R> &ph,
-                                            const CellPos &c, const typename St<S>::Raw (&rv)[Q], uint32_t mask, Sink &sink,
-                                            StabAcc<typename St<S>::R> *sa = nullptr)
-{
-    using R = typename St<S>::R;
-    const uint64_t qs = g.qstride;
-    const R sc = ph.scale;
-    const CellWalls w = cell_walls<XYW>(g, c);
-    R fv[Q];
-#pragma unroll
-    for (int q = 0; q < Q; ++q) fv[q] = St<S>::val(rv[q], ph.inv_scale);
     // the forms that round a pair's second value in two steps (collide)
     constexpr bool split = BND || STAB || (ODD && (XYW || std::is_same_v<S, bf16s>));
     collide<R, split, STAB>(fv, ph, R(1) / ph.rho0, sa);
@@ -508,17 +486,6 @@ __device__ __forceinline__ void finish_cell(S *__restrict__ f, const Geo &g, con
     });
     (void)six_r0;
     (void)sink;
-}
-
-template <typename S, bool ODD, bool BND, bool STAB, bool XYW, typename Sink>
-__device__ __forceinline__ void update_cell(S *__restrict__ f, const Geo &g, const Phys<typename St<S>::R> &ph,
-                                            uint32_t cell, uint32_t mask, Sink &sink,
-                                            StabAcc<typename St<S>::R> *sa = nullptr)
-{
-    typename St<S>::Raw rv[Q];
-    const CellPos c = cell_pos(g, cell);
-    gather_cell<S, ODD, XYW>(f, g, c, rv);
-    finish_cell<S, ODD, BND, STAB, XYW>(f, g, ph, c, rv, mask, sink, sa);
 }
 
 // The moving-obstacle bounce-back (Eq. LBMMovWall) of one fiber link from
