@@ -582,12 +582,19 @@ lbm_status lbm_create(const lbm_params *p, lbm_ctx **out)
         const uint32_t nchunk = uint32_t((double(p->nx) * p->ny * p->nz + 255.0) / 256.0);
         // measured: FP32/FP64 best near 512 workgroups (256^3: 507 us against
         // 520 at 768 and 548 at 1024), 16-bit storage near 4096 (280 us, 360
-        // at 512, 302 at 1024); with walls on the x or y faces or free-slip z
-        // walls the odd sweep selects its sources and 768 hide that
-        // arithmetic better (160^2 x 1200: 983 us against 1076 at 512 and 1013
-        // at 1024)
-        const bool walls = p->x_walls || p->y_walls || p->z_free_slip;
-        const uint32_t dflt = (p->storage == LBM_F16DEV || p->storage == LBM_BF16DEV) ? 4096u : (walls ? 768u : 512u);
+        // at 512, 302 at 1024).  With walls on the x or y faces 768 hide the
+        // selection of the sources better in FP32, given four rounds of
+        // chunks: odd sweep at 512, 768 and 1024, us, box closed by no-slip
+        // walls (by free-slip walls): 160^2 x 1200 952, 851, 1037 (939, 949,
+        // 848), 256^3 605, 530, 530 (596, 520, 521), 128^3 71, 63, 73 (68, 61,
+        // 72), 96^3 36, 34, 35, but 64^3, 1024 chunks, 14.6, 17.1, 13.2.  With
+        // free-slip z walls alone few waves select: 160^2 x 1200 799, 827, 858.
+        // FP64 gains nothing (192^3 448, 478, 472; 160^2 x 1200 1655, 1784, 1722;
+        // 256^3 1005, 1069, 1062).
+        const bool sides = p->x_walls || p->y_walls;
+        const uint32_t dflt = (p->storage == LBM_F16DEV || p->storage == LBM_BF16DEV) ? 4096u
+                              : (sides && p->storage == LBM_F32 && nchunk >= 3072u)  ? 768u
+                                                                                      : 512u;
         uint32_t gsz = p->sweep_grid > 0 ? uint32_t(p->sweep_grid) : dflt;
         c->sweep_grid = gsz < nchunk ? gsz : nchunk;
     }

@@ -31,7 +31,11 @@ namespace lbm {
 // mixes reads and writes and takes 551).
 // STAB: momentum stabilization; stab[0..2] is the mean velocity the
 // collisions subtract, and workgroup b writes its sums to part[4 b .. 4 b + 3].
-// XYW: walls on the x and/or y faces.
+// XYW: walls on the x and/or y faces (or free-slip z walls).  Its odd sweep lets a
+// wave take another quarter of each chunk: waves at a wall are the slower
+// ones, and where rows are whole waves the same wave would meet the wall in
+// every chunk, its fellows run ahead and the band fall apart (256^3 FP32, 768
+// workgroups, closed box: 617 us without, 530 with; 192^3 275 and 236).
 template <typename S, bool ODD, bool STAB, bool XYW>
 __global__ __launch_bounds__(256) void k_sweep_bulk(S *__restrict__ f, const uint8_t *__restrict__ flags,
                                                     Geo g, Phys<typename St<S>::R> ph, const double *stab,
@@ -42,8 +46,10 @@ __global__ __launch_bounds__(256) void k_sweep_bulk(S *__restrict__ f, const uin
     NoLinks none;
     if constexpr (STAB) stab_begin(sa, stab);
     const uint32_t nchunk = (g.ncell + 255u) >> 8;
+    uint32_t at = threadIdx.x;
     for (uint32_t ch = xcd_block(blockIdx.x, gridDim.x); ch < nchunk; ch += gridDim.x) {
-        const uint32_t cell = (ch << 8) + threadIdx.x;
+        const uint32_t cell = (ch << 8) + at;
+        if constexpr (ODD && XYW) at = (at + 64u) & 255u;
         if (cell < g.ncell && !flags[cell])   // fiber cells idle; boundary cells: k_boundary
             update_cell<S, ODD, false, STAB, XYW>(f, g, ph, cell, 0u, none, &sa);
     }
