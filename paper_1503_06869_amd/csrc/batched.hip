@@ -136,12 +136,12 @@ struct OwnLinks {
 
 // ------------------------------------------------------------------ sweep of all cases
 // Workgroups [0, nblk) take the boundary cells of the cases, 256 list entries
-// of one case at a time; the others stride over the 256-cell chunks of all
-// cases together, so that the card works on one compact band of memory and
-// the cases' sizes do not matter.  Bound by HBM: 512 cases of edges 24 to 64
-// in FP32, 1.43 ms for the bulk cells (4.6 TB/s) and 1.64 with the boundary
-// cells, whose lines are scattered; with a workgroup to a case, all steps in a
-// row, the sweep took 1.80 ms, as the cases of one edge 64 outlast the rest.
+// of one case at a time; the others take the 256-cell chunks of all cases
+// together, so that the card works on one compact band of memory and the
+// cases' sizes do not matter.  Bound by HBM: 512 cases of edges 24 to 64 in
+// FP32, 1.38 ms the even and 1.44 the odd sweep (4.8 and 4.5 TB/s) with the
+// scattered lines of the boundary cells; with a workgroup to a case, all steps
+// in a row, the sweep took 1.80 ms, as the cases of one edge 64 outlast the rest.
 template <typename S, bool ODD>
 __global__ __launch_bounds__(256, 3) void k_bsweep(BatchDev bd, S *__restrict__ f, const uint8_t *__restrict__ flags,
                                                 const CaseDev *__restrict__ cases,
@@ -878,11 +878,18 @@ lbm_status lbm_batch_create(const lbm_batch_params *p, const lbm_batch_case *cas
     }
     b->nchunk = uint32_t(chunk.size());
     b->nblk = uint32_t(blk.size() / 2);
-    // workgroups that stride over the chunks: three a CU are resident.  512
-    // cases of edges 24 to 64 (43 million cells), ms a step at two, three, four
-    // and sixteen a CU: FP32 1.95, 1.76, 1.97, 1.75; FP16 1.43, 1.09, 1.35,
-    // 1.11; FP64 3.83, 3.47, 3.47, 2.80.
-    b->sweep_grid = std::min(b->nchunk, uint32_t((b->sk == S_F64 ? 16 : 3) * b->cu));
+    // workgroups that stride over the chunks (2^23 at most: a launch holds fewer
+    // than 2^32 lanes): one per chunk in FP32 and FP64, which the dispatch
+    // order keeps as compact a band as few resident ones, and no round is left
+    // half empty; 32 a CU in 16-bit storage, where a chunk is too short to pay
+    // for its workgroup.  us a step at 3, 32 and 128 a CU and one per chunk:
+    //   FP32 512 cases of edges 24-64 1837, 1759, 1697, 1586; 512 of 24-32 564,
+    //   534, 506, 512; 64 of 48-64 522, 494, 470, 465; 8 of 100-120 456, 439, 417,
+    //   415; 2 of 140-160 313, 297, 291, 290.  FP64 3571, 3465, 3418, 3254; 1035,
+    //   993, 974, 967; 955, 909, 873, 862; 862, 827, 773, 741; 554, 540, 508, 515.
+    //   FP16 1081, 1063, 1054, 1202; 371, 369, 394, 404; 335, 333, 349, 358; 310,
+    //   309, 325, 333; 226, 192, 193, 194.
+    b->sweep_grid = std::min(b->nchunk, b->esz == 2 ? uint32_t(32 * b->cu) : 1u << 23);
     if (hipMalloc(&b->f, b->nf * b->esz) != hipSuccess) return bail(LBM_E_NOMEM, "populations");
     b->device_bytes += int64_t(b->nf * b->esz);
     if (balloc(b, &b->cases, ncases) != hipSuccess || balloc(b, &b->flags, b->ncells) != hipSuccess ||
