@@ -434,7 +434,7 @@ static void launch_one_step(lbm_ctx *c, int64_t step_index, bool with_events, hi
     if (c->nbulk && !with_events) {
         // small lattice: one branch, the sweep inside the boundary launch
         if (e == hipSuccess)
-            e = launch_boundary(c->sk, odd, c->f, c->g, c->ph, b, c->st, su, sp, c->flags[step_index & 1], c->nbulk);
+            e = launch_boundary(c->sk, odd, c->f, c->g, c->ph, b, c->st, su, sp, c->flags[step_index & 1], c->nbulk, 0u);
         if (e == hipSuccess) e = launch_rigid(pd, c->g, c->st);
         if (e == hipSuccess)
             e = launch_map(c->sk, !odd, c->f, c->pid, c->flags[(step_index + 1) & 1], c->list_cell, c->list_mask, pd,
@@ -449,20 +449,26 @@ static void launch_one_step(lbm_ctx *c, int64_t step_index, bool with_events, hi
     if (e == hipSuccess) e = hipStreamWaitEvent(c->st2, c->ev_fork, 0);
     // Launch order of the two branches (measured): the branch expected to be
     // longer goes first.  A resident grid-stride bulk grid (up to 1024
-    // workgroups, FP32/FP64) over a lattice large against the boundary list
-    // (256^3 with 64 fibers) goes first, since all its workgroups must start
-    // together; the boundary launch goes first when the bulk grid is large
-    // (16-bit storage: it would hold the boundary workgroups off until it
-    // drains) or the lattice is small against the list (128^3 with 200
-    // fibers: the particle branch is the longer one).
-    const bool bulk_first = c->sweep_grid <= 1024u && uint64_t(c->g.ncell) >= 32ull * c->list_cap;
+    // workgroups, FP32/FP64) goes first over a lattice that is large against
+    // the boundary list (160^3 with 16 fibers 135 us a step, 141 after the
+    // boundary launch) or large itself, beyond the memory-side cache (192^3 with
+    // 100 fibers 346 and 355 us, 256^3 with 200 688 and 733, 320^3 with 250 1140
+    // and 1240; FP64 256^3 with 300 1455 and 1516), since all its workgroups
+    // must start together.  The boundary launch goes first when the bulk grid
+    // is large (16-bit storage: it would hold the boundary workgroups off
+    // until it drains) or a lattice is small in both ways, so that the particle
+    // branch is the longer one (128^3 with 200 fibers 142 and 150 us, 160^3 with
+    // 100 178 and 186, 176^3 with 60 214 and 220).
+    const bool bulk_first =
+        c->sweep_grid <= 1024u && (uint64_t(c->g.ncell) >= 32ull * c->list_cap || c->g.ncell >= 6000000u);
+    const uint32_t bnd_lds = c->sk == S_F32 ? BND_LDS : 0u;
     if (e == hipSuccess && !bulk_first)
-        e = launch_boundary(c->sk, odd, c->f, c->g, c->ph, b, c->st2, su, sp_b, nullptr, 0u);
+        e = launch_boundary(c->sk, odd, c->f, c->g, c->ph, b, c->st2, su, sp_b, nullptr, 0u, bnd_lds);
     if (e == hipSuccess)
         e = launch_sweep(c->sk, odd, c->f, c->flags[step_index & 1], c->g, c->ph, c->sweep_grid, c->st,
                          with_events ? e0 : nullptr, with_events ? e1 : nullptr, su, sp, c->bulk_lds);
     if (e == hipSuccess && bulk_first)
-        e = launch_boundary(c->sk, odd, c->f, c->g, c->ph, b, c->st2, su, sp_b, nullptr, 0u);
+        e = launch_boundary(c->sk, odd, c->f, c->g, c->ph, b, c->st2, su, sp_b, nullptr, 0u, bnd_lds);
     if (e == hipSuccess) e = launch_rigid(pd, c->g, c->st2);
     if (e == hipSuccess)
         e = launch_map(c->sk, !odd, c->f, c->pid, c->flags[(step_index + 1) & 1], c->list_cell, c->list_mask, pd, c->g,

@@ -111,10 +111,11 @@ __device__ __forceinline__ void wave_sum4(const double (&v)[4], double *out)
     }
 }
 
-// Register budget: the bulk sweep keeps 2 waves of 80 VGPRs per SIMD
-// resident for its whole grid-stride run; this kernel runs beside it with
-// up to 2 waves per SIMD, so it must stay within 176 VGPRs, or bulk
-// workgroups launched after it start late and the sweep stretches.
+// Beside the FP32 bulk sweep, whose two waves a SIMD stay resident for its
+// whole grid-stride run, this kernel must leave them room: of its own waves
+// (158 to 186 VGPRs) three fill a SIMD, and bulk workgroups that come after them
+// then sit unevenly on the card and the sweep stretches by half.  The launch
+// reserves LDS (BND_LDS) so that a CU holds four.
 // Grid: np * bpf waves; wave (fiber p, part j) takes entries 64 j, 64 (j +
 // bpf), ... of the fiber's list segment.
 // nbulk further waves take the cells of the bulk sweep, 64 each (STAB: 64 at a
@@ -259,34 +260,36 @@ __global__ __launch_bounds__(64, 2) void k_boundary(S *__restrict__ f, Geo g, Ph
 
 template <typename S>
 static hipError_t boundary_t(bool odd, void *f, const Geo &g, const Phys<double> &ph, const BndData &b,
-                             hipStream_t st, const double *stab, double *part, const uint8_t *flags, uint32_t nbulk)
+                             hipStream_t st, const double *stab, double *part, const uint8_t *flags, uint32_t nbulk,
+                             uint32_t lds)
 {
     using R = typename St<S>::R;
     const Phys<R> p = cast_phys<R>(ph);
     const dim3 grid(uint32_t(b.np * b.bpf) + nbulk), bl(64);
     const int mode = (odd ? 1 : 0) | (stab ? 2 : 0) | ((g.xw || g.yw || g.zs) ? 4 : 0);
     switch (mode) {
-    case 0: hipLaunchKernelGGL((k_boundary<S, false, false, false>), grid, bl, 0, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
-    case 1: hipLaunchKernelGGL((k_boundary<S, true, false, false>), grid, bl, 0, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
-    case 2: hipLaunchKernelGGL((k_boundary<S, false, true, false>), grid, bl, 0, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
-    case 3: hipLaunchKernelGGL((k_boundary<S, true, true, false>), grid, bl, 0, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
-    case 4: hipLaunchKernelGGL((k_boundary<S, false, false, true>), grid, bl, 0, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
-    case 5: hipLaunchKernelGGL((k_boundary<S, true, false, true>), grid, bl, 0, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
-    case 6: hipLaunchKernelGGL((k_boundary<S, false, true, true>), grid, bl, 0, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
-    default: hipLaunchKernelGGL((k_boundary<S, true, true, true>), grid, bl, 0, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
+    case 0: hipLaunchKernelGGL((k_boundary<S, false, false, false>), grid, bl, lds, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
+    case 1: hipLaunchKernelGGL((k_boundary<S, true, false, false>), grid, bl, lds, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
+    case 2: hipLaunchKernelGGL((k_boundary<S, false, true, false>), grid, bl, lds, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
+    case 3: hipLaunchKernelGGL((k_boundary<S, true, true, false>), grid, bl, lds, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
+    case 4: hipLaunchKernelGGL((k_boundary<S, false, false, true>), grid, bl, lds, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
+    case 5: hipLaunchKernelGGL((k_boundary<S, true, false, true>), grid, bl, lds, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
+    case 6: hipLaunchKernelGGL((k_boundary<S, false, true, true>), grid, bl, lds, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
+    default: hipLaunchKernelGGL((k_boundary<S, true, true, true>), grid, bl, lds, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
     }
     return hipGetLastError();
 }
 
 hipError_t launch_boundary(int sk, bool odd, void *f, const Geo &g, const Phys<double> &ph, const BndData &b,
-                           hipStream_t st, const double *stab, double *part, const uint8_t *flags, uint32_t nbulk)
+                           hipStream_t st, const double *stab, double *part, const uint8_t *flags, uint32_t nbulk,
+                           uint32_t lds)
 {
     if (b.np <= 0 || b.bpf <= 0) return hipSuccess;
     switch (sk) {
-    case S_F32: return boundary_t<float>(odd, f, g, ph, b, st, stab, part, flags, nbulk);
-    case S_F16: return boundary_t<_Float16>(odd, f, g, ph, b, st, stab, part, flags, nbulk);
-    case S_BF16: return boundary_t<bf16s>(odd, f, g, ph, b, st, stab, part, flags, nbulk);
-    default: return boundary_t<double>(odd, f, g, ph, b, st, stab, part, flags, nbulk);
+    case S_F32: return boundary_t<float>(odd, f, g, ph, b, st, stab, part, flags, nbulk, lds);
+    case S_F16: return boundary_t<_Float16>(odd, f, g, ph, b, st, stab, part, flags, nbulk, lds);
+    case S_BF16: return boundary_t<bf16s>(odd, f, g, ph, b, st, stab, part, flags, nbulk, lds);
+    default: return boundary_t<double>(odd, f, g, ph, b, st, stab, part, flags, nbulk, lds);
     }
 }
 

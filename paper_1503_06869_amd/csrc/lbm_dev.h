@@ -277,9 +277,17 @@ hipError_t launch_sweep(int sk, bool odd, void *f, const uint8_t *flags, const G
 // boundary cells of the list (update, links, momentum exchange), one launch
 // (boundary.hip); stab as for the sweep.  nbulk > 0: the bulk sweep too, by
 // nbulk waves of 64 cells each, or with stab as many as it takes (flags; part:
-// nbulk slots of the bulk waves first)
+// nbulk slots of the bulk waves first).  lds: bytes of LDS that each wave
+// reserves beside its own, to bound how many of them a CU holds
 hipError_t launch_boundary(int sk, bool odd, void *f, const Geo &g, const Phys<double> &ph, const BndData &b,
-                           hipStream_t st, const double *stab, double *part, const uint8_t *flags, uint32_t nbulk);
+                           hipStream_t st, const double *stab, double *part, const uint8_t *flags, uint32_t nbulk,
+                           uint32_t lds);
+// Reserved beside the FP32 sweep: with the wave's own 9472, four waves in the
+// 160 K of a CU.  Step in us at 0, 18000, 24000, 31000, 42000 and 70000 bytes:
+// 256^3 with 110 fibers 716, 601, 657, 660, 650, 646; 200 fibers 912, 692, 689,
+// 616, 690, 612; 64 fibers 560, 558, 558, 556, 554, 549; 320^3 with 100 1426,
+// 1170, 1171, 1142, 1140, 1165; 160^3 with 16 129, 129, 129, 131, 136, 138.
+constexpr uint32_t BND_LDS = 24000;
 hipError_t launch_decode(int sk, bool swapped, const void *f, const uint8_t *flags,
                          const int32_t *pid, const PState *ps, const Geo &g, const Phys<double> &ph,
                          void *rho, void *u, double *fout, hipStream_t st);
