@@ -102,6 +102,28 @@ __device__ __forceinline__ uint32_t claims(const PState &s, const PConst &c, int
     return m;
 }
 
+// The predicate at the cell alone (bit 0, as in claims) and whether a
+// neighbour may be inside (bit 1; all but exact with `quick`).
+__device__ __forceinline__ uint32_t claim_or_near(const PState &s, const PConst &c, int32_t x, int32_t y, int32_t z,
+                                                  const Geo &g, bool quick)
+{
+    const double dx = mi_d(double(x) - s.X[0], g.nx, true);
+    const double dy = mi_d(double(y) - s.X[1], g.ny, true);
+    const double dz = mi_d(double(z) - s.X[2], g.nz, g.zper != 0);
+    const double a = dx * s.t[0] + dy * s.t[1] + dz * s.t[2];
+    const double q = (dx * dx + dy * dy + dz * dz) - a * a;
+    const double hl = 0.5 * c.length, r2 = c.radius * c.radius, rr = c.radius + 1.5;
+    const uint32_t near = !quick || !(fabs(a) > hl + 1.5 || q > rr * rr) ? 2u : 0u;
+    bool in;
+    if (c.shape == 1) {
+        const double e = fabs(a) - (hl - c.radius);
+        in = e <= 0.0 ? q <= r2 : q + e * e <= r2;
+    } else {
+        in = (a * a <= hl * hl) && (q <= r2);
+    }
+    return near | (in ? 1u : 0u);
+}
+
 // whether a cell and its neighbours see a fiber through the same periodic image
 __device__ __forceinline__ bool quick_claims(const PConst &c, const Geo &g)
 {
