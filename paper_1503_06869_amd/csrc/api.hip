@@ -17,6 +17,11 @@
 
 using namespace lbm;
 
+// Fibers of a context.  No kernel sets these bounds (the rigid update takes a
+// wave and fixed LDS for each fiber); they are the documented range, up to
+// which the forms of a step are tested and timed.
+constexpr int MAX_FIBERS = 303, MAX_FIBERS_CONTACT = 248;
+
 struct lbm_ctx {
     lbm_params p{};
     std::string err;
@@ -733,8 +738,8 @@ lbm_status lbm_add_fiber(lbm_ctx *c, const lbm_fiber *f, int32_t *id)
         if (!per && (f->center[k] - ext < 1.0 || f->center[k] + ext > n[k] - 2.0))
             return fail(c, LBM_E_GEOM, "fiber within one cell of a wall");
     }
-    if ((c->np + 1) * NACC * 8 > 65536) return fail(c, LBM_E_ARG, "at most 302 fibers per context");
-    if (c->p.contact_stiffness > 0.0 && (c->np + 1) * (NACC + 6) * 8 > 65536)
+    if (c->np >= MAX_FIBERS) return fail(c, LBM_E_ARG, "at most 303 fibers per context");
+    if (c->p.contact_stiffness > 0.0 && c->np >= MAX_FIBERS_CONTACT)
         return fail(c, LBM_E_ARG, "at most 248 fibers per context with contacts");
     const PConst pc = fiber_constants(f->length, f->radius, f->density_ratio * c->p.rho0, f->shape, f->force,
                                       f->torque);
@@ -1230,7 +1235,7 @@ lbm_status lbm_load(const char *path, void *stream, lbm_ctx **out)
     get(&steps, 8);
     get(&np, 4);
     get(&stale, 4);
-    if (!ok || steps < 0 || np < 0 || np > 302) {
+    if (!ok || steps < 0 || np < 0 || np > MAX_FIBERS) {
         std::fclose(fp);
         return LBM_E_ARG;
     }
