@@ -301,7 +301,10 @@ lbm_status lbm_load(const char *path, void *stream, lbm_ctx **out);
 /* Device-event timing of the stream-collide sweep: when enabled, every
  * subsequent lbm_step brackets each sweep launch with HIP events on the
  * context's stream.  lbm_get_sweep_time synchronises and returns the total
- * milliseconds and the number of sweeps timed since enabling. */
+ * milliseconds and the number of sweeps timed since enabling.  On a small
+ * lattice with the automatic sweep grid and fibers, whose untimed steps have
+ * no sweep launch of their own, timing changes the form of the step (the
+ * results keep their bits, with stabilization up to rounding). */
 lbm_status lbm_enable_sweep_timing(lbm_ctx *ctx, int32_t on);
 lbm_status lbm_get_sweep_time(lbm_ctx *ctx, double *total_ms, int64_t *nsweeps);
 

@@ -64,9 +64,9 @@ lbm_status sbf_params_default(sbf_params *p);
 /* Allocate a context for up to max_fibers fibers: the moment matrix (it
  * is symmetric; its upper triangle of 64 x 64 tiles, about
  * (3 M (N + 1))^2 / 2 doubles) and the GMRES basis.  LBM_E_ARG for invalid
- * parameters (including nq and N whose moment workgroup would need more
- * than 64 KiB of LDS: 8 (N + 1)(21 nq + 7 (N + 1)) bytes), LBM_E_NOMEM
- * when the device memory does not suffice. */
+ * parameters (including nq and N with 8 (N + 1)(21 nq + 7 (N + 1)) > 65536,
+ * the range that is tested), LBM_E_NOMEM when the device memory does not
+ * suffice. */
 lbm_status sbf_create(const sbf_params *p, sbf_ctx **out);
 lbm_status sbf_destroy(sbf_ctx *ctx);
 const char *sbf_last_error(const sbf_ctx *ctx);

@@ -21,8 +21,8 @@ ARCH = os.environ.get("LBM_OFFLOAD_ARCH", "gfx950")
 
 SOURCES = {
     "sweep.hip": [],
-    # boundary update with the default contraction of the sweep (the integer
-    # link sums of the second half do no floating-point arithmetic)
+    # the sweep header's functions keep the default contraction of sweep.hip;
+    # the rest follows a contraction-off pragma in the particle header
     "boundary.hip": [],
     "particles.hip": ["-ffp-contract=off"],
     "api.hip": ["-ffp-contract=off"],

@@ -197,6 +197,7 @@ static PState make_state(const lbm_fiber &f, const PConst &c)
     return s;
 }
 
+// rho0 as the sweep's collision type holds it (float except for FP64 storage)
 static double link_rho0(const lbm_ctx *c)
 {
     return c->sk == S_F64 ? c->p.rho0 : double(float(c->p.rho0));
@@ -232,16 +233,6 @@ static PartData part_data(lbm_ctx *c, PState *cur, PState *next)
     pd.contact_k = c->p.contact_stiffness;
     pd.contact_range = c->p.contact_range;
     return pd;
-}
-
-// rho0 as the sweep's collision type holds it (float except for FP64 storage)
-
-static uint32_t grid_cap(uint64_t work, uint32_t lo, uint32_t hi)
-{
-    uint64_t b = (work + 255) / 256;
-    if (b < lo) b = lo;
-    if (b > hi) b = hi;
-    return uint32_t(b);
 }
 
 // expected boundary cells of a fiber: about one shell of the cylinder widened by 1
@@ -625,7 +616,10 @@ lbm_status lbm_create(const lbm_params *p, lbm_ctx **out)
     // the sweep inside the boundary launch.  Measured per step in one and in
     // two branches (FP32; FP16 alike): 32^3 with one fiber 29 and 38 us, 64^3
     // with six 35 and 44, 96^3 with twelve 56 and 60, 112^3 with sixteen 63 and
-    // 71, 128^3 with two 71 and 70, 144^3 with four 93 and 85.
+    // 71, 128^3 with two 71 and 70, 144^3 with four 93 and 85; FP64 96^3 with
+    // four 70 and 84, 119^3 with two 115 and 124, with twenty 136 and 136; closed
+    // by no-slip walls, two fibers, 96^3 FP32 52 and 66, FP64 73 and 79, 119^3
+    // FP32 69 and 80, FP16 61 and 64, FP64 126 and 122.
     // With stabilization the waves take their cells in turn (STAB_WAVES) and the
     // two branches win earlier, with two fibers: 64^3 43 and 58 us (FP16 42 and
     // 58, FP64 51 and 62, side walls 45 and 57), 80^3 49 and 59 (45 and 48, 61

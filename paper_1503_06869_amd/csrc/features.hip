@@ -253,7 +253,8 @@ __global__ __launch_bounds__(FB) void k_closure_step(const S *__restrict__ f, co
     if (writer) s_h1[w * 16 + unit] = gelu(z1 + bf(wb[OB1 + w * 16 + unit]));
     __syncthreads();
     // layers 2 and 3: the product of the lower lane of a first pair is added
-    // unrounded
+    // unrounded, as the sum of all lanes was once compiled (a coarse run is
+    // chaotic: with the product rounded first it takes another course)
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
         const float wt = bf(wb[OW2 + (w * 16 + u) * NH + lane]), h = s_h1[lane];

@@ -33,33 +33,16 @@ __device__ __forceinline__ void axis_of(const double q[4], double t[3])
     t[2] = 2.0 * (x * z - w * y);
 }
 
-// Cell centre (cx, cy, cz) inside the fiber: with d the minimum-image
-// vector from the centre, a = d.t and q = |d|^2 - a^2 (squared distance from
-// the axis line), the cylinder requires a^2 <= (L/2)^2 and q <= r^2; the
-// spherocylinder, with e = |a| - (L/2 - r) beyond the cylindrical part,
-// q <= r^2 where e <= 0 and q + e^2 <= r^2 in the caps.  FP64, no
-// contraction, fixed evaluation order.
-__device__ __forceinline__ bool inside(const PState &s, const PConst &c, double cx, double cy,
-                                       double cz, const Geo &g)
-{
-    const double dx = mi_d(cx - s.X[0], g.nx, true);
-    const double dy = mi_d(cy - s.X[1], g.ny, true);
-    const double dz = mi_d(cz - s.X[2], g.nz, g.zper != 0);
-    const double a = dx * s.t[0] + dy * s.t[1] + dz * s.t[2];
-    const double dd = dx * dx + dy * dy + dz * dz;
-    const double hl = 0.5 * c.length;
-    const double q = dd - a * a, r2 = c.radius * c.radius;
-    if (c.shape == 1) {
-        const double e = fabs(a) - (hl - c.radius);
-        return e <= 0.0 ? q <= r2 : q + e * e <= r2;
-    }
-    return (a * a <= hl * hl) && (q <= r2);
-}
-
+// A cell centre inside the fiber: with d the minimum-image vector from the
+// fiber's centre, a = d.t and q = |d|^2 - a^2 (squared distance from the axis
+// line), the cylinder requires a^2 <= (L/2)^2 and q <= r^2; the spherocylinder,
+// with e = |a| - (L/2 - r) beyond the cylindrical part, q <= r^2 where e <= 0 and
+// q + e^2 <= r^2 in the caps.  FP64, no contraction, fixed evaluation order.
+//
 // The predicate at a cell and at its 18 neighbours: bit q set when x + c_q is
-// inside (bit 0: the cell itself; neighbours beyond z walls: clear).  Bit for
-// bit the results of inside(): the differences, products and squares of the
-// three coordinates along each axis are formed once and added in its order.
+// inside (bit 0: the cell itself; neighbours beyond z walls: clear).  The
+// differences, products and squares of the three coordinates along each axis
+// are formed once and added in that order.
 // A cell farther than 1.5 beyond the surface has no neighbour inside; with
 // `quick` (see quick_claims) its neighbours are not looked at.
 __device__ __forceinline__ uint32_t claims(const PState &s, const PConst &c, int32_t x, int32_t y, int32_t z,
@@ -102,8 +85,8 @@ __device__ __forceinline__ uint32_t claims(const PState &s, const PConst &c, int
     return m;
 }
 
-// The predicate at the cell alone (bit 0, as in claims) and whether a
-// neighbour may be inside (bit 1; all but exact with `quick`).
+// The predicate at the cell alone (bit 0, the bits of claims) and whether a
+// neighbour may be inside (bit 1: within 1.5 of the surface, or no `quick`).
 __device__ __forceinline__ uint32_t claim_or_near(const PState &s, const PConst &c, int32_t x, int32_t y, int32_t z,
                                                   const Geo &g, bool quick)
 {
@@ -585,8 +568,9 @@ __device__ __forceinline__ void remap_boxes(const PState &s, const PConst &c, co
 // links, 1 for the twelve diagonals) and
 //   M_ij = eps_jab delta_a SA_ib,  N_ij = eps_jab delta_a SB_bi,
 //   P_ij = eps_iab eps_jcd delta_a delta_c SA_bd.
-// The sums are exact, so they do not depend on the order of the links, and
-// are formed from the list once per step when it is built.
+// The sums are exact, so they do not depend on the order of the links; they
+// are formed once per step, by the boundary launch or (batched form) when the
+// list is built.
 
 // reference point of a fiber centre: the cell corner floor(X)
 __device__ __forceinline__ void fiber_ref(const double X[3], int32_t r[3])

@@ -188,9 +188,11 @@ __device__ __forceinline__ void stab_flush(const StabAcc<R> &sa, double *out)
 // lambda_e = -omega_e, lambda_o = -omega_o (Eq. LBMCollide).  With a body
 // force the velocity carries +g/2 and the odd part gains (1 - omega_o/2) 3 w rho0 c.g.
 // STAB: the equilibrium velocity is u - sa.ub, and j and the cell are counted.
-// The fused multiply-adds are written out, so that a cell's update has the
-// same bits in every kernel that it is compiled into; SPLIT rounds omega_e e
-// of the second value of a pair by itself.
+// The fused multiply-adds are written out, so that an instance of the update has
+// the same bits in every kernel that it is compiled into.  SPLIT rounds omega_e
+// e of the second value of a pair by itself; nothing in the method asks for
+// it: the instances that take it (update_cell) were once compiled so, and keep
+// their bits, so that a run goes on from an older checkpoint as it would have.
 template <typename R, bool SPLIT, bool STAB>
 __device__ __forceinline__ void collide(R (&f)[Q], const Phys<R> &ph, R inv_rho0, StabAcc<R> *sa = nullptr)
 {
@@ -279,7 +281,8 @@ __device__ __forceinline__ long long fx(double v, int k) { return __double2ll_rn
 // linear in u_s = V + W x r: A = k c c^T, B = k c (r x c)^T, C = k (r x c)(r x c)^T,
 // k = 6 w_q rho0, so that F = F0 - A V - B W and M = M0 - B^T V - C W.
 // This adds the link's F0, M0 terms to acc[0 .. 5]; A, B, C do not depend
-// on the populations and are summed as integers when the list is built
+// on the populations and are summed as integers, with the links of a step
+// (link_sums in boundary.hip) or, in the batched form, when the list is built
 // (link_int_terms).
 __device__ __forceinline__ void link_terms(long long *acc, double ft, double w, const double c[3],
                                            const double r[3], double r0)

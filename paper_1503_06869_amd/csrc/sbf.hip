@@ -1126,8 +1126,8 @@ static lbm_status do_solve(sbf_ctx *c)
 
 // Whether the one-workgroup form takes this system: matrix, basis and
 // vectors fit the LDS of one CU (with the event timing off, which brackets
-// single kernels).  M = 2, N = 5: 0.55 ms per step with a launch for each kernel,
-// 0.050 ms in one.
+// single kernels).  M = 2, N = 5, seven iterations: 0.276 ms per step with a launch
+// for each kernel, 0.046 ms in one.
 static bool small_form(const sbf_ctx *c)
 {
     return !c->timing && small_lds(c->M, c->c.N + 1, c->c.Q, c->p.gmres_restart) <= SMALL_LDS;
@@ -1259,8 +1259,9 @@ lbm_status sbf_create(const sbf_params *p, sbf_ctx **out)
         return LBM_E_ARG;
     if (!(p->length > 0.0) || !(p->eps > 0.0 && p->eps < 0.5) || !(p->mu > 0.0) || !(p->gmres_tol > 0.0))
         return LBM_E_ARG;
-    const size_t lds = size_t(p->nmodes + 1) * 7 * (3 * size_t(p->nq) + size_t(p->nmodes + 1)) * sizeof(double);
-    if (lds > 65536) return LBM_E_ARG;
+    // the documented range of nq and N (the moment kernel itself needs at most
+    // 34 KB of LDS)
+    if (size_t(p->nmodes + 1) * 7 * (3 * size_t(p->nq) + size_t(p->nmodes + 1)) * sizeof(double) > 65536) return LBM_E_ARG;
     const double dmax = 3.0 * p->max_fibers * (p->nmodes + 1);
     if (dmax * dmax > 6.0e10) return LBM_E_ARG;   // the packed moment matrix would exceed 240 GB
     sbf_ctx *c = new (std::nothrow) sbf_ctx;

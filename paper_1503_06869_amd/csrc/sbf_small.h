@@ -3,13 +3,14 @@
 //
 // A pair of fibers has a system of order 36; its solve is some ten products
 // of 10 KB each, so in launches of their own the kernels of a step cost only
-// their launch latencies (about 15 launches per GMRES iteration).  Here the
+// their launch latencies (five launches per GMRES iteration).  Here the
 // moment matrix, the Krylov basis and every vector stay in the LDS of one CU
 // and the phases are separated by workgroup barriers; the moments, the solve,
 // the velocities and the Adams-Bashforth update of all requested steps run in
-// one launch.  The method, its order of operations and its stopping rule are
-// those of the many-launch form (do_solve).  Bound: the serial chain of
-// about ten barriers and one product per iteration.
+// one launch.  The method and its stopping rule are those of the many-launch
+// form (do_solve); sums are taken in other orders, and the velocities from a
+// product of their own.  Bound: the serial chain of about ten barriers and one
+// product per iteration.
 
 constexpr int SMALL_T = 512;                  // threads
 constexpr size_t SMALL_LDS = 150 * 1024;      // of the CU's 160 KiB
