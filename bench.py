@@ -44,8 +44,8 @@ HBM_PEAK_GBS = 8000.0
 # scaled by the counters' readings for a plain copy of known size.  Valid only
 # for the sources it was measured on (SHA-1 of sweep.hip followed by
 # lbm_sweep_dev.h, below); otherwise reported null.
-SWEEP_TRAFFIC = {"sweep_sha1": "eab16654fc5ad227e92e0626921d60e2b7133355",
-                 "bytes_per_launch": 2.5730e+09}
+SWEEP_TRAFFIC = {"sweep_sha1": "62770086b9293ef6db4243d804a34b34f415cdbc",
+                 "bytes_per_launch": 2.5729e+09}
 # algorithmic bytes per lattice update of the bulk sweep: 19 loads + 19
 # stores of the population type + the 1-byte cell flag
 BYTES_PER_LUP = {"f32": 19 * 4 * 2 + 1, "f16": 19 * 2 * 2 + 1, "bf16": 19 * 2 * 2 + 1,
