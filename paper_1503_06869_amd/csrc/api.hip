@@ -50,6 +50,7 @@ struct lbm_ctx {
     long long *mea = nullptr;
     uint32_t *seg_off = nullptr, *seg_cap = nullptr, *seg_cnt = nullptr;
     int nslab = 4, bpf = 1;
+    bool map_queue = false;   // k_map collects the cells near a surface
     double *traj = nullptr;
     int64_t *traj_pos = nullptr;
     double *ft = nullptr, *hist = nullptr;
@@ -219,6 +220,7 @@ static PartData part_data(lbm_ctx *c, PState *cur, PState *next)
     pd.seg_cap = c->seg_cap;
     pd.seg_cnt = c->seg_cnt;
     pd.nslab = c->nslab;
+    pd.queue = c->map_queue ? 1 : 0;
     pd.traj = c->traj;
     pd.traj_pos = c->traj_pos;
     pd.ft_out = c->ft;
@@ -268,6 +270,7 @@ static lbm_status upload_particles(lbm_ctx *c)
     // within sqrt(2) of its cylinder; bound them by the cylinder widened by 2.5
     std::vector<uint32_t> soff(np), scap(np);
     double total = 0.0, maxsurf = 0.0;
+    uint32_t maxcap = 0;
     for (int i = 0; i < np; ++i) {
         const double r = c->fib[i].radius + 2.5, L = c->fib[i].length + 5.0;
         const double cap = 1.25 * (M_PI * r * r * L + 4.0 * M_PI * r * r) + 256.0;
@@ -275,9 +278,16 @@ static lbm_status upload_particles(lbm_ctx *c)
         scap[i] = uint32_t(cap);
         total += double(scap[i]);
         maxsurf = std::max(maxsurf, shell_cells(c->fib[i]));
+        maxcap = std::max(maxcap, scap[i]);
     }
     if (total >= 4294967295.0) return fail(c, LBM_E_ARG, "boundary list too large");
     c->list_cap = uint32_t(total);
+    // The mapping's queue (k_map) pays with many fibers, or where the blocks of a
+    // fiber have more than a round or two of cells: step in us without and with
+    // it at entries of the largest fiber's segment, FP32: 2243 (32^3) 29.7 and
+    // 30.6, 4176 (three fibers) 50.5 and 50.3, 7545 38.0 and 35.3, 8386 61.5 and
+    // 58.9, 17622 69 and 64, 117550 140 and 116, 369417 420 and 355.
+    c->map_queue = np >= 4 || maxcap >= 6000u;
     // The 4096 workgroups of the 16-bit sweep fill every register of the card,
     // and the particle branch finds room only as they end: with 64 fibers at
     // 256^3 the odd boundary launch took 296 us, the mapping 250, and the branch
@@ -447,16 +457,17 @@ static void launch_one_step(lbm_ctx *c, int64_t step_index, bool with_events, hi
     // longer goes first.  A resident grid-stride bulk grid (up to 1024
     // workgroups, FP32/FP64) goes first over a lattice that is large against
     // the boundary list (160^3 with 16 fibers 135 us a step, 141 after the
-    // boundary launch) or large itself, beyond the memory-side cache (192^3 with
-    // 100 fibers 346 and 355 us, 256^3 with 200 688 and 733, 320^3 with 250 1140
-    // and 1240; FP64 256^3 with 300 1455 and 1516), since all its workgroups
-    // must start together.  The boundary launch goes first when the bulk grid
-    // is large (16-bit storage: it would hold the boundary workgroups off
-    // until it drains) or a lattice is small in both ways, so that the particle
-    // branch is the longer one (128^3 with 200 fibers 142 and 150 us, 160^3 with
-    // 100 178 and 186, 176^3 with 60 214 and 220).
-    const bool bulk_first =
-        c->sweep_grid <= 1024u && (uint64_t(c->g.ncell) >= 32ull * c->list_cap || c->g.ncell >= 6000000u);
+    // boundary launch), since all its workgroups must start together; in FP32,
+    // where the boundary launch leaves it room (BND_LDS), also over one beyond
+    // the memory-side cache with fibers of ordinary size (192^3 with 100 fibers
+    // 346 and 355 us, 256^3 with 200 688 and 733, 320^3 with 250 1140 and 1240;
+    // but 192^3 with one of radius 30 and length 80 418 and 410, FP64 707 and
+    // 630).  Otherwise the boundary launch goes first: the bulk grid is large
+    // (16-bit storage: it would hold the boundary workgroups off until it
+    // drains) or the particle branch the longer one (128^3 with 200 fibers 142
+    // and 150 us, 160^3 with 100 178 and 186, 176^3 with 60 214 and 220).
+    const bool vast = c->sk == S_F32 && c->g.ncell >= 6000000u && c->list_cap <= 32768ull * uint64_t(c->np);
+    const bool bulk_first = c->sweep_grid <= 1024u && (uint64_t(c->g.ncell) >= 32ull * c->list_cap || vast);
     const uint32_t bnd_lds = c->sk == S_F32 ? BND_LDS : 0u;
     if (e == hipSuccess && !bulk_first)
         e = launch_boundary(c->sk, odd, c->f, c->g, c->ph, b, c->st2, su, sp_b, nullptr, 0u, bnd_lds);

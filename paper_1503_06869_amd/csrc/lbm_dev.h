@@ -217,6 +217,7 @@ struct PartData {
     DevCounters *ctr;
     uint32_t list_cap;
     int32_t nslab;             // blocks per fiber (z-planes of a box dealt round robin)
+    int32_t queue;             // the mapping collects the cells near a surface (k_map)
     long long *mea;            // [np][NACC] fixed-point momentum-exchange sums
     const uint32_t *seg_off;   // [np] list segment of each fiber: start
     const uint32_t *seg_cap;   // [np] capacity

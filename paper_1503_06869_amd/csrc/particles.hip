@@ -280,16 +280,15 @@ __device__ __forceinline__ bool owned_here(const RegionTable &t, int k, int32_t 
 // 1.5 of a surface only.  These are about a third of a region's cells: with
 // QUEUE a wave collects them and tests 64 at a time, one to a lane, instead
 // of sitting through the tests for the few of each 64 cells that need them.
-// The detour costs a single fiber, whose blocks have a round of cells or two,
-// 0.8 of 9.3 us.  Step in us without and with the queue: 32^3 one fiber 29.7,
-// 30.6; 48^3 two 37.3, 37.6; 64^3 six 45.0, 44.3; 93^3 BF16 ten 65.0, 64.0; 128^3
-// with 200 152, 140, FP16 with 300 182, 165; 256^3 FP16 with 300 482, 459.
+// The detour costs 0.8 of 9.3 us where a fiber's blocks have a round of cells or
+// two (the rule is where the fibers are set up).  Step in us without and with
+// the queue: 64^3 six fibers 45.0, 44.3; 93^3 BF16 ten 65.0, 64.0; 128^3 with 200
+// 152, 140, FP16 with 300 182, 165; 256^3 FP16 with 300 482, 459.
 // The list is cut into one segment per fiber; a block
 // stages the boundary cells it finds in all its planes in LDS and reserves a
 // range of its fiber's segment with a single atomic (cells beyond the stage
 // are appended one by one).  advance: end of a time step (the step counter).
 constexpr int LSTAGE = 1024;
-constexpr int QUEUE_FIBERS = 4;   // fibers from which the queue pays
 
 template <typename S, bool QUEUE>
 __global__ __launch_bounds__(256) void k_map(S *__restrict__ f, int32_t *__restrict__ pid,
@@ -453,7 +452,7 @@ hipError_t launch_map(int sk, bool next_odd, void *f, int32_t *pid, uint8_t *fla
     const dim3 gr(pd.np * pd.nslab), bl(256);
     auto go = [&](auto *fp) {
         using S = std::remove_pointer_t<decltype(fp)>;
-        if (pd.np >= QUEUE_FIBERS)
+        if (pd.queue)
             hipLaunchKernelGGL((k_map<S, true>), gr, bl, 0, st, fp, pid, flags, list_cell, list_mask, pd, g, no, rho0, scale, ad);
         else
             hipLaunchKernelGGL((k_map<S, false>), gr, bl, 0, st, fp, pid, flags, list_cell, list_mask, pd, g, no, rho0, scale, ad);
