@@ -440,7 +440,8 @@ static void launch_one_step(lbm_ctx *c, int64_t step_index, bool with_events, hi
     if (c->nbulk && !with_events) {
         // small lattice: one branch, the sweep inside the boundary launch
         if (e == hipSuccess)
-            e = launch_boundary(c->sk, odd, c->f, c->g, c->ph, b, c->st, su, sp, c->flags[step_index & 1], c->nbulk, 0u);
+            e = launch_boundary(c->sk, odd, c->f, c->g, c->ph, b, c->st, su, sp, c->flags[step_index & 1], c->nbulk,
+                                0u, false);
         if (e == hipSuccess) e = launch_rigid(pd, c->g, c->st);
         if (e == hipSuccess)
             e = launch_map(c->sk, !odd, c->f, c->pid, c->flags[(step_index + 1) & 1], c->list_cell, c->list_mask, pd,
@@ -469,13 +470,21 @@ static void launch_one_step(lbm_ctx *c, int64_t step_index, bool with_events, hi
     const bool vast = c->sk == S_F32 && c->g.ncell >= 6000000u && c->list_cap <= 32768ull * uint64_t(c->np);
     const bool bulk_first = c->sweep_grid <= 1024u && (uint64_t(c->g.ncell) >= 32ull * c->list_cap || vast);
     const uint32_t bnd_lds = c->sk == S_F32 ? BND_LDS : 0u;
+    // FP64 behind the sweep: the boundary launch that fits beside it.  us a step
+    // without and with, at cells over list capacity: 128^3 158 and 153 (31), 192^3
+    // 570 and 537 (41), 256^3 1280 and 1250 (60), 1201 and 1118 (251), 160^3 305 and
+    // 275 (510); where the boundary launch is the longer branch its spills tell:
+    // 128^3 201 and 209 (5), 160^3 374 and 379 (14).  With walls on the sides or free
+    // slip the sweep leaves less idle, and small lattices lose: 128^3 145 and 148,
+    // 160^3 279 and 275, 256^3 1192 and 1170.
+    const bool lean = c->sk == S_F64 && bulk_first && (c->g.ncell >= 4000000u || !(c->g.xw || c->g.yw || c->g.zs));
     if (e == hipSuccess && !bulk_first)
-        e = launch_boundary(c->sk, odd, c->f, c->g, c->ph, b, c->st2, su, sp_b, nullptr, 0u, bnd_lds);
+        e = launch_boundary(c->sk, odd, c->f, c->g, c->ph, b, c->st2, su, sp_b, nullptr, 0u, bnd_lds, lean);
     if (e == hipSuccess)
         e = launch_sweep(c->sk, odd, c->f, c->flags[step_index & 1], c->g, c->ph, c->sweep_grid, c->st,
                          with_events ? e0 : nullptr, with_events ? e1 : nullptr, su, sp, c->bulk_lds);
     if (e == hipSuccess && bulk_first)
-        e = launch_boundary(c->sk, odd, c->f, c->g, c->ph, b, c->st2, su, sp_b, nullptr, 0u, bnd_lds);
+        e = launch_boundary(c->sk, odd, c->f, c->g, c->ph, b, c->st2, su, sp_b, nullptr, 0u, bnd_lds, lean);
     if (e == hipSuccess) e = launch_rigid(pd, c->g, c->st2);
     if (e == hipSuccess)
         e = launch_map(c->sk, !odd, c->f, c->pid, c->flags[(step_index + 1) & 1], c->list_cell, c->list_mask, pd, c->g,

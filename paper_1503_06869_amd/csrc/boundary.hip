@@ -122,8 +122,12 @@ __device__ __forceinline__ void wave_sum4(const double (&v)[4], double *out)
 // time, strided).  STAB: momentum stabilization (mean velocity stab[0..2]; every
 // wave writes its sums to a slot of part, the bulk waves first).  XYW: walls on
 // the x and/or y faces.
-template <typename S, bool ODD, bool STAB, bool XYW>
-__global__ __launch_bounds__(64, 2) void k_boundary(S *__restrict__ f, Geo g, Phys<typename St<S>::R> ph, BndData b,
+// LEAN (FP64): 168 VGPRs, for 140 to 196 bytes of spills.  At its own 217 and 208
+// no wave fits beside the two of the FP64 sweep (148 and 164 of 512 each), and
+// behind a sweep that starts first the whole launch waits for its end (256^3 with
+// 16 fibers 1201 us a step, 1118 so).
+template <typename S, bool ODD, bool STAB, bool XYW, bool LEAN = false>
+__global__ __launch_bounds__(64, LEAN ? 3 : 2) void k_boundary(S *__restrict__ f, Geo g, Phys<typename St<S>::R> ph, BndData b,
                                                     const double *stab, double *part,
                                                     const uint8_t *__restrict__ flags, uint32_t nbulk)
 {
@@ -261,12 +265,23 @@ __global__ __launch_bounds__(64, 2) void k_boundary(S *__restrict__ f, Geo g, Ph
 template <typename S>
 static hipError_t boundary_t(bool odd, void *f, const Geo &g, const Phys<double> &ph, const BndData &b,
                              hipStream_t st, const double *stab, double *part, const uint8_t *flags, uint32_t nbulk,
-                             uint32_t lds)
+                             uint32_t lds, bool lean)
 {
     using R = typename St<S>::R;
     const Phys<R> p = cast_phys<R>(ph);
     const dim3 grid(uint32_t(b.np * b.bpf) + nbulk), bl(64);
     const int mode = (odd ? 1 : 0) | (stab ? 2 : 0) | ((g.xw || g.yw || g.zs) ? 4 : 0);
+    if constexpr (std::is_same_v<S, double>) {
+        if (lean && !stab) {
+            switch (mode) {
+            case 0: hipLaunchKernelGGL((k_boundary<S, false, false, false, true>), grid, bl, lds, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
+            case 1: hipLaunchKernelGGL((k_boundary<S, true, false, false, true>), grid, bl, lds, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
+            case 4: hipLaunchKernelGGL((k_boundary<S, false, false, true, true>), grid, bl, lds, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
+            default: hipLaunchKernelGGL((k_boundary<S, true, false, true, true>), grid, bl, lds, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
+            }
+            return hipGetLastError();
+        }
+    }
     switch (mode) {
     case 0: hipLaunchKernelGGL((k_boundary<S, false, false, false>), grid, bl, lds, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
     case 1: hipLaunchKernelGGL((k_boundary<S, true, false, false>), grid, bl, lds, st, (S *)f, g, p, b, stab, part, flags, nbulk); break;
@@ -282,14 +297,14 @@ static hipError_t boundary_t(bool odd, void *f, const Geo &g, const Phys<double>
 
 hipError_t launch_boundary(int sk, bool odd, void *f, const Geo &g, const Phys<double> &ph, const BndData &b,
                            hipStream_t st, const double *stab, double *part, const uint8_t *flags, uint32_t nbulk,
-                           uint32_t lds)
+                           uint32_t lds, bool lean)
 {
     if (b.np <= 0 || b.bpf <= 0) return hipSuccess;
     switch (sk) {
-    case S_F32: return boundary_t<float>(odd, f, g, ph, b, st, stab, part, flags, nbulk, lds);
-    case S_F16: return boundary_t<_Float16>(odd, f, g, ph, b, st, stab, part, flags, nbulk, lds);
-    case S_BF16: return boundary_t<bf16s>(odd, f, g, ph, b, st, stab, part, flags, nbulk, lds);
-    default: return boundary_t<double>(odd, f, g, ph, b, st, stab, part, flags, nbulk, lds);
+    case S_F32: return boundary_t<float>(odd, f, g, ph, b, st, stab, part, flags, nbulk, lds, lean);
+    case S_F16: return boundary_t<_Float16>(odd, f, g, ph, b, st, stab, part, flags, nbulk, lds, lean);
+    case S_BF16: return boundary_t<bf16s>(odd, f, g, ph, b, st, stab, part, flags, nbulk, lds, lean);
+    default: return boundary_t<double>(odd, f, g, ph, b, st, stab, part, flags, nbulk, lds, lean);
     }
 }
 

@@ -279,10 +279,11 @@ hipError_t launch_sweep(int sk, bool odd, void *f, const uint8_t *flags, const G
 // (boundary.hip); stab as for the sweep.  nbulk > 0: the bulk sweep too, by
 // nbulk waves of 64 cells each, or with stab as many as it takes (flags; part:
 // nbulk slots of the bulk waves first).  lds: bytes of LDS that each wave
-// reserves beside its own, to bound how many of them a CU holds
+// reserves beside its own, to bound how many of them a CU holds.  lean: FP64
+// without stab in fewer registers, to run beside the sweep
 hipError_t launch_boundary(int sk, bool odd, void *f, const Geo &g, const Phys<double> &ph, const BndData &b,
                            hipStream_t st, const double *stab, double *part, const uint8_t *flags, uint32_t nbulk,
-                           uint32_t lds);
+                           uint32_t lds, bool lean);
 // Reserved beside the FP32 sweep: with the wave's own 9472, four waves in the
 // 160 K of a CU.  Step in us at 0, 18000, 24000, 31000, 42000 and 70000 bytes:
 // 256^3 with 110 fibers 716, 601, 657, 660, 650, 646; 200 fibers 912, 692, 689,
